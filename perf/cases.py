@@ -113,12 +113,13 @@ def _planted(g, sizes):
     start = torch.cumsum(sizes, 0) - sizes
     com = torch.repeat_interleave(torch.arange(k, device=DEV), sizes)
     r = torch.rand(n, generator=g, device=DEV, dtype=f64)
-    theta = torch.clamp((1 - r) ** (-1 / 1.5), max=max(2.0, n / k / 8))
-    cum = torch.zeros(n + 1, dtype=f64, device=DEV)
+    # whole numbers: their sums do not depend on the order they are taken in
+    theta = (1024 * torch.clamp((1 - r) ** (-1 / 1.5), max=max(2.0, n / k / 8))).long()
+    cum = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
     cum[1:] = torch.cumsum(theta, 0)
 
     def heavy(lo, hi):  # a vertex of the id range [lo, hi), by weight
-        x = cum[lo] + torch.rand(lo.numel(), generator=g, device=DEV, dtype=f64) * (cum[hi] - cum[lo])
+        x = cum[lo] + (torch.rand(lo.numel(), generator=g, device=DEV, dtype=f64) * (cum[hi] - cum[lo])).long()
         return torch.minimum(torch.clamp(torch.searchsorted(cum, x, right=True) - 1, min=0), hi - 1)
 
     u0 = torch.arange(n, device=DEV).repeat_interleave(PICKS)
@@ -329,10 +330,14 @@ def prepare(case, seed):
 # ---- one pass ------------------------------------------------------------------
 def _named(C):
     """Communities named by their smallest member."""
-    c = C.long()
-    own = torch.arange(c.numel(), device=c.device)
-    low = torch.full_like(own, c.numel()).scatter_reduce_(0, c, own, "amin")
-    return low[c]
+    n = C.numel()
+    own = torch.arange(n, device=C.device)
+    label, order = torch.sort(C, stable=True)
+    head = torch.ones(n, dtype=torch.bool, device=C.device)
+    head[1:] = label[1:] != label[:-1]
+    low = torch.empty(2 * n, dtype=torch.int64, device=C.device)
+    low.scatter_(0, torch.where(head, label.long(), own + n), order)
+    return low[C.long()]
 
 
 def run(state):
