@@ -21,6 +21,8 @@
 // Weights are summed in FP64 and stored rounded to float32; the next level's
 // K' is the FP64 sum of the stored row weights.  Every sum is taken in an
 // order fixed by the input, so results do not depend on scheduling.
+#include <algorithm>
+
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -126,9 +128,13 @@ void agg_group(const AggArgs &a, const int32_t *crow, const int32_t *pos, const 
 }
 
 // ---- 4: small segments -------------------------------------------------------
-// A wavefront per segment of at most kAggSmall entries (the wavefronts take
-// 64 communities at a time, spread over the whole id range, since costly
-// segments cluster in id order): up to 64 entries are sorted in registers with a
+// A wavefront per segment of at most kAggSmall entries (a wavefront takes its
+// communities spread over the whole id range, since costly segments cluster
+// in id order; it looks at up to 64 of them at a time, one per lane).  A
+// segment is a chain of dependent steps, so a level needs as many wavefronts
+// as it has communities, up to the 32768 of the grid: with 64 communities for
+// every wavefront a level of 700 communities ran on 11 wavefronts (190 us,
+// 44 us with one each), one of 780,000 on 12,000 (4.8 ms, 3.7 ms).  Up to 64 entries are sorted in registers with a
 // bitonic network over the lanes, up to 256 with the same network over R = 2
 // or 4 registers per lane, larger ones (up to 1024) in the wavefront's LDS
 // area (more registers per lane would spill).
@@ -446,8 +452,8 @@ __global__ __launch_bounds__(256) void k_agg_small(const int64_t *seg, int64_t n
 void agg_small(const int64_t *seg, int64_t ncomm, const uint32_t *gkey, const float *gval, uint32_t *ukey,
                float *uval, double *u64, int32_t *rowlen, double *K, hipStream_t s) {
   if (ncomm > 0)
-    hipLaunchKernelGGL(k_agg_small, flat_grid(ceil_div(ncomm, kWave), 4, 8192), 256, 0, s, seg, ncomm, gkey, gval,
-                       ukey, uval, u64, rowlen, K);
+    hipLaunchKernelGGL(k_agg_small, flat_grid(ncomm, 4, 8192), 256, 0, s, seg, ncomm, gkey, gval, ukey, uval, u64,
+                       rowlen, K);
 }
 
 // ---- 5: large segments ----------------------------------------------------------
@@ -671,13 +677,15 @@ void agg_large_rows(int64_t nl, const int32_t *lc, const int64_t *tfirst, const 
 __global__ __launch_bounds__(256) void k_agg_csmall(const int64_t *seg, int64_t ncomm, const int32_t *rowlen,
                                                     const int64_t *out_off, const uint32_t *ukey, const float *uval,
                                                     const double *v64, int32_t *out_idx, float *out_w,
-                                                    double *out_w64) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t c0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave * kWave; c0 < ncomm; c0 += stride) {
+                                                    double *out_w64, int per) {
+  // a wavefront copies the rows of `per` (at most 64) consecutive communities
+  const int64_t nw = (int64_t)gridDim.x * (256 / kWave);
+  const int64_t w = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+  for (int64_t c0 = w * per; c0 < ncomm; c0 += nw * per) {
     const int64_t c = c0 + lane();
     int64_t s0 = 0, d0 = 0, len = 0;
     int r = 0;
-    if (c < ncomm) {
+    if (lane() < per && c < ncomm) {
       s0 = seg[c];
       len = seg[c + 1] - s0;
       r = rowlen[c];
@@ -722,9 +730,14 @@ void agg_compact(const int64_t *seg, int64_t ncomm, const int32_t *lc, const int
                  const int64_t *tfirst, int64_t ntl, const int32_t *rowlen, const int64_t *out_off,
                  const uint32_t *ukey, const float *uval, const uint32_t *lkey, const float *lval,
                  const double *v64, int32_t *out_idx, float *out_w, double *out_w64, hipStream_t s) {
-  if (ncomm > 0)
-    hipLaunchKernelGGL(k_agg_csmall, flat_grid(ncomm, 256, 8192), 256, 0, s, seg, ncomm, rowlen, out_off, ukey, uval,
-                       v64, out_idx, out_w, out_w64);
+  if (ncomm > 0) {
+    // rows are copied one after another by a wavefront: as many wavefronts as
+    // the grid may have before one takes more than one community (24 us to
+    // 6 us a level of 700 communities)
+    const int per = (int)std::min<int64_t>(kWave, ceil_div(ncomm, 8192 * 4));
+    hipLaunchKernelGGL(k_agg_csmall, flat_grid(ceil_div(ncomm, per), 4, 8192), 256, 0, s, seg, ncomm, rowlen, out_off,
+                       ukey, uval, v64, out_idx, out_w, out_w64, per);
+  }
   if (ntl > 0)
     hipLaunchKernelGGL(k_agg_clarge, (int)ntl, 256, 0, s, lc, lsb, tseg, tfirst, rowlen, out_off, lkey, lval,
                        v64, out_idx, out_w, out_w64);
