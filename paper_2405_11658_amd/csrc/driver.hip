@@ -42,7 +42,7 @@ enum Slot {
   A_lidx, A_lc, A_lsb, A_lse, A_ltn, A_tseg, A_hc, A_tin, A_rowlen,
   // hubs
   H_v, H_cnt, H_ch, H_tab, H_sg, H_chub, H_shub, H_tk, H_tv, H_own, H_pg, H_pc, H_soff,
-  H_fill, H_bnd, H_flag, L_act, W_keys, W_vals, W_list, W_blk,
+  H_fill, H_bnd, H_flag, L_act, W_keys, W_vals, W_list,
   // primitives
   T_tmp,
   // batch
@@ -70,7 +70,6 @@ struct DevScal {
   unsigned long long hub_scanned;
   unsigned long long sweep_work[4];  // [vertices, edges] of the move sweeps, then of the refine sweeps
   unsigned long long anext;
-  unsigned long long bnext;
 };
 
 struct Workspace {
@@ -174,15 +173,6 @@ int level_waves(const leiden_params &p, int cap, int64_t n, int pass) {
   int64_t w = n / (pass == 0 ? vpw0 : vpw1);
   w = std::max<int64_t>(1, std::min<int64_t>(w, cap));
   return (int)(w < 4 ? w : w / 4 * 4);  // whole 4-wavefront workgroups, never above cap
-}
-
-// Workgroups that sweep the level's blen vertices of degree in (hub_degree,
-// kHubDeg]: one in hub_slices of them moves at a time, as when they moved in
-// hub_slices slices; one wavefront alone (the serial sweep) stays one at a time.
-constexpr int kMaxBlockGroups = 2048;
-int block_groups(int waves, int slices, int64_t blen) {
-  if (waves <= 1) return 1;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(blen / slices, kMaxBlockGroups));
 }
 
 struct KProf;
@@ -431,7 +421,7 @@ struct Layout {
   int64_t nhub;
 };
 
-Layout level_layout(Ctx &x, const Level &g, int S, int64_t mid, int32_t *region_dev, int32_t *counts_tmp,
+Layout level_layout(Ctx &x, const Level &g, int S, int64_t hubdeg, int32_t *region_dev, int32_t *counts_tmp,
                     int32_t *scnt,
                     int32_t *soff_dev, int32_t *sfill, int32_t *vbyslice) {
   Layout L;
@@ -439,7 +429,7 @@ Layout level_layout(Ctx &x, const Level &g, int S, int64_t mid, int32_t *region_
   const int nb = S * kNB;
   x.zero(counts_tmp, nb);
   x.zero(scnt, S);
-  slice_hist(g.off, g.n, S, mid, counts_tmp, scnt, x.s);
+  slice_hist(g.off, g.n, S, hubdeg, counts_tmp, scnt, x.s);
   x.launched("slice_hist");
   int32_t *hp = (int32_t *)x.pin();
   x.check(hipMemcpyAsync(hp, counts_tmp, sizeof(int32_t) * nb, hipMemcpyDeviceToHost, x.s), "D2H");
@@ -490,7 +480,7 @@ struct HubHost {
   std::vector<int64_t> hs, qs, gs;  // per-slice starts (S+1): hubs, chunks, segments
 };
 
-HubHost hub_plan(Ctx &x, const Level &g, int S, const Layout &B) {
+HubHost hub_plan(Ctx &x, const Level &g, int S, int64_t hubdeg, const Layout &B) {
   HubHost H;
   memset(&H.p, 0, sizeof(H.p));
   H.hs.assign(S + 1, 0);
@@ -508,7 +498,7 @@ HubHost hub_plan(Ctx &x, const Level &g, int S, const Layout &B) {
   x.check(hipMemcpyAsync(hsoff, up, sizeof(int32_t) * (S + 1), hipMemcpyHostToDevice, x.s), "H2D");
   x.zero(hfill, S);
   H.p.hubv = x.get<int32_t>(H_v, nh);
-  hub_find(g.off, g.n, S, kHubDeg, hsoff, hfill, H.p.hubv, x.s);
+  hub_find(g.off, g.n, S, hubdeg, hsoff, hfill, H.p.hubv, x.s);
   int64_t *cnt = x.get<int64_t>(H_cnt, 3 * (nh + 1));
   hub_sizes(g.off, H.p.hubv, nh, cnt, cnt + (nh + 1), cnt + 2 * (nh + 1), x.s);
   x.launched("hub plan");
@@ -784,9 +774,9 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
   double *tiles = x.get<double>(L_tiles, n / 256 + 2);
   uint8_t *act = x.get<uint8_t>(L_act, n);
   const bool async = p.sync_mode == 0;
-  // degree up to which a vertex is a wavefront's; up to kHubDeg it is a
-  // workgroup's, above that it moves in the hub slices
-  const int64_t hubdeg = !async ? 256 : p.hub_degree > 0 ? p.hub_degree : kHubDeg;
+  // degree above which a vertex moves in the hub slices before the sweep
+  // (asynchronous mode); the synchronous mode keeps the table-size boundary
+  const int64_t hubdeg = (async && p.hub_degree > 0) ? p.hub_degree : kHubDeg;
   const int NW = async ? (p.async_waves > 0 ? p.async_waves : kDefaultAsyncWaves) : 0;
   int *akeys = async ? x.get<int>(W_keys, (int64_t)NW * 2 * kHubDeg) : nullptr;
   double *avals = async ? x.get<double>(W_vals, (int64_t)NW * 2 * kHubDeg) : nullptr;
@@ -822,27 +812,18 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     const int64_t nl = g.n;
     const int64_t nfull = nl + niso;
     const Layout B = level_layout(x, g, NS, hubdeg, region, counts, scnt, soff, sfill, vbs);
-    const HubHost hh = hub_plan(x, g, NS, B);
+    const HubHost hh = hub_plan(x, g, NS, hubdeg, B);
     const int64_t alen = B.region[NS * kNB];  // vertices with edges
-    int64_t blen = 0;  // vertices swept by workgroups
-    int32_t *alist = nullptr, *blist = nullptr;
+    int32_t *alist = nullptr;
     if (async && alen > 0) {
       int32_t *flags = x.get<int32_t>(L_flags, nl + 1);
       int32_t *pos = x.get<int32_t>(L_map, nl + 1);
       alist = x.get<int32_t>(W_list, alen);
-      degree_flags(g.off, nl, 0, INT64_MAX, flags, x.s);
+      edge_flags(g.off, nl, flags, x.s);
       scan_i32(x, flags, pos, nl);
-      degree_list(g.off, nl, 0, INT64_MAX, pos, alist, x.s);
-      for (int sl = 0; sl < NS; ++sl) blen += B.region[sl * kNB + kNB - 1] - B.region[sl * kNB + kNB - 2];
-      if (blen > 0) {
-        blist = x.get<int32_t>(W_blk, blen);
-        degree_flags(g.off, nl, hubdeg, kHubDeg, flags, x.s);
-        scan_i32(x, flags, pos, nl);
-        degree_list(g.off, nl, hubdeg, kHubDeg, pos, blist, x.s);
-      }
-      x.launched("vertex lists");
+      edge_list(g.off, nl, pos, alist, x.s);
+      x.launched("edge list");
     }
-    const int groups = block_groups(NW, NS, blen);
     if (pass > 0) fill_u8(rng, 1, nl, x.s);
     const double Tp = tau * M2 * M2 / 2.0;
 
@@ -861,7 +842,6 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     ma.sweep_work = x.kp && x.kp->on ? sc->sweep_work : nullptr;
     ma.anext = &sc->anext; ma.akeys = akeys; ma.avals = avals;
     ma.alist = alist; ma.alen = alen;
-    ma.blist = blist; ma.blen = blen; ma.bnext = &sc->bnext;
     ma.hubdeg = hubdeg;
     ma.cached = async && nfull >= kCachedLevel;
     ma.defer = async && NW > 1;
@@ -872,11 +852,10 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     bool stalled = false;
     tm.mark(CAT_OTHER);
     for (int it = 0; it < p.max_iter; ++it) {
-      reset_iter(counts, NS * kNB, &sc->gain, &sc->moves, async ? &sc->anext : nullptr,
-                 async ? &sc->bnext : nullptr, x.s);
+      reset_iter(counts, NS * kNB, &sc->gain, &sc->moves, async ? &sc->anext : nullptr, x.s);
       if (gi) x.zero(gi, nl);
       // asynchronous mode: the hub slices of the iteration timed as one region
-      hipEvent_t th = (x.kp && async && (hh.nhub > 0 || blen > 0)) ? x.kp->begin() : nullptr;
+      hipEvent_t th = (x.kp && async && hh.nhub > 0) ? x.kp->begin() : nullptr;
       for (int sl = 0; sl < NS; ++sl) {
         ma.s = sl;
         ma.vbeg = B.soff[sl];
@@ -902,7 +881,6 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
         }
         move_apply(ma, B.region.data(), x.s);
       }
-      if (async) move_blocks(ma, groups, x.s);
       if (th) x.kp->end(th, LEIDEN_PROF_HUB_GATHER, 0, 0);
       if (async) {
         // after the hubs: the other vertices then see the hubs' new communities
@@ -963,13 +941,11 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     ra.refined = &sc->refined;
     ra.anext = &sc->anext; ra.akeys = akeys; ra.avals = avals;
     ra.alist = alist; ra.alen = alen;
-    ra.blist = blist; ra.blen = blen; ra.bnext = &sc->bnext;
     ra.hubdeg = hubdeg;
     ra.cached = async && nfull >= kCachedLevel;
     ra.defer = async && NW > 1;
     ra.sweep_work = x.kp && x.kp->on ? sc->sweep_work + 2 : nullptr;
-    reset_iter(counts, NS * kNB, nullptr, &sc->refined, async ? &sc->anext : nullptr,
-               async ? &sc->bnext : nullptr, x.s);
+    reset_iter(counts, NS * kNB, nullptr, &sc->refined, async ? &sc->anext : nullptr, x.s);
     refine_break(ra, x.s);
     x.launched("break");
     ra.hp = hh.p;
@@ -995,7 +971,6 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
       refine_accept(ra, B.region.data(), x.s);
     }
     if (async) {
-      refine_blocks(ra, groups, x.s);
       hipEvent_t t0 = x.kp ? x.kp->begin() : nullptr;
       refine_async(ra, level_waves(p, NW, alen, pass), wide_tables(g.nnz, alen), x.s);
       if (x.kp) x.kp->end(t0, LEIDEN_PROF_REFINE_SWEEP, 0, 0);

@@ -12,10 +12,8 @@
 // wavefront (degree <= 2048), and applies its best move immediately: C store,
 // Sigma atomics, neighbours marked unprocessed.  Changes to the Sigma of the
 // few communities holding a large share of the weight are summed per
-// wavefront and added every few chunks (Pend below).  Before the sweep, the
-// vertices above the wavefront's degree are swept the same way by workgroups
-// (degree <= 2048), and those of higher degree by the multi-workgroup hub
-// kernels.
+// wavefront and added every few chunks (Pend below).  Vertices of higher
+// degree are handled before the sweep by the multi-workgroup hub kernels.
 //
 // Refinement follows the same scheme: an isolated vertex of a changed bound
 // (Sigma of its community equal to its own K) looks for the best community
@@ -698,316 +696,20 @@ void refine_async(const RefineArgs &a, int waves, bool wide, hipStream_t s) {
   else launch_async(k_refine_async<4, 512, false>, k_refine_async<2, 2048, false>, a, waves, wide, s);
 }
 
-// ---- vertices of degree in (hubdeg, kHubDeg]: a workgroup each --------------------
-// Their neighbour tables do not fit a wavefront's LDS table, and a workgroup
-// with a table of its own reads all their edges at once (at most 8 a thread).
-// They were moved by the multi-workgroup hub kernels before, five launches
-// for each of 64 slices of a few vertices: ~45 us a slice with the gaps,
-// whatever the slice held.  Here the workgroups of one launch take them one
-// after another and apply each move at once, as the wavefronts of the other
-// sweep do; nblk / hub_slices workgroups run, so the same share of them moves
-// at a time as when they moved in hub_slices slices.
-constexpr int kBlk = 256;
-constexpr int kBlkSlots = 2 * (int)kHubDeg;
-constexpr int kBlkPer = (int)kHubDeg / kBlk;  // edges per thread
-constexpr int kBlkGrab = 4;                   // list positions per visit to the counter
-
-struct BlockLds {
-  int keys[kBlkSlots];
-  double vals[kBlkSlots];
-  double rd[kBlk / kWave], rs[kBlk / kWave];
-  int rc[kBlk / kWave];
-  int v[kBlkGrab], c[kBlkGrab], cb[kBlkGrab], go[kBlkGrab];
-  int64_t e0[kBlkGrab], e1[kBlkGrab];
-  double k[kBlkGrab];
-  long long base;
-  int again;
-};
-
-__device__ __forceinline__ void block_init(BlockLds &l) {
-  for (int s = threadIdx.x; s < kBlkSlots; s += kBlk) { l.keys[s] = kEmpty; l.vals[s] = 0.0; }
-  __syncthreads();
+__global__ void k_edge_flags(const int64_t *off, int64_t n, int32_t *flags) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    flags[i] = off[i + 1] > off[i];
 }
-
-// Sum over the workgroup, in every thread; r is free again after the next barrier.
-__device__ __forceinline__ double block_total(double v, double *r) {
-  v = wave_sum(v);
-  if (lane() == 0) r[threadIdx.x / kWave] = v;
-  __syncthreads();
-  return (r[0] + r[1]) + (r[2] + r[3]);
+void edge_flags(const int64_t *off, int64_t n, int32_t *flags, hipStream_t s) {
+  if (n > 0) hipLaunchKernelGGL(k_edge_flags, flat_grid(n), 256, 0, s, off, n, flags);
 }
-
-// Adds w to key's slot; the slot when this call took it, else -1.  Fewer
-// distinct keys than slots, so the probes end.
-__device__ __forceinline__ int block_slot(BlockLds &l, int key, double w) {
-  uint32_t h = mix32((uint32_t)key) & (kBlkSlots - 1);
-  for (int probe = 0; probe < kBlkSlots; ++probe) {
-    const int old = atomicCAS(&l.keys[h], kEmpty, key);
-    if (old == kEmpty || old == key) {
-      atomicAdd(&l.vals[h], w);
-      return old == kEmpty ? (int)h : -1;
-    }
-    h = (h + 1) & (kBlkSlots - 1);
-  }
-  return -1;
+__global__ void k_edge_list(const int64_t *off, int64_t n, const int32_t *pos, int32_t *list) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    if (off[i + 1] > off[i]) list[pos[i]] = (int32_t)i;
 }
-
-// Best positive-gain community among the edges' (c, x), d's own left out
-// (their weight is b): the edges summed by community in the LDS table, each
-// slot scored and cleared by the thread that took it.  Uniform results; ends
-// with the table clear and usable after the caller's next barrier.
-template <bool CA>
-__device__ __forceinline__ void block_best(BlockLds &l, const int (&c)[kBlkPer], const float (&x)[kBlkPer],
-                                           double M2, double b, double Ki, double Sd, const double *Sig, double &bg,
-                                           int &bc, double &bs) {
-  int own[kBlkPer];
-#pragma unroll
-  for (int u = 0; u < kBlkPer; ++u) own[u] = c[u] != kEmpty ? block_slot(l, c[u], (double)x[u]) : -1;
-  double S[kBlkPer];
-#pragma unroll
-  for (int u = 0; u < kBlkPer; ++u) S[u] = own[u] >= 0 ? ld_s<CA>(&Sig[c[u]]) : 0.0;
-  __syncthreads();
-  bg = 0.0;
-  bc = kNoComm;
-  bs = 0.0;
-#pragma unroll
-  for (int u = 0; u < kBlkPer; ++u) {
-    if (own[u] < 0) continue;
-    const double g = move_score(M2, l.vals[own[u]], b, Ki, S[u], Sd);
-    l.keys[own[u]] = kEmpty;
-    l.vals[own[u]] = 0.0;
-    if (g > 0.0 && better(g, c[u], bg, bc)) { bg = g; bc = c[u]; bs = S[u]; }
-  }
-  const int lc = bc;
-  wave_argmax(bg, bc);
-  const unsigned long long wl = __ballot(bc != kNoComm && lc == bc);
-  bs = __shfl(bs, wl ? __ffsll(wl) - 1 : 0);
-  const int wv = threadIdx.x / kWave;
-  if (lane() == 0) { l.rd[wv] = bg; l.rc[wv] = bc; l.rs[wv] = bs; }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kBlk / kWave; ++k)
-    if (k == 0 || better(l.rd[k], l.rc[k], bg, bc)) { bg = l.rd[k]; bc = l.rc[k]; bs = l.rs[k]; }
-}
-
-// The workgroup's next kBlkGrab list positions (uniform).
-__device__ __forceinline__ int64_t block_grab(BlockLds &l, unsigned long long *next) {
-  __syncthreads();
-  if (threadIdx.x == 0) l.base = (long long)atomicAdd(next, (unsigned long long)kBlkGrab);
-  __syncthreads();
-  return (int64_t)l.base;
-}
-
-template <bool CA>
-__global__ __launch_bounds__(kBlk) void k_move_block(MoveArgs a) {
-  __shared__ BlockLds l;
-  block_init(l);
-  const int tid = (int)threadIdx.x;
-  double gsum = 0.0;
-  unsigned long long mv = 0, ne = 0;
-  for (;;) {
-    const int64_t base = block_grab(l, a.bnext);
-    if (base >= a.blen) break;
-    if (tid < kBlkGrab) {
-      const int64_t p = base + tid;
-      int go = 0;
-      if (p < a.blen) {
-        const int v = a.blist[p];
-        go = a.rng[v] && ld_u8(&a.U[v]);
-        l.v[tid] = v;
-        l.e0[tid] = a.off[v];
-        l.e1[tid] = a.off[v + 1];
-        l.c[tid] = a.C[v];  // only this workgroup writes C[v] during the sweep
-        l.k[tid] = a.K[v];
-      }
-      l.go[tid] = go;
-    }
-    __syncthreads();
-    for (int q = 0; q < kBlkGrab; ++q) {
-      if (!l.go[q]) continue;
-      const int i = l.v[q], d = l.c[q];
-      const int64_t e0 = l.e0[q], e1 = l.e1[q];
-      const double Ki = l.k[q];
-      if (tid == 0) st_u8(&a.U[i], 0);
-      ne += (unsigned long long)(e1 - e0);
-      const double Sd = ld_s<CA>(&a.Sig[d]);
-      int j[kBlkPer], c[kBlkPer];
-      float x[kBlkPer];
-#pragma unroll
-      for (int u = 0; u < kBlkPer; ++u) {
-        const int64_t e = e0 + tid + u * kBlk;
-        j[u] = i;
-        x[u] = 0.0f;
-        if (e < e1) { j[u] = a.idx[e]; x[u] = a.w[e]; }
-      }
-#pragma unroll
-      for (int u = 0; u < kBlkPer; ++u) c[u] = j[u] != i ? ld_c<CA>(&a.C[j[u]]) : kEmpty;
-      // the own community, usually most of the edges, is summed in registers
-      double b = 0.0;
-#pragma unroll
-      for (int u = 0; u < kBlkPer; ++u)
-        if (c[u] == d) { b += (double)x[u]; c[u] = kEmpty; }
-      __syncthreads();  // the table is clear and rd free
-      b = block_total(b, l.rs);
-      double bg, bs;
-      int bc;
-      block_best<CA>(l, c, x, a.M2, b, Ki, Sd, a.Sig, bg, bc, bs);
-      if (bc == kNoComm) continue;
-      if (tid == 0) {
-        st_int(&a.C[i], bc);
-        unsafeAtomicAdd(&a.Sig[d], -Ki);
-        unsafeAtomicAdd(&a.Sig[bc], Ki);
-        if (a.track) { set_flag<true>(&a.dC[d]); set_flag<true>(&a.dC[bc]); }
-        gsum += bg;
-        mv += 1;
-      }
-#pragma unroll
-      for (int u = 0; u < kBlkPer; ++u)
-        if (j[u] != i) {
-          if (a.defer) set_flag<true>(&a.U[j[u]]);
-          else set_flag<false>(&a.U[j[u]]);
-        }
-    }
-  }
-  if (tid == 0) {
-    if (gsum != 0.0) unsafeAtomicAdd(a.gain, gsum);
-    if (mv) atomicAdd(a.moves, mv);
-    if (a.hub_scanned && ne) atomicAdd(a.hub_scanned, ne);
-  }
-}
-
-// The refinement's candidates as in k_refine_async, a workgroup each.
-template <bool CA>
-__global__ __launch_bounds__(kBlk) void k_refine_block(RefineArgs a) {
-  __shared__ BlockLds l;
-  block_init(l);
-  const int tid = (int)threadIdx.x;
-  unsigned long long nv = 0, ne = 0;
-  for (;;) {
-    const int64_t base = block_grab(l, a.bnext);
-    if (base >= a.blen) break;
-    if (tid < kBlkGrab) {
-      const int64_t p = base + tid;
-      int go = 0;
-      if (p < a.blen) {
-        const int v = a.blist[p];
-        const int cb = a.CB[v], c = a.C[v];
-        const double kv = a.K[v];
-        go = a.dC[cb] && ld_dbl(&a.Sig[c]) == kv;
-        l.v[tid] = v;
-        l.cb[tid] = cb;
-        l.c[tid] = c;
-        l.e0[tid] = a.off[v];
-        l.e1[tid] = a.off[v + 1];
-        l.k[tid] = kv;
-      }
-      l.go[tid] = go;
-    }
-    __syncthreads();
-    for (int q = 0; q < kBlkGrab; ++q) {
-      if (!l.go[q]) continue;
-      const int i = l.v[q], cc = l.c[q], cb = l.cb[q];
-      const int64_t e0 = l.e0[q], e1 = l.e1[q];
-      const double Ki = l.k[q];
-      for (int attempt = 0; attempt < kRefineTries; ++attempt) {
-        nv += 1;
-        ne += (unsigned long long)(e1 - e0);
-        int j[kBlkPer], c[kBlkPer];
-        float x[kBlkPer];
-#pragma unroll
-        for (int u = 0; u < kBlkPer; ++u) {
-          const int64_t e = e0 + tid + u * kBlk;
-          j[u] = i;
-          x[u] = 0.0f;
-          if (e < e1) { j[u] = a.idx[e]; x[u] = a.w[e]; }
-        }
-        unsigned long long pk[kBlkPer];
-#pragma unroll
-        for (int u = 0; u < kBlkPer; ++u) pk[u] = j[u] != i ? ld_p<CA>(&a.CP[j[u]]) : ~0ull;
-        double b = 0.0;  // edges to the vertex's own community: none while it is alone
-#pragma unroll
-        for (int u = 0; u < kBlkPer; ++u) {
-          c[u] = (j[u] != i && (int)(pk[u] >> 32) == cb) ? (int)(uint32_t)pk[u] : kEmpty;
-          if (c[u] == cc) { b += (double)x[u]; c[u] = kEmpty; }
-        }
-        __syncthreads();  // the table is clear and rs free
-        b = block_total(b, l.rs);
-        double bg, bs;
-        int bc;
-        block_best<CA>(l, c, x, a.M2, b, Ki, Ki, a.Sig, bg, bc, bs);
-        if (bc == kNoComm) break;
-        // held: as in k_refine_async
-        int seen = 0;
-#pragma unroll
-        for (int u = 0; u < kBlkPer; ++u) seen |= c[u] == bc && j[u] != bc;
-        const bool held = __syncthreads_or(seen) != 0;
-        if (tid == 0) {
-          int again = 0;
-          if (!held && ld_int(&a.C[bc]) != bc) {
-            again = 1;
-          } else {
-            unsigned long long *sc = (unsigned long long *)&a.Sig[cc];
-            const unsigned long long want = __double_as_longlong(Ki);
-            if (atomicCAS(sc, want, 0ull) == want) {
-              bool joined = true;
-              if (held) {
-                unsafeAtomicAdd(&a.Sig[bc], Ki);
-              } else if (!join_nonempty(&a.Sig[bc], Ki)) {
-                unsafeAtomicAdd(&a.Sig[cc], Ki);  // the target emptied meanwhile: stay, look again
-                again = 1;
-                joined = false;
-              }
-              if (joined) {
-                st_int(&a.C[i], bc);
-                __hip_atomic_store(&a.CP[i], ((unsigned long long)(uint32_t)cb << 32) | (uint32_t)bc,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              }
-            }
-          }
-          l.again = again;
-        }
-        __syncthreads();
-        if (!l.again) break;
-      }
-    }
-  }
-  if (tid == 0 && a.sweep_work && nv) {
-    atomicAdd(&a.sweep_work[0], nv);
-    atomicAdd(&a.sweep_work[1], ne);
-  }
-}
-
-void move_blocks(const MoveArgs &a, int groups, hipStream_t s) {
-  if (a.blen <= 0) return;
-  if (a.cached) hipLaunchKernelGGL(k_move_block<true>, groups, kBlk, 0, s, a);
-  else hipLaunchKernelGGL(k_move_block<false>, groups, kBlk, 0, s, a);
-}
-void refine_blocks(const RefineArgs &a, int groups, hipStream_t s) {
-  if (a.blen <= 0) return;
-  if (a.cached) hipLaunchKernelGGL(k_refine_block<true>, groups, kBlk, 0, s, a);
-  else hipLaunchKernelGGL(k_refine_block<false>, groups, kBlk, 0, s, a);
-}
-
-// ---- vertex lists by degree --------------------------------------------------------
-__global__ void k_degree_flags(const int64_t *off, int64_t n, int64_t lo, int64_t hi, int32_t *flags) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t deg = off[i + 1] - off[i];
-    flags[i] = deg > lo && deg <= hi;
-  }
-}
-void degree_flags(const int64_t *off, int64_t n, int64_t lo, int64_t hi, int32_t *flags, hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(k_degree_flags, flat_grid(n), 256, 0, s, off, n, lo, hi, flags);
-}
-__global__ void k_degree_list(const int64_t *off, int64_t n, int64_t lo, int64_t hi, const int32_t *pos,
-                              int32_t *list) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t deg = off[i + 1] - off[i];
-    if (deg > lo && deg <= hi) list[pos[i]] = (int32_t)i;
-  }
-}
-void degree_list(const int64_t *off, int64_t n, int64_t lo, int64_t hi, const int32_t *pos, int32_t *list,
-                 hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(k_degree_list, flat_grid(n), 256, 0, s, off, n, lo, hi, pos, list);
+void edge_list(const int64_t *off, int64_t n, const int32_t *pos, int32_t *list, hipStream_t s) {
+  if (n > 0) hipLaunchKernelGGL(k_edge_list, flat_grid(n), 256, 0, s, off, n, pos, list);
 }
 
 }  // namespace lk
+

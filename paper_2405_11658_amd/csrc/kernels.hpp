@@ -8,7 +8,7 @@
 
 namespace lk {
 
-constexpr int kNB = 6;        // degree buckets (degree_bucket)
+constexpr int kNB = 6;        // degree buckets: <=4, <=8, <=32, <=256, <=2048, >2048
 
 // Slice of a vertex in a sweep: MurmurHash3's 32-bit finaliser of the id,
 // modulo the number of slices.
@@ -23,11 +23,8 @@ __host__ __device__ inline int slice_of(int64_t i, int S) {
 }
 constexpr int kChunk = 1024;  // CSR positions per chunk in chunked edge kernels
 
-constexpr int64_t kHubDeg = 2048;  // degree above which a vertex is a hub (several workgroups)
-// Degree bucket of a vertex with edges: 0-2 groups of 4 / 8 / 32 lanes, 3 a
-// wavefront (degree <= mid), 4 a workgroup, 5 several workgroups.
-__host__ __device__ inline int degree_bucket(int64_t deg, int64_t mid) {
-  return deg > kHubDeg ? 5 : deg > mid ? 4 : deg <= 4 ? 0 : deg <= 8 ? 1 : deg <= 32 ? 2 : 3;
+inline int bucket_of_host(int64_t deg) {
+  return deg <= 4 ? 0 : deg <= 8 ? 1 : deg <= 32 ? 2 : deg <= 256 ? 3 : deg <= 2048 ? 4 : 5;
 }
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int flat_grid(int64_t n, int block = 256, int cap = 4096) {
@@ -75,7 +72,7 @@ size_t scan_excl_i64(void *temp, size_t tbytes, const int64_t *in, int64_t *out,
 size_t scan_excl_i32_to_i64(void *temp, size_t tbytes, const int32_t *in, int64_t *out, int64_t n,
                             hipStream_t s);
 void reset_iter(int32_t *counts, int n, double *d0, unsigned long long *u0, unsigned long long *u1,
-                unsigned long long *u2, hipStream_t s);
+                hipStream_t s);
 size_t sort_pairs_u64_i32(void *temp, size_t tbytes, const unsigned long long *kin,
                           unsigned long long *kout, const int32_t *vin, int32_t *vout, int64_t n,
                           hipStream_t s);
@@ -138,6 +135,7 @@ int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipSt
 // Hub plan of a level: the vertices of the largest degree bucket grouped by
 // slice, each split into edge chunks (one gather workgroup each) and owning
 // a global open-addressing table split into scoring segments.
+constexpr int64_t kHubDeg = 2048;  // degree above which a vertex is a hub
 constexpr int kHubEC = 512;        // edges per gather workgroup
 constexpr int kHubSeg = 4096;      // table slots per scoring workgroup
 constexpr int64_t kHubMinCap = 256; // smallest hub table (a power of two)
@@ -202,18 +200,14 @@ struct MoveArgs {
   int64_t alen;
   int *akeys;                 // per-wavefront global tables, 2*kHubDeg slots each
   double *avals;
-  int64_t hubdeg;             // degree above which a vertex is no longer a wavefront's (<= kHubDeg)
-  const int32_t *blist;       // vertices of degree in (hubdeg, kHubDeg]: a workgroup's
-  int64_t blen;
-  unsigned long long *bnext;  // device counter: next position of blist (zeroed per sweep)
+  int64_t hubdeg;             // degree above which a vertex takes the hub path (<= kHubDeg)
   int32_t cached;             // asynchronous sweep: cache-served reads of C and Sigma (large levels)
   int32_t defer;              // asynchronous sweep: batch the Sigma updates of popular communities
 };
 // Per level: counts[s*kNB+b] of vertices with edges, slice sizes, and the
 // vertex-by-slice grouping (slice_fill zeroed, slice_off = starts of slices).
-// Vertices of degree > kHubDeg go to the last (hub) bucket, those of degree
-// > mid (<= kHubDeg) to the one before it.
-void slice_hist(const int64_t *off, int64_t n, int S, int64_t mid, int32_t *counts, int32_t *slice_cnt,
+// Vertices of degree > hubdeg (<= kHubDeg) go to the last (hub) bucket.
+void slice_hist(const int64_t *off, int64_t n, int S, int64_t hubdeg, int32_t *counts, int32_t *slice_cnt,
                 hipStream_t s);
 void slice_scatter(int64_t n, int S, const int32_t *slice_off, int32_t *slice_fill, int32_t *vbyslice,
                    hipStream_t s);
@@ -272,14 +266,11 @@ struct RefineArgs {
   int64_t alen;
   int *akeys;
   double *avals;
-  const int32_t *blist;
-  int64_t blen;
-  unsigned long long *bnext;
   // multi-workgroup path for hub candidates (as in MoveArgs)
   HubPlan hp;
   uint8_t *act;
   int64_t hbeg, hend, qbeg, qend, gbeg, gend;
-  int64_t hubdeg;           // as in MoveArgs
+  int64_t hubdeg;
 };
 void refine_break(const RefineArgs &a, hipStream_t s);
 void refine_propose_bucket(const RefineArgs &a, const int64_t *region_h, int b, hipStream_t s);
@@ -292,15 +283,12 @@ constexpr int kAsyncChunk = 64;  // vertex ids taken per grab of the asynchronou
 // Tables: LDS, else 2*kHubDeg slots per wavefront in akeys/avals; `wide`
 // selects larger LDS tables (for levels of high average degree).
 void move_async(const MoveArgs &a, int waves, bool wide, hipStream_t s);
+// list of vertices with edges in ascending order: flags then scan then scatter
+void edge_flags(const int64_t *off, int64_t n, int32_t *flags, hipStream_t s);
+void edge_list(const int64_t *off, int64_t n, const int32_t *pos, int32_t *list, hipStream_t s);
 void refine_async(const RefineArgs &a, int waves, bool wide, hipStream_t s);
-// `groups` workgroups sweep a.blist, one vertex each at a time.
-void move_blocks(const MoveArgs &a, int groups, hipStream_t s);
-void refine_blocks(const RefineArgs &a, int groups, hipStream_t s);
-// flags[i] = lo < degree <= hi; list of the flagged (pos = scanned flags)
-void degree_flags(const int64_t *off, int64_t n, int64_t lo, int64_t hi, int32_t *flags, hipStream_t s);
-void degree_list(const int64_t *off, int64_t n, int64_t lo, int64_t hi, const int32_t *pos, int32_t *list,
-                 hipStream_t s);
 void pack_cb(const int32_t *C, const int32_t *CB, int64_t n, unsigned long long *CP, hipStream_t s);
+// hub frontier of slice a.s (a.hbeg..a.hend of the hub plan) for the hub-only sliced phase
 
 // ---- k_aggregate.hip -----------------------------------------------------------
 struct AggArgs {
