@@ -55,6 +55,57 @@ __device__ __forceinline__ long long group_sum_ll(long long v) {
   return v;
 }
 
+// Reductions over the whole wavefront without LDS permutes (each of those is
+// a round trip of ~100 cycles through the LDS pipe, three per step of a
+// (gain, id) argmax): four steps inside the rows of 16 lanes with DPP moves,
+// then the four rows' results through scalar registers.  Called by all 64
+// lanes; every lane gets the result.
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = dpp_move<CTRL>((int)b), hi = dpp_move<CTRL>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;           // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // within 8 and 16 lanes
+__device__ __forceinline__ int lane_value(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_move<kDppXor1>(v);
+  v += dpp_move<kDppXor2>(v);
+  v += dpp_move<kDppHalfMirror>(v);
+  v += dpp_move<kDppMirror>(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+template <int CTRL>
+__device__ __forceinline__ void dpp_argmax(double &g, int &c) {
+  const double og = dpp_move<CTRL>(g);
+  const int oc = dpp_move<CTRL>(c);
+  if (better(og, oc, g, c)) { g = og; c = oc; }
+}
+__device__ __forceinline__ void wave_argmax(double &g, int &c) {
+  dpp_argmax<kDppXor1>(g, c);
+  dpp_argmax<kDppXor2>(g, c);
+  dpp_argmax<kDppHalfMirror>(g, c);
+  dpp_argmax<kDppMirror>(g, c);
+  const double g0 = g;
+  const int c0 = c;
+#pragma unroll
+  for (int r = 0; r < kWave; r += 16) {
+    const double og = lane_value(g0, r);
+    const int oc = lane_value(c0, r);
+    if (r == 0 || better(og, oc, g, c)) { g = og; c = oc; }
+  }
+}
+
 // 32-bit integer finaliser "lowbias32" (xorshift-multiply; constants from
 // C. Wellons' published hash-prospector search).
 __device__ __forceinline__ uint32_t mix32(uint32_t x) {

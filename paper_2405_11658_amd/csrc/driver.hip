@@ -472,20 +472,24 @@ void scan_i32_i64(Ctx &x, const int32_t *in, int64_t *out, int64_t n) {
 }
 
 // Multi-workgroup hub plan of a level (local-moving of the largest degree
-// bucket): hub list per slice, chunk / table / segment layout, tables
+// bucket): hub list per slice, and for the hubs of degree > kHubDeg their chunk / table / segment layout, tables
 // cleared, and per-slice bounds on the host.
 struct HubHost {
   HubPlan p;
   int64_t nhub = 0;
   std::vector<int64_t> hs, qs, gs;  // per-slice starts (S+1): hubs, chunks, segments
+  std::vector<bool> wide;     // per slice: hubs of degree in (kHubDeg, kWideDeg]
+  std::vector<bool> chunked;  // per slice: the hubs above kHubDeg move in chunks
 };
 
-HubHost hub_plan(Ctx &x, const Level &g, int S, int64_t hubdeg, const Layout &B) {
+HubHost hub_plan(Ctx &x, const Level &g, int S, int64_t hubdeg, bool async, const Layout &B) {
   HubHost H;
   memset(&H.p, 0, sizeof(H.p));
   H.hs.assign(S + 1, 0);
   H.qs.assign(S + 1, 0);
   H.gs.assign(S + 1, 0);
+  H.wide.assign(S, false);
+  H.chunked.assign(S, !async);
   for (int s = 0; s < S; ++s)
     H.hs[s + 1] = H.hs[s] + (B.region[s * kNB + kNB] - B.region[s * kNB + kNB - 1]);
   H.nhub = H.hs[S];
@@ -499,8 +503,9 @@ HubHost hub_plan(Ctx &x, const Level &g, int S, int64_t hubdeg, const Layout &B)
   x.zero(hfill, S);
   H.p.hubv = x.get<int32_t>(H_v, nh);
   hub_find(g.off, g.n, S, hubdeg, hsoff, hfill, H.p.hubv, x.s);
-  int64_t *cnt = x.get<int64_t>(H_cnt, 3 * (nh + 1));
-  hub_sizes(g.off, H.p.hubv, nh, cnt, cnt + (nh + 1), cnt + 2 * (nh + 1), x.s);
+  int64_t *cnt = x.get<int64_t>(H_cnt, 4 * (nh + 1));
+  int64_t *big = cnt + 3 * (nh + 1);
+  hub_sizes(g.off, H.p.hubv, nh, cnt, cnt + (nh + 1), cnt + 2 * (nh + 1), big, x.s);
   x.launched("hub plan");
   H.p.hch = x.get<int64_t>(H_ch, nh + 1);
   H.p.htab = x.get<int64_t>(H_tab, nh + 1);
@@ -509,20 +514,28 @@ HubHost hub_plan(Ctx &x, const Level &g, int S, int64_t hubdeg, const Layout &B)
   scan_i64(x, cnt, H.p.hch, nh + 1);
   scan_i64(x, cnt + (nh + 1), H.p.htab, nh + 1);
   scan_i64(x, cnt + 2 * (nh + 1), H.p.hsg, nh + 1);
-  int64_t *bnd = x.get<int64_t>(H_bnd, 3 * (S + 1));
+  scan_i64(x, big, big, nh + 1);
+  int64_t *bnd = x.get<int64_t>(H_bnd, 4 * (S + 1));
+  gather_bounds(big, hsoff, S + 1, bnd + 3 * (S + 1), x.s);
   gather_bounds(H.p.hch, hsoff, S + 1, bnd, x.s);
   gather_bounds(H.p.hsg, hsoff, S + 1, bnd + (S + 1), x.s);
   gather_bounds(H.p.htab, hsoff, S + 1, bnd + 2 * (S + 1), x.s);
   hub_rel(H.p.htab, nh, hsoff, S, bnd + 2 * (S + 1), x.s);
   x.launched("hub bounds");
   int64_t *hb = (int64_t *)((char *)x.pin() + 8192);
-  x.check(hipMemcpyAsync(hb, bnd, sizeof(int64_t) * 3 * (S + 1), hipMemcpyDeviceToHost, x.s), "D2H");
+  x.check(hipMemcpyAsync(hb, bnd, sizeof(int64_t) * 4 * (S + 1), hipMemcpyDeviceToHost, x.s), "D2H");
   x.check(hipStreamSynchronize(x.s), "sync");
   int64_t ntab = 0;  // the largest slice's tables
   for (int s = 0; s <= S; ++s) {
     H.qs[s] = hb[s];
     H.gs[s] = hb[S + 1 + s];
-    if (s < S) ntab = std::max(ntab, hb[2 * (S + 1) + s + 1] - hb[2 * (S + 1) + s]);
+    if (s == S) break;
+    const int64_t nbig = hb[3 * (S + 1) + s + 1] - hb[3 * (S + 1) + s];
+    H.wide[s] = (int32_t)nbig > 0;
+    // a slice of the asynchronous mode needs the chunks only for hubs that no
+    // workgroup can read at once
+    if (async) H.chunked[s] = nbig >> 32 > 0;
+    if (H.chunked[s]) ntab = std::max(ntab, hb[2 * (S + 1) + s + 1] - hb[2 * (S + 1) + s]);
   }
   H.p.chub = x.get<int32_t>(H_chub, H.qs[S]);
   H.p.shub = x.get<int32_t>(H_shub, H.gs[S]);
@@ -533,8 +546,9 @@ HubHost hub_plan(Ctx &x, const Level &g, int S, int64_t hubdeg, const Layout &B)
   x.zero(H.p.vals, ntab);
   H.p.own = x.get<double>(H_own, nh);
   x.zero(H.p.own, nh);
-  H.p.flag = x.get<int32_t>(H_flag, nh);
-  x.zero(H.p.flag, nh);
+  H.p.flag = x.get<int32_t>(H_flag, 2 * nh);
+  x.zero(H.p.flag, 2 * nh);
+  H.p.done = H.p.flag + nh;
   H.p.pg = x.get<double>(H_pg, H.gs[S]);
   H.p.pc = x.get<int32_t>(H_pc, H.gs[S]);
   x.launched("hub tables");
@@ -812,7 +826,7 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     const int64_t nl = g.n;
     const int64_t nfull = nl + niso;
     const Layout B = level_layout(x, g, NS, hubdeg, region, counts, scnt, soff, sfill, vbs);
-    const HubHost hh = hub_plan(x, g, NS, hubdeg, B);
+    const HubHost hh = hub_plan(x, g, NS, hubdeg, async, B);
     const int64_t alen = B.region[NS * kNB];  // vertices with edges
     int32_t *alist = nullptr;
     if (async && alen > 0) {
@@ -861,14 +875,11 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
         ma.vbeg = B.soff[sl];
         ma.vend = B.soff[sl + 1];
         ma.hbeg = hh.hs[sl]; ma.hend = hh.hs[sl + 1];
-        ma.qbeg = hh.qs[sl]; ma.qend = hh.qs[sl + 1];
+        ma.qbeg = hh.qs[sl]; ma.qend = hh.chunked[sl] ? hh.qs[sl + 1] : ma.qbeg;
         ma.gbeg = hh.gs[sl]; ma.gend = hh.gs[sl + 1];
         if (async) {
           // hubs: synchronous among the hubs of the slice; the rest below
-          if (ma.hend == ma.hbeg) continue;
-          move_hub_gather(ma, x.s);
-          move_hub_score(ma, x.s);
-          move_apply_bucket(ma, B.region.data(), kNB - 1, x.s);
+          move_hubs(ma, hh.wide[sl], x.s);
           continue;
         }
         move_frontier(ma, x.s);
@@ -959,16 +970,15 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     for (int sl = 0; sl < NS; ++sl) {
       ra.s = sl;
       ra.hbeg = hh.hs[sl]; ra.hend = hh.hs[sl + 1];
-      ra.qbeg = hh.qs[sl]; ra.qend = hh.qs[sl + 1];
+      ra.qbeg = hh.qs[sl]; ra.qend = hh.chunked[sl] ? hh.qs[sl + 1] : ra.qbeg;
       ra.gbeg = hh.gs[sl]; ra.gend = hh.gs[sl + 1];
       if (async) {
         // hubs of the slice (synchronous among themselves), the rest below
-        if (B.region[sl * kNB + kNB] == B.region[sl * kNB + kNB - 1]) continue;
-        refine_propose_bucket(ra, B.region.data(), kNB - 1, x.s);
+        refine_hubs(ra, B.region.data(), hh.wide[sl], x.s);
       } else {
         refine_propose(ra, B.region.data(), x.s);
+        refine_accept(ra, B.region.data(), x.s);
       }
-      refine_accept(ra, B.region.data(), x.s);
     }
     if (async) {
       hipEvent_t t0 = x.kp ? x.kp->begin() : nullptr;

@@ -16,6 +16,7 @@
 // Degree buckets pick the table: registers of a 4/8/32-lane group (all-pairs
 // combine), an LDS table per wavefront or workgroup, or a global-memory table
 // per workgroup for hubs.
+#include "block_table.hpp"
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -248,29 +249,32 @@ __global__ __launch_bounds__(BLOCK) void k_propose_team(MoveArgs a, int b) {
 }
 
 // ---- propose: hubs, several workgroups per vertex --------------------------
+struct HubGatherLds {
+  int keys[2 * kHubEC];
+  double vals[2 * kHubEC];
+  int used[kHubEC];  // slots taken (at most one per edge)
+  int nused;
+};
 // gather: a workgroup merges one edge chunk of a frontier hub in an LDS
 // table, then adds its distinct communities into the hub's global table (the
 // hub's own community into `own`).
-__global__ __launch_bounds__(256) void k_hub_gather(MoveArgs a) {
+__device__ __forceinline__ void hub_gather_chunk(const MoveArgs &a, int64_t q, HubGatherLds &l) {
   constexpr int T = 2 * kHubEC;
   constexpr int PER = kHubEC / 256;  // edges per thread
   static_assert(kHubEC % 256 == 0, "edge chunk must be a multiple of the workgroup size");
-  __shared__ int keys[T];
-  __shared__ double vals[T];
-  __shared__ int used[kHubEC];  // slots taken (at most one per edge)
-  __shared__ int nused;
-  const int64_t q = a.qbeg + blockIdx.x;
+  int *keys = l.keys, *used = l.used;
+  double *vals = l.vals;
+  int &nused = l.nused;
   const int h = a.hp.chub[q];
   const int i = a.hp.hubv[h];
   if (a.hub_front) {
     // The hub enters the frontier of its slice: every chunk takes the same
-    // decision from the processed flag, which k_hub_rev clears; the first
+    // decision from the processed flag, which the scoring clears; the first
     // chunk records it and resets the proposal.
     const bool go = a.U[i] && a.rng[i];
     if (q == a.hp.hch[h] && threadIdx.x == 0) {
       a.prop[i] = -1;
       a.act[i] = go;
-      if (go) a.lists[a.region[a.s * kNB + (kNB - 1)] + atomicAdd(a.counts + a.s * kNB + (kNB - 1), 1)] = i;
     }
     if (!go) return;
   } else if (!a.act[i]) {
@@ -321,22 +325,23 @@ __global__ __launch_bounds__(256) void k_hub_gather(MoveArgs a) {
     else table_add(a.hp.keys + t0, a.hp.vals + t0, mask, cs, vals[s]);
   }
 }
+__global__ __launch_bounds__(256) void k_hub_gather(MoveArgs a) {
+  __shared__ HubGatherLds l;
+  hub_gather_chunk(a, a.qbeg + blockIdx.x, l);
+}
 
 // score: a workgroup scans one table segment of a frontier hub, frees the
 // slots it reads, and leaves the segment's best (gain, community).
-__global__ __launch_bounds__(256) void k_hub_score(MoveArgs a) {
+// Result (gain bg, community bc) valid in thread 0.
+__device__ __forceinline__ void hub_score_segment(const MoveArgs &a, int64_t q, int h, int i, double &bg, int &bc) {
   __shared__ double rg[256 / kWave];
   __shared__ int rc[256 / kWave];
-  const int64_t q = a.gbeg + blockIdx.x;
-  const int h = a.hp.shub[q];
-  const int i = a.hp.hubv[h];
-  if (!a.act[i]) return;
   const int64_t s0 = a.hp.htab[h] + (q - a.hp.hsg[h]) * kHubSeg;
   const int64_t s1 = s0 + min((int64_t)kHubSeg, a.hp.hcap[h]);
   const int d = a.C[i];
   const double Ki = a.K[i], Sd = a.Sig[d], bown = a.hp.own[h];
-  double bg = 0.0;
-  int bc = kNoComm;
+  bg = 0.0;
+  bc = kNoComm;
   for (int64_t s = s0 + threadIdx.x; s < s1; s += blockDim.x) {
     const int c = a.hp.keys[s];
     if (c == kEmpty) continue;
@@ -347,6 +352,15 @@ __global__ __launch_bounds__(256) void k_hub_score(MoveArgs a) {
     if (x > 0.0 && better(x, c, bg, bc)) { bg = x; bc = c; }
   }
   team_argmax<256, 256>(bg, bc, rg, rc);
+}
+__global__ __launch_bounds__(256) void k_hub_score(MoveArgs a) {
+  const int64_t q = a.gbeg + blockIdx.x;
+  const int h = a.hp.shub[q];
+  const int i = a.hp.hubv[h];
+  if (!a.act[i]) return;
+  double bg;
+  int bc;
+  hub_score_segment(a, q, h, i, bg, bc);
   if (threadIdx.x == 0) { a.hp.pg[q] = bg; a.hp.pc[q] = bc; }
 }
 
@@ -408,11 +422,13 @@ void hub_find(const int64_t *off, int64_t n, int S, int64_t hubdeg, const int32_
 }
 
 __global__ void k_hub_sizes(const int64_t *off, const int32_t *hubv, int64_t nhub, int64_t *nch, int64_t *ncap,
-                            int64_t *nseg) {
+                            int64_t *nseg, int64_t *nbig) {
   for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h <= nhub; h += (int64_t)gridDim.x * blockDim.x) {
-    if (h == nhub) { nch[h] = 0; ncap[h] = 0; nseg[h] = 0; continue; }
+    if (h == nhub) { nch[h] = 0; ncap[h] = 0; nseg[h] = 0; nbig[h] = 0; continue; }
     const int i = hubv[h];
     const int64_t deg = off[i + 1] - off[i];
+    nbig[h] = deg > kWideDeg ? (int64_t)1 << 32 : deg > kHubDeg;
+    if (deg <= kHubDeg) { nch[h] = 0; ncap[h] = 0; nseg[h] = 0; continue; }
     int64_t cap = kHubMinCap;
     while (cap < 2 * deg) cap <<= 1;
     nch[h] = ceil_div(deg, (int64_t)kHubEC);
@@ -421,8 +437,8 @@ __global__ void k_hub_sizes(const int64_t *off, const int32_t *hubv, int64_t nhu
   }
 }
 void hub_sizes(const int64_t *off, const int32_t *hubv, int64_t nhub, int64_t *nch, int64_t *ncap, int64_t *nseg,
-               hipStream_t s) {
-  hipLaunchKernelGGL(k_hub_sizes, flat_grid(nhub + 1), 256, 0, s, off, hubv, nhub, nch, ncap, nseg);
+               int64_t *nbig, hipStream_t s) {
+  hipLaunchKernelGGL(k_hub_sizes, flat_grid(nhub + 1), 256, 0, s, off, hubv, nhub, nch, ncap, nseg, nbig);
 }
 
 // Table offsets counted from the start of each hub's slice: the slices run
@@ -658,12 +674,9 @@ void move_apply_bucket(const MoveArgs &a, const int64_t *region_h, int b, hipStr
 // exact reverse move with priority flags the hub blocked; (2) every chunk of
 // an unblocked hub marks its neighbours unprocessed and the first one moves
 // the hub, while the first chunk of a blocked hub leaves it unprocessed.
-__global__ __launch_bounds__(256) void k_hub_rev(MoveArgs a) {
-  const int64_t q = a.qbeg + blockIdx.x;
+__device__ __forceinline__ void hub_rev_chunk(const MoveArgs &a, int64_t q) {
   const int h = a.hp.chub[q];
   const int i = a.hp.hubv[h];
-  // the frontier read in the gather is complete: clear the processed flag
-  if (a.hub_front && q == a.hp.hch[h] && threadIdx.x == 0) a.U[i] = 0;
   if (!a.act[i]) return;
   const int p = a.prop[i];
   if (p < 0) return;
@@ -678,6 +691,7 @@ __global__ __launch_bounds__(256) void k_hub_rev(MoveArgs a) {
   }
   if (blocked) a.hp.flag[h] = 1;
 }
+__global__ __launch_bounds__(256) void k_hub_rev(MoveArgs a) { hub_rev_chunk(a, a.qbeg + blockIdx.x); }
 
 __global__ __launch_bounds__(256) void k_hub_mark(MoveArgs a) {
   const int64_t q = a.qbeg + blockIdx.x;
@@ -710,6 +724,140 @@ void move_hub_apply(const MoveArgs &a, hipStream_t s) {
   if (a.qend <= a.qbeg) return;
   hipLaunchKernelGGL(k_hub_rev, (int)(a.qend - a.qbeg), 256, 0, s, a);
   hipLaunchKernelGGL(k_hub_mark, (int)(a.qend - a.qbeg), 256, 0, s, a);
+}
+
+// ---- the hub slices of the asynchronous mode -------------------------------------
+// A level's hubs move in up to 256 slices, one after another, and most slices
+// hold a handful of hubs of a few hundred to a few thousand edges: a slice is
+// a chain of launches, each bound by its own latency.  A hub that a workgroup
+// can read at once gets one workgroup, with its table in LDS and its edges in
+// registers, so that the chain is two launches of ~7 us (propose; reverse
+// check and apply) instead of the five of the chunked kernels above (gather
+// 11, score 10, final, rev and mark 3 each).  A slice with hubs beyond a
+// workgroup's reach is four launches: its chunks ride with the other hubs'
+// workgroups, and the last segment of a hub to be scored picks the hub's
+// best.  The rule is that of the sliced sweep: the proposals of a slice all
+// read the state before it.  (Moving 1/64 of the hubs at a time without the
+// slices, each applied at once, was faster still, but cost 5e-3 to 7e-3 of
+// modularity on R-MAT graphs of scale 16 to 22.)
+template <int T, int PER, int SLOTS>
+__device__ __forceinline__ void hub_propose(const MoveArgs &a, int64_t h, int64_t lo, int64_t hi,
+                                            BlockTable<T, PER, SLOTS> &l) {
+  const int i = a.hp.hubv[h];
+  const int64_t e0 = a.off[i];
+  const int deg = (int)min(a.off[i + 1] - e0, (int64_t)INT_MAX);
+  if (deg <= lo || deg > hi) return;
+  // only this workgroup writes the hub's flag in this launch, after the
+  // barriers of block_best
+  const bool go = a.U[i] && a.rng[i];
+  if (!go) {
+    if (threadIdx.x == 0) a.prop[i] = -1;
+    return;
+  }
+  int j[PER], c[PER];
+  float x[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = threadIdx.x + u * T;
+    j[u] = i;
+    x[u] = 0.0f;
+    if (e < deg) { j[u] = a.idx[e0 + e]; x[u] = a.w[e0 + e]; }
+  }
+  const int d = a.C[i];
+  const double Ki = a.K[i], Sd = a.Sig[d];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) c[u] = j[u] != i ? a.C[j[u]] : kEmpty;
+  double bg;
+  int bc;
+  block_best(l, deg, c, x, d, a.M2, Ki, Sd, a.Sig, bg, bc);
+  if (threadIdx.x == 0) {
+    a.U[i] = 0;
+    a.from[i] = d;
+    a.prop[i] = bc == kNoComm ? -1 : bc;
+    a.gp[i] = bg;
+    if (a.hub_scanned) atomicAdd(a.hub_scanned, (unsigned long long)deg);
+  }
+}
+
+// Hubs of degree <= kHubDeg; the first `chunks` workgroups gather the chunks
+// of the others.
+__global__ __launch_bounds__(256) void k_hub_propose(MoveArgs a, int chunks) {
+  __shared__ union {
+    HubGatherLds gather;
+    BlockTable<256, 8, 4096> table;
+  } l;
+  if ((int)blockIdx.x < chunks) hub_gather_chunk(a, a.qbeg + blockIdx.x, l.gather);
+  else hub_propose<256, 8, 4096>(a, a.hbeg + blockIdx.x - chunks, 0, kHubDeg, l.table);
+}
+__global__ __launch_bounds__(512) void k_hub_propose_wide(MoveArgs a) {
+  __shared__ BlockTable<512, 12, 8192> l;
+  hub_propose<512, 12, 8192>(a, a.hbeg + blockIdx.x, kHubDeg, kWideDeg, l);
+}
+
+// Scores the segments of the chunked hubs; a hub's last one to finish reduces
+// them all to the hub's proposal.
+__global__ __launch_bounds__(256) void k_hub_score_final(MoveArgs a) {
+  const int64_t q = a.gbeg + blockIdx.x;
+  const int h = a.hp.shub[q];
+  const int i = a.hp.hubv[h];
+  if (!a.act[i]) return;
+  double bg;
+  int bc;
+  hub_score_segment(a, q, h, i, bg, bc);
+  if (!hub_last_segment(a.hp, h, q, bg, bc)) return;
+  hub_reduce_segments(a.hp, h, bg, bc);
+  if (threadIdx.x == 0) {
+    a.from[i] = a.C[i];
+    a.prop[i] = bc == kNoComm ? -1 : bc;
+    a.gp[i] = bg;
+    a.U[i] = 0;  // the gather has read it
+  }
+}
+
+// Reverse check of the slice's proposals; hubs of degree <= hi (a workgroup
+// each) then move, the chunked ones in k_hub_mark.
+__global__ __launch_bounds__(256) void k_hub_apply(MoveArgs a, int chunks, int64_t hi) {
+  if ((int)blockIdx.x < chunks) {
+    hub_rev_chunk(a, a.qbeg + blockIdx.x);
+    return;
+  }
+  const int i = a.hp.hubv[a.hbeg + blockIdx.x - chunks];
+  const int64_t e0 = a.off[i], e1 = a.off[i + 1];
+  if (e1 - e0 > hi) return;
+  const int p = a.prop[i];
+  if (p < 0) return;
+  const int fi = a.from[i];
+  const double g = a.gp[i];
+  int blocked = 0;
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+    const int j = a.idx[e];
+    if (j != i && reverse_wins(a, j, i, fi, p, g)) blocked = 1;
+  }
+  if (__syncthreads_or(blocked)) {
+    if (threadIdx.x == 0) a.U[i] = 1;
+    return;
+  }
+  if (threadIdx.x == 0) {
+    double gsum = 0.0;
+    long long mv = 0;
+    do_move(a, i, fi, p, g, gsum, mv);
+    if (gsum != 0.0 && a.gain) unsafeAtomicAdd(a.gain, gsum);
+    atomicAdd(a.moves, 1ull);
+  }
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+    const int j = a.idx[e];
+    if (j != i) a.U[j] = 1;
+  }
+}
+
+void move_hubs(const MoveArgs &a, bool wide, hipStream_t s) {
+  const int nh = (int)(a.hend - a.hbeg), nq = (int)(a.qend - a.qbeg);
+  if (nh <= 0) return;
+  hipLaunchKernelGGL(k_hub_propose, nq + nh, 256, 0, s, a, nq);
+  if (nq > 0) hipLaunchKernelGGL(k_hub_score_final, (int)(a.gend - a.gbeg), 256, 0, s, a);
+  else if (wide) hipLaunchKernelGGL(k_hub_propose_wide, nh, 512, 0, s, a);
+  hipLaunchKernelGGL(k_hub_apply, nq + nh, 256, 0, s, a, nq, nq > 0 ? kHubDeg : kWideDeg);
+  if (nq > 0) hipLaunchKernelGGL(k_hub_mark, nq, 256, 0, s, a);
 }
 
 // ---- fixed-order gain total (synchronous mode) ------------------------------------

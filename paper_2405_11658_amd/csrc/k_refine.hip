@@ -11,6 +11,7 @@
 //     accepted when the target's representative is not proposing in the
 //     slice, or when the two propose to each other and the proposer has
 //     priority (larger gain, then smaller id).
+#include "block_table.hpp"
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -237,15 +238,19 @@ static int rgrid(int64_t cap, int per_block, int maxb = 4096) {
 // count; the own community is the vertex itself.  Each gather chunk tests
 // candidacy itself (nothing it reads changes during the launch) and the
 // hub's first chunk records it for the later launches.
-__global__ __launch_bounds__(256) void k_rhub_gather(RefineArgs a) {
+struct RHubGatherLds {
+  int keys[2 * kHubEC];
+  double vals[2 * kHubEC];
+  int used[kHubEC];  // slots taken (at most one per edge)
+  int nused;
+};
+__device__ __forceinline__ void rhub_gather_chunk(const RefineArgs &a, int64_t q, RHubGatherLds &l) {
   constexpr int T = 2 * kHubEC;
   constexpr int PER = kHubEC / 256;  // edges per thread
   static_assert(kHubEC % 256 == 0, "edge chunk must be a multiple of the workgroup size");
-  __shared__ int keys[T];
-  __shared__ double vals[T];
-  __shared__ int used[kHubEC];  // slots taken (at most one per edge)
-  __shared__ int nused;
-  const int64_t q = a.qbeg + blockIdx.x;
+  int *keys = l.keys, *used = l.used;
+  double *vals = l.vals;
+  int &nused = l.nused;
   const int h = a.hp.chub[q];
   const int i = a.hp.hubv[h];
   const bool go = a.dC[a.CB[i]] && a.C[i] == i && a.S[i] == 1;
@@ -314,18 +319,21 @@ __global__ __launch_bounds__(256) void k_rhub_gather(RefineArgs a) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_rhub_score(RefineArgs a) {
+__global__ __launch_bounds__(256) void k_rhub_gather(RefineArgs a) {
+  __shared__ RHubGatherLds l;
+  rhub_gather_chunk(a, a.qbeg + blockIdx.x, l);
+}
+
+// Result (gain bg, community bc) valid in thread 0.
+__device__ __forceinline__ void rhub_score_segment(const RefineArgs &a, int64_t q, int h, int i, double &bg,
+                                                   int &bc) {
   __shared__ double rg[256 / kWave];
   __shared__ int rc[256 / kWave];
-  const int64_t q = a.gbeg + blockIdx.x;
-  const int h = a.hp.shub[q];
-  const int i = a.hp.hubv[h];
-  if (!a.act[i]) return;
   const int64_t s0 = a.hp.htab[h] + (q - a.hp.hsg[h]) * kHubSeg;
   const int64_t s1 = s0 + min((int64_t)kHubSeg, a.hp.hcap[h]);
   const double Ki = a.K[i], Sd = a.Sig[i], bown = a.hp.own[h];
-  double bg = 0.0;
-  int bc = kNoComm;
+  bg = 0.0;
+  bc = kNoComm;
   for (int64_t s = s0 + threadIdx.x; s < s1; s += blockDim.x) {
     const int c = a.hp.keys[s];
     if (c == kEmpty) continue;
@@ -336,6 +344,15 @@ __global__ __launch_bounds__(256) void k_rhub_score(RefineArgs a) {
     if (x > 0.0 && better(x, c, bg, bc)) { bg = x; bc = c; }
   }
   team_argmax<256, 256>(bg, bc, rg, rc);
+}
+__global__ __launch_bounds__(256) void k_rhub_score(RefineArgs a) {
+  const int64_t q = a.gbeg + blockIdx.x;
+  const int h = a.hp.shub[q];
+  const int i = a.hp.hubv[h];
+  if (!a.act[i]) return;
+  double bg;
+  int bc;
+  rhub_score_segment(a, q, h, i, bg, bc);
   if (threadIdx.x == 0) { a.hp.pg[q] = bg; a.hp.pc[q] = bc; }
 }
 
@@ -356,7 +373,7 @@ __global__ __launch_bounds__(256) void k_rhub_final(RefineArgs a) {
   }
 }
 
-static void refine_hubs(const RefineArgs &a, hipStream_t s) {
+static void refine_hubs_sync(const RefineArgs &a, hipStream_t s) {
   if (a.hend <= a.hbeg || a.qend <= a.qbeg) return;  // every hub has edge chunks
   hipLaunchKernelGGL(k_rhub_gather, (int)(a.qend - a.qbeg), 256, 0, s, a);
   hipLaunchKernelGGL(k_rhub_score, (int)(a.gend - a.gbeg), 256, 0, s, a);
@@ -376,7 +393,7 @@ void refine_propose_bucket(const RefineArgs &a, const int64_t *region_h, int b, 
     case 2: hipLaunchKernelGGL(k_rprop_small<32>, rgrid(cap, 8), 256, 0, s, a, b); break;
     case 3: hipLaunchKernelGGL((k_rprop_team<64, 512, 256>), rgrid(cap, 4), 256, 0, s, a, b); break;
     case 4: hipLaunchKernelGGL((k_rprop_team<256, 4096, 256>), rgrid(cap, 1, 2048), 256, 0, s, a, b); break;
-    case 5: refine_hubs(a, s); break;
+    case 5: refine_hubs_sync(a, s); break;
   }
 }
 
@@ -405,6 +422,82 @@ __global__ void k_raccept(RefineArgs a, int64_t beg, int64_t end) {
 
 void refine_accept(const RefineArgs &a, const int64_t *region_h, hipStream_t s) {
   const int64_t beg = region_h[a.s * kNB], end = region_h[(a.s + 1) * kNB];
+  if (end > beg) hipLaunchKernelGGL(k_raccept, flat_grid(end - beg), 256, 0, s, a, beg, end);
+}
+
+// ---- the hub slices of the asynchronous mode ---------------------------------------
+// As in local moving (k_move.hip): a workgroup per candidate it can read at
+// once, so that a slice is two launches (propose, accept) instead of four, or
+// three when some of its hubs are chunked.
+template <int T, int PER, int SLOTS>
+__device__ __forceinline__ void rhub_propose(const RefineArgs &a, int64_t h, int64_t lo, int64_t hi,
+                                             BlockTable<T, PER, SLOTS> &l) {
+  const int i = a.hp.hubv[h];
+  const int64_t e0 = a.off[i];
+  const int deg = (int)min(a.off[i + 1] - e0, (int64_t)INT_MAX);
+  if (deg <= lo || deg > hi) return;
+  const int cbi = a.CB[i];
+  if (!(a.dC[cbi] && a.C[i] == i && a.S[i] == 1)) return;  // prop is -1 since the break
+  int j[PER], c[PER];
+  float x[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = threadIdx.x + u * T;
+    j[u] = i;
+    x[u] = 0.0f;
+    if (e < deg) { j[u] = a.idx[e0 + e]; x[u] = a.w[e0 + e]; }
+  }
+  const double Ki = a.K[i], Sd = a.Sig[i];
+  unsigned long long pk[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) pk[u] = j[u] != i ? a.CP[j[u]] : 0ull;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) c[u] = (j[u] != i && (int)(pk[u] >> 32) == cbi) ? (int)(uint32_t)pk[u] : kEmpty;
+  double bg;
+  int bc;
+  block_best(l, deg, c, x, i, a.M2, Ki, Sd, a.Sig, bg, bc);
+  if (threadIdx.x == 0) {
+    a.prop[i] = bc == kNoComm ? -1 : bc;
+    a.gp[i] = bg;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_rhub_propose(RefineArgs a, int chunks) {
+  __shared__ union {
+    RHubGatherLds gather;
+    BlockTable<256, 8, 4096> table;
+  } l;
+  if ((int)blockIdx.x < chunks) rhub_gather_chunk(a, a.qbeg + blockIdx.x, l.gather);
+  else rhub_propose<256, 8, 4096>(a, a.hbeg + blockIdx.x - chunks, 0, kHubDeg, l.table);
+}
+__global__ __launch_bounds__(512) void k_rhub_propose_wide(RefineArgs a) {
+  __shared__ BlockTable<512, 12, 8192> l;
+  rhub_propose<512, 12, 8192>(a, a.hbeg + blockIdx.x, kHubDeg, kWideDeg, l);
+}
+__global__ __launch_bounds__(256) void k_rhub_score_final(RefineArgs a) {
+  const int64_t q = a.gbeg + blockIdx.x;
+  const int h = a.hp.shub[q];
+  const int i = a.hp.hubv[h];
+  if (!a.act[i]) return;
+  double bg;
+  int bc;
+  rhub_score_segment(a, q, h, i, bg, bc);
+  if (!hub_last_segment(a.hp, h, q, bg, bc)) return;
+  hub_reduce_segments(a.hp, h, bg, bc);
+  if (threadIdx.x == 0) {
+    a.prop[i] = bc == kNoComm ? -1 : bc;
+    a.gp[i] = bg;
+  }
+}
+
+void refine_hubs(const RefineArgs &a, const int64_t *region_h, bool wide, hipStream_t s) {
+  const int nh = (int)(a.hend - a.hbeg), nq = (int)(a.qend - a.qbeg);
+  if (nh <= 0) return;
+  hipLaunchKernelGGL(k_rhub_propose, nq + nh, 256, 0, s, a, nq);
+  if (nq > 0) hipLaunchKernelGGL(k_rhub_score_final, (int)(a.gend - a.gbeg), 256, 0, s, a);
+  else if (wide) hipLaunchKernelGGL(k_rhub_propose_wide, nh, 512, 0, s, a);
+  // only hubs have proposals: their bucket alone
+  const int64_t beg = region_h[a.s * kNB + kNB - 1], end = region_h[(a.s + 1) * kNB];
   if (end > beg) hipLaunchKernelGGL(k_raccept, flat_grid(end - beg), 256, 0, s, a, beg, end);
 }
 

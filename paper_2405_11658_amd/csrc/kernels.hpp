@@ -136,6 +136,9 @@ int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipSt
 // slice, each split into edge chunks (one gather workgroup each) and owning
 // a global open-addressing table split into scoring segments.
 constexpr int64_t kHubDeg = 2048;  // degree above which a vertex is a hub
+// Degree up to which a workgroup of 512 threads reads all edges of a hub at
+// once (up to kHubDeg: of 256 threads; asynchronous mode).
+constexpr int64_t kWideDeg = 6144;
 constexpr int kHubEC = 512;        // edges per gather workgroup
 constexpr int kHubSeg = 4096;      // table slots per scoring workgroup
 constexpr int64_t kHubMinCap = 256; // smallest hub table (a power of two)
@@ -154,6 +157,7 @@ struct HubPlan {
   double *pg;      // per-segment best gain
   int32_t *pc;     // per-segment best community
   int32_t *flag;   // [nhub] 1 when the hub's move is blocked (reset by the final reduction)
+  int32_t *done;   // [nhub] segments of the hub scored so far (k_hub_score_final; back at 0 after the last)
 };
 
 struct MoveArgs {
@@ -216,8 +220,10 @@ void slice_scatter(int64_t n, int S, const int32_t *slice_off, int32_t *slice_fi
 // into hch, htab, hsg); expansion into chub / shub; bounds[k] = arr[at[k]].
 void hub_find(const int64_t *off, int64_t n, int S, int64_t hubdeg, const int32_t *hub_soff, int32_t *hub_fill,
               int32_t *hubv, hipStream_t s);
+// Hubs of degree <= kHubDeg have no chunks and tables; nbig = 1 for those above
+// it, 2^32 for those above kWideDeg.
 void hub_sizes(const int64_t *off, const int32_t *hubv, int64_t nhub, int64_t *nch, int64_t *ncap, int64_t *nseg,
-               hipStream_t s);
+               int64_t *nbig, hipStream_t s);
 void hub_expand(const HubPlan &h, int64_t nhub, hipStream_t s);
 void hub_rel(int64_t *htab, int64_t nhub, const int32_t *hub_soff, int S, const int64_t *slice_base, hipStream_t s);
 void gather_bounds(const int64_t *arr, const int32_t *at, int count, int64_t *out, hipStream_t s);
@@ -230,6 +236,10 @@ void move_apply_bucket(const MoveArgs &a, const int64_t *region_h, int b, hipStr
 void move_hub_gather(const MoveArgs &a, hipStream_t s);
 void move_hub_score(const MoveArgs &a, hipStream_t s);
 void move_apply(const MoveArgs &a, const int64_t *region_h, hipStream_t s);
+// Asynchronous mode: the hubs of the slice, a workgroup each up to degree
+// kHubDeg (up to kWideDeg when the slice has no chunks: qbeg == qend), the
+// others in chunks; wide: the slice has hubs in (kHubDeg, kWideDeg].
+void move_hubs(const MoveArgs &a, bool wide, hipStream_t s);
 // out = sum of gi in ascending 256-tiles then sequentially (fixed order).
 void tiled_sum(const double *gi, int64_t n, double *tiles, double *out, hipStream_t s);
 
@@ -276,6 +286,8 @@ void refine_break(const RefineArgs &a, hipStream_t s);
 void refine_propose_bucket(const RefineArgs &a, const int64_t *region_h, int b, hipStream_t s);
 void refine_propose(const RefineArgs &a, const int64_t *region_h, hipStream_t s);
 void refine_accept(const RefineArgs &a, const int64_t *region_h, hipStream_t s);
+// Asynchronous mode: the hub candidates of the slice, proposed and accepted.
+void refine_hubs(const RefineArgs &a, const int64_t *region_h, bool wide, hipStream_t s);
 
 // ---- k_async.hip ---------------------------------------------------------------
 constexpr int kAsyncChunk = 64;  // vertex ids taken per grab of the asynchronous sweeps
