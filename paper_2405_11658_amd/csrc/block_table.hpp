@@ -94,7 +94,11 @@ __device__ __forceinline__ bool hub_last_segment(const HubPlan &p, int h, int64_
     __hip_atomic_store(&p.pg[q], bg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&p.pc[q], bc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int n = (int)(p.hsg[h + 1] - p.hsg[h]);
-    const int done = __hip_atomic_fetch_add(&p.done[h], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    // the stores above have reached memory before the count (a wait; a release
+    // at device scope would write the L2 back, for every workgroup)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    const int done = __hip_atomic_fetch_add(&p.done[h], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     last = done == n - 1;
     if (last) p.done[h] = 0;
   }

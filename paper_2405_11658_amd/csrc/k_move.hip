@@ -342,14 +342,30 @@ __device__ __forceinline__ void hub_score_segment(const MoveArgs &a, int64_t q, 
   const double Ki = a.K[i], Sd = a.Sig[d], bown = a.hp.own[h];
   bg = 0.0;
   bc = kNoComm;
-  for (int64_t s = s0 + threadIdx.x; s < s1; s += blockDim.x) {
-    const int c = a.hp.keys[s];
-    if (c == kEmpty) continue;
-    const double v = a.hp.vals[s];
+  // the thread's slots in three rounds of loads: keys, then weights and Sigma,
+  // each round's together
+  constexpr int PER = kHubSeg / 256;
+  int c[PER];
+  double v[PER], S[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t s = s0 + threadIdx.x + u * 256;
+    c[u] = s < s1 ? a.hp.keys[s] : kEmpty;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t s = s0 + threadIdx.x + u * 256;
+    v[u] = c[u] != kEmpty ? a.hp.vals[s] : 0.0;
+    S[u] = c[u] != kEmpty ? a.Sig[c[u]] : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (c[u] == kEmpty) continue;
+    const int64_t s = s0 + threadIdx.x + u * 256;
     a.hp.keys[s] = kEmpty;
     a.hp.vals[s] = 0.0;
-    const double x = move_score(a.M2, v, bown, Ki, a.Sig[c], Sd);
-    if (x > 0.0 && better(x, c, bg, bc)) { bg = x; bc = c; }
+    const double x = move_score(a.M2, v[u], bown, Ki, S[u], Sd);
+    if (x > 0.0 && better(x, c[u], bg, bc)) { bg = x; bc = c[u]; }
   }
   team_argmax<256, 256>(bg, bc, rg, rc);
 }
@@ -789,9 +805,15 @@ __global__ __launch_bounds__(256) void k_hub_propose(MoveArgs a, int chunks) {
   if ((int)blockIdx.x < chunks) hub_gather_chunk(a, a.qbeg + blockIdx.x, l.gather);
   else hub_propose<256, 8, 4096>(a, a.hbeg + blockIdx.x - chunks, 0, kHubDeg, l.table);
 }
-__global__ __launch_bounds__(512) void k_hub_propose_wide(MoveArgs a) {
-  __shared__ BlockTable<512, 12, 8192> l;
-  hub_propose<512, 12, 8192>(a, a.hbeg + blockIdx.x, kHubDeg, kWideDeg, l);
+// One kind of hub of a large slice: degree in (lo, hi].
+template <int PER, int SLOTS>
+__global__ __launch_bounds__(256) void k_hub_propose_kind(MoveArgs a, int64_t lo, int64_t hi) {
+  __shared__ BlockTable<256, PER, SLOTS> l;
+  hub_propose<256, PER, SLOTS>(a, a.hbeg + blockIdx.x, lo, hi, l);
+}
+__global__ __launch_bounds__(kWideT) void k_hub_propose_wide(MoveArgs a, int64_t lo) {
+  __shared__ BlockTable<kWideT, kWidePer, 8192> l;
+  hub_propose<kWideT, kWidePer, 8192>(a, a.hbeg + blockIdx.x, lo, kWideDeg, l);
 }
 
 // Scores the segments of the chunked hubs; a hub's last one to finish reduces
@@ -853,9 +875,18 @@ __global__ __launch_bounds__(256) void k_hub_apply(MoveArgs a, int chunks, int64
 void move_hubs(const MoveArgs &a, bool wide, hipStream_t s) {
   const int nh = (int)(a.hend - a.hbeg), nq = (int)(a.qend - a.qbeg);
   if (nh <= 0) return;
-  hipLaunchKernelGGL(k_hub_propose, nq + nh, 256, 0, s, a, nq);
+  // the large workgroups, one a CU, take all hubs of a slice while they find
+  // a CU each
+  const bool all = nq == 0 && wide && nh <= kWideAll;
+  if (nq + nh > kShareLaunch) {
+    move_hub_gather(a, s);
+    hipLaunchKernelGGL((k_hub_propose_kind<2, 1024>), nh, 256, 0, s, a, (int64_t)0, kSmallHubDeg);
+    hipLaunchKernelGGL((k_hub_propose_kind<8, 4096>), nh, 256, 0, s, a, kSmallHubDeg, kHubDeg);
+  } else if (!all) {
+    hipLaunchKernelGGL(k_hub_propose, nq + nh, 256, 0, s, a, nq);
+  }
   if (nq > 0) hipLaunchKernelGGL(k_hub_score_final, (int)(a.gend - a.gbeg), 256, 0, s, a);
-  else if (wide) hipLaunchKernelGGL(k_hub_propose_wide, nh, 512, 0, s, a);
+  else if (wide) hipLaunchKernelGGL(k_hub_propose_wide, nh, kWideT, 0, s, a, all ? 0 : kHubDeg);
   hipLaunchKernelGGL(k_hub_apply, nq + nh, 256, 0, s, a, nq, nq > 0 ? kHubDeg : kWideDeg);
   if (nq > 0) hipLaunchKernelGGL(k_hub_mark, nq, 256, 0, s, a);
 }

@@ -334,14 +334,30 @@ __device__ __forceinline__ void rhub_score_segment(const RefineArgs &a, int64_t 
   const double Ki = a.K[i], Sd = a.Sig[i], bown = a.hp.own[h];
   bg = 0.0;
   bc = kNoComm;
-  for (int64_t s = s0 + threadIdx.x; s < s1; s += blockDim.x) {
-    const int c = a.hp.keys[s];
-    if (c == kEmpty) continue;
-    const double v = a.hp.vals[s];
+  // the thread's slots in three rounds of loads: keys, then weights and Sigma,
+  // each round's together
+  constexpr int PER = kHubSeg / 256;
+  int c[PER];
+  double v[PER], S[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t s = s0 + threadIdx.x + u * 256;
+    c[u] = s < s1 ? a.hp.keys[s] : kEmpty;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t s = s0 + threadIdx.x + u * 256;
+    v[u] = c[u] != kEmpty ? a.hp.vals[s] : 0.0;
+    S[u] = c[u] != kEmpty ? a.Sig[c[u]] : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (c[u] == kEmpty) continue;
+    const int64_t s = s0 + threadIdx.x + u * 256;
     a.hp.keys[s] = kEmpty;
     a.hp.vals[s] = 0.0;
-    const double x = move_score(a.M2, v, bown, Ki, a.Sig[c], Sd);
-    if (x > 0.0 && better(x, c, bg, bc)) { bg = x; bc = c; }
+    const double x = move_score(a.M2, v[u], bown, Ki, S[u], Sd);
+    if (x > 0.0 && better(x, c[u], bg, bc)) { bg = x; bc = c[u]; }
   }
   team_argmax<256, 256>(bg, bc, rg, rc);
 }
@@ -470,9 +486,14 @@ __global__ __launch_bounds__(256) void k_rhub_propose(RefineArgs a, int chunks) 
   if ((int)blockIdx.x < chunks) rhub_gather_chunk(a, a.qbeg + blockIdx.x, l.gather);
   else rhub_propose<256, 8, 4096>(a, a.hbeg + blockIdx.x - chunks, 0, kHubDeg, l.table);
 }
-__global__ __launch_bounds__(512) void k_rhub_propose_wide(RefineArgs a) {
-  __shared__ BlockTable<512, 12, 8192> l;
-  rhub_propose<512, 12, 8192>(a, a.hbeg + blockIdx.x, kHubDeg, kWideDeg, l);
+template <int PER, int SLOTS>
+__global__ __launch_bounds__(256) void k_rhub_propose_kind(RefineArgs a, int64_t lo, int64_t hi) {
+  __shared__ BlockTable<256, PER, SLOTS> l;
+  rhub_propose<256, PER, SLOTS>(a, a.hbeg + blockIdx.x, lo, hi, l);
+}
+__global__ __launch_bounds__(kWideT) void k_rhub_propose_wide(RefineArgs a, int64_t lo) {
+  __shared__ BlockTable<kWideT, kWidePer, 8192> l;
+  rhub_propose<kWideT, kWidePer, 8192>(a, a.hbeg + blockIdx.x, lo, kWideDeg, l);
 }
 __global__ __launch_bounds__(256) void k_rhub_score_final(RefineArgs a) {
   const int64_t q = a.gbeg + blockIdx.x;
@@ -493,9 +514,16 @@ __global__ __launch_bounds__(256) void k_rhub_score_final(RefineArgs a) {
 void refine_hubs(const RefineArgs &a, const int64_t *region_h, bool wide, hipStream_t s) {
   const int nh = (int)(a.hend - a.hbeg), nq = (int)(a.qend - a.qbeg);
   if (nh <= 0) return;
-  hipLaunchKernelGGL(k_rhub_propose, nq + nh, 256, 0, s, a, nq);
+  const bool all = nq == 0 && wide && nh <= kWideAll;
+  if (nq + nh > kShareLaunch) {
+    if (nq > 0) hipLaunchKernelGGL(k_rhub_gather, nq, 256, 0, s, a);
+    hipLaunchKernelGGL((k_rhub_propose_kind<2, 1024>), nh, 256, 0, s, a, (int64_t)0, kSmallHubDeg);
+    hipLaunchKernelGGL((k_rhub_propose_kind<8, 4096>), nh, 256, 0, s, a, kSmallHubDeg, kHubDeg);
+  } else if (!all) {
+    hipLaunchKernelGGL(k_rhub_propose, nq + nh, 256, 0, s, a, nq);
+  }
   if (nq > 0) hipLaunchKernelGGL(k_rhub_score_final, (int)(a.gend - a.gbeg), 256, 0, s, a);
-  else if (wide) hipLaunchKernelGGL(k_rhub_propose_wide, nh, 512, 0, s, a);
+  else if (wide) hipLaunchKernelGGL(k_rhub_propose_wide, nh, kWideT, 0, s, a, all ? 0 : kHubDeg);
   // only hubs have proposals: their bucket alone
   const int64_t beg = region_h[a.s * kNB + kNB - 1], end = region_h[(a.s + 1) * kNB];
   if (end > beg) hipLaunchKernelGGL(k_raccept, flat_grid(end - beg), 256, 0, s, a, beg, end);

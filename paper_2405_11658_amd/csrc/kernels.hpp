@@ -136,9 +136,21 @@ int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipSt
 // slice, each split into edge chunks (one gather workgroup each) and owning
 // a global open-addressing table split into scoring segments.
 constexpr int64_t kHubDeg = 2048;  // degree above which a vertex is a hub
-// Degree up to which a workgroup of 512 threads reads all edges of a hub at
-// once (up to kHubDeg: of 256 threads; asynchronous mode).
+// Degree up to which a large workgroup reads all edges of a hub at once (up
+// to kHubDeg: one of 256 threads; asynchronous mode).
 constexpr int64_t kWideDeg = 6144;
+constexpr int kWideT = 512, kWidePer = (int)kWideDeg / kWideT;
+// Hubs of a slice up to which the large workgroups (98 KB of LDS, one a CU)
+// take them all, instead of a launch for each size: 256 CUs.  Two updates of
+// 524,288 vertices 38.8 -> 35.9 ms, of 8.4M 147.5 -> 141.4; 1024 threads with
+// 6 edges each: no difference.
+constexpr int kWideAll = 256;
+// Workgroups of a slice up to which its hubs and chunks share one launch (49
+// KB of LDS for either, three a CU); larger slices are bound by how many
+// workgroups a CU holds, not by the chain of launches, and get launches with
+// the LDS that each kind needs (hubs of at most kSmallHubDeg edges: 12 KB).
+constexpr int kShareLaunch = 768;
+constexpr int64_t kSmallHubDeg = 512;
 constexpr int kHubEC = 512;        // edges per gather workgroup
 constexpr int kHubSeg = 4096;      // table slots per scoring workgroup
 constexpr int64_t kHubMinCap = 256; // smallest hub table (a power of two)
