@@ -78,12 +78,86 @@ __device__ __forceinline__ double lane_value(double x, int l) {
   const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
+__device__ __forceinline__ int64_t lane_value64(int64_t x, int l) {
+  const int lo = __builtin_amdgcn_readlane((int)x, l), hi = __builtin_amdgcn_readlane((int)(x >> 32), l);
+  return ((int64_t)hi << 32) | (unsigned int)lo;
+}
 __device__ __forceinline__ double wave_sum(double v) {
   v += dpp_move<kDppXor1>(v);
   v += dpp_move<kDppXor2>(v);
   v += dpp_move<kDppHalfMirror>(v);
   v += dpp_move<kDppMirror>(v);
   return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+// x of the lane ^ J, the lane before (0 in lane 0) and the lane after (0 in
+// lane 63), without the LDS pipe.
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+  if constexpr (J == 1) {
+    return (uint32_t)dpp_move<kDppXor1>((int)x);
+  } else if constexpr (J == 2) {
+    return (uint32_t)dpp_move<kDppXor2>((int)x);
+  } else if constexpr (J == 4) {
+    return (uint32_t)dpp_move<0x1B>(dpp_move<kDppHalfMirror>((int)x));  // (l ^ 7) ^ 3
+  } else if constexpr (J == 8) {
+    return (uint32_t)dpp_move<0x128>((int)x);  // row_ror:8
+  } else if constexpr (J == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return (lane() & 16) ? r[0] : r[1];
+  } else {
+    static_assert(J == 32, "a power of two below the wavefront");
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return (lane() & 32) ? r[0] : r[1];
+  }
+}
+template <int J>
+__device__ __forceinline__ float lane_xor(float x) {
+  return __uint_as_float(lane_xor<J>(__float_as_uint(x)));
+}
+constexpr int kDppWaveShr1 = 0x138, kDppWaveShl1 = 0x130;
+template <class T>
+__device__ __forceinline__ T lane_before(T x) {
+  return (T)dpp_move<kDppWaveShr1>((int)x);
+}
+__device__ __forceinline__ double lane_before(double x) { return dpp_move<kDppWaveShr1>(x); }
+template <class T>
+__device__ __forceinline__ T lane_after(T x) {
+  return (T)dpp_move<kDppWaveShl1>((int)x);
+}
+constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
+// Inclusive prefix sum over the lanes; *tot the wavefront's.
+__device__ __forceinline__ int wave_scan(int x, int *tot) {
+  x += dpp_move<kDppRowShr1>(x);
+  x += dpp_move<kDppRowShr2>(x);
+  x += dpp_move<kDppRowShr4>(x);
+  x += dpp_move<kDppRowShr8>(x);
+  const int a = lane_value(x, 15), b = a + lane_value(x, 31), c = b + lane_value(x, 47);
+  *tot = c + lane_value(x, 63);
+  const int r = lane() >> 4;
+  return x + (r == 0 ? 0 : r == 1 ? a : r == 2 ? b : c);
+}
+template <int CTRL>
+__device__ __forceinline__ void dpp_seg_add(double &x, int &f) {
+  const double y = dpp_move<CTRL>(x);
+  const int yf = dpp_move<CTRL>(f);
+  if (!f) x += y;
+  f |= yf;
+}
+// Segmented inclusive sum over the lanes (f: the lane starts a segment); on
+// return f says whether any lane up to this one does.
+__device__ __forceinline__ void wave_seg_scan(double &x, int &f) {
+  dpp_seg_add<kDppRowShr1>(x, f);
+  dpp_seg_add<kDppRowShr2>(x, f);
+  dpp_seg_add<kDppRowShr4>(x, f);
+  dpp_seg_add<kDppRowShr8>(x, f);
+  const unsigned long long fl = __ballot(f);
+  // sums open at the ends of the rows before
+  const double a = lane_value(x, 15);
+  const double b = (fl >> 31) & 1ull ? lane_value(x, 31) : a + lane_value(x, 31);
+  const double c = (fl >> 47) & 1ull ? lane_value(x, 47) : b + lane_value(x, 47);
+  const int r = lane() >> 4;
+  if (!f) x += r == 0 ? 0.0 : r == 1 ? a : r == 2 ? b : c;
+  f = (fl & (~0ull >> (63 - lane()))) != 0;
 }
 template <int CTRL>
 __device__ __forceinline__ void dpp_argmax(double &g, int &c) {

@@ -134,163 +134,119 @@ void agg_group(const AggArgs &a, const int32_t *crow, const int32_t *pos, const 
 // segment is a chain of dependent steps, so a level needs as many wavefronts
 // as it has communities, up to the 32768 of the grid: with 64 communities for
 // every wavefront a level of 700 communities ran on 11 wavefronts (190 us,
-// 44 us with one each), one of 780,000 on 12,000 (4.8 ms, 3.7 ms).  Up to 64 entries are sorted in registers with a
-// bitonic network over the lanes, up to 256 with the same network over R = 2
-// or 4 registers per lane, larger ones (up to 1024) in the wavefront's LDS
-// area (more registers per lane would spill).
-// The network is data-oblivious and exchanges only strictly ordered pairs,
-// so equal keys end in an order fixed by the input.  Runs of equal keys are
-// summed with a segmented scan (fixed tree), each run written at its rank in
-// the row; K' is the sum of the stored row weights (fixed tree).
+// 44 us with one each).  The segment is sorted in registers with a bitonic
+// network, R = 1 to 16 registers per lane.  The network is data-oblivious and
+// exchanges only strictly ordered pairs, so equal keys end in an order fixed
+// by the input.  Runs of equal keys are summed with a segmented scan (fixed
+// tree), each run written at its rank in the row; K' is the sum of the stored
+// row weights (fixed tree).  Exchanges, scans and sums between lanes are DPP
+// and lane-swap moves: LDS permutes, ~100 a segment, left the kernel at the
+// rate of the CU's one LDS pipe (3.2M segments of ~50 entries 3.7 -> 2.0 ms;
+// 61,000 of 65 to 1024 entries 1.6 -> 0.6 ms, those above 256 in LDS before).
 constexpr uint32_t kKeyPad = 0xffffffffu;  // above every community id
 
-// Orders a wavefront's own LDS accesses (one wavefront's LDS operations
-// execute in issue order; this keeps the compiler from reordering them).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-__device__ __forceinline__ int blk_excl_int(int x, int *tot, int *sw) {
-  int incl = x;
+// The bitonic network over the blocked layout of small_segment.  Distances of
+// at least R are between lanes (lane distance LJ), smaller ones between the
+// registers of a lane; up: the block of the positions sorts upwards.
+template <int R, int LJ>
+__device__ __forceinline__ void exchange_lanes(uint32_t (&key)[R], float (&v)[R], bool up) {
+  const bool least = ((lane() & LJ) == 0) == up;  // keeps the smaller key of the pair
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(incl, o);
-    if (lane() >= o) incl += y;
-  }
-  const int w = (int)threadIdx.x / kWave;
-  if (lane() == kWave - 1) sw[w] = incl;
-  __syncthreads();
-  int pre = 0, all = 0;
-  for (int k = 0; k < (int)blockDim.x / kWave; ++k) {
-    if (k < w) pre += sw[k];
-    all += sw[k];
-  }
-  __syncthreads();
-  *tot = all;
-  return pre + incl - x;
-}
-
-__device__ __forceinline__ void seg_scan(double &x, int &f) {
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const double yx = __shfl_up(x, o);
-    const int yf = __shfl_up(f, o);
-    if (lane() >= o) {
-      if (!f) x += yx;
-      f |= yf;
-    }
+  for (int r = 0; r < R; ++r) {
+    const uint32_t ok = lane_xor<LJ>(key[r]);
+    const float ov = lane_xor<LJ>(v[r]);
+    const bool take = least ? ok < key[r] : ok > key[r];
+    key[r] = take ? ok : key[r];
+    v[r] = take ? ov : v[r];
   }
 }
-
-__device__ __forceinline__ void small_regs(const uint32_t *gkey, const float *gval, int64_t sb, int sl, int c,
-                                           uint32_t *ukey, float *uval, double *u64, int32_t *rowlen, double *K) {
-  uint32_t key = kKeyPad;
-  float v = 0.0f;
-  if (lane() < sl) {
-    key = gkey[sb + lane()];
-    v = gval[sb + lane()];
-  }
-#pragma unroll
-  for (int k = 2; k <= kWave; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const uint32_t ok = __shfl_xor(key, j);
-      const float ov = __shfl_xor(v, j);
-      const bool up = (lane() & k) == 0;
-      const bool low = (lane() & j) == 0;
-      // ascending pairs: the lower lane keeps the smaller key
-      const bool take = (low == up) ? ok < key : ok > key;
-      if (take) {
-        key = ok;
-        v = ov;
-      }
-    }
-  }
-  const bool act = lane() < sl;
-  const uint32_t pk = __shfl_up(key, 1), nk = __shfl_down(key, 1);
-  const bool head = act && (lane() == 0 || pk != key);
-  const bool rend = act && (lane() == sl - 1 || nk != key);
-  double x = act ? (double)v : 0.0;
-  int f = head ? 1 : 0;
-  seg_scan(x, f);
-  const unsigned long long hm = __ballot(head);
-  const int rank = __popcll(hm & ((2ull << lane()) - 1ull)) - 1;
-  double kx = 0.0;
-  if (rend) {
-    const float wf = (float)x;
-    ukey[sb + rank] = key;
-    uval[sb + rank] = wf;
-    if (u64) u64[sb + rank] = x;
-    kx = (double)wf;
-  }
-  kx = group_sum<kWave>(kx);
-  if (lane() == 0) {
-    rowlen[c] = __popcll(hm);
-    if (K) K[c] = kx;
-  }
+template <int R, int J>
+__device__ __forceinline__ void exchange_regs(uint32_t (&key)[R], float (&v)[R], int r, bool up) {
+  const int q = r | J;
+  // selects, not a branch around a swap: those become copies under an exec mask
+  const uint32_t a = key[r], b = key[q];
+  const float x = v[r], y = v[q];
+  const bool swap = up ? a > b : a < b;
+  key[r] = swap ? b : a;
+  key[q] = swap ? a : b;
+  v[r] = swap ? y : x;
+  v[q] = swap ? x : y;
 }
-
-// One exchange step (block size K, distance J) of the bitonic network over
-// the blocked layout of small_wide, then the following steps of the block.
+// Distances J, J/2, .. 1 inside the lanes, direction `up` (blocks of at least
+// R) or by register (blocks of K < R).
 template <int R, int K, int J>
-__device__ __forceinline__ void bitonic_step(uint32_t (&key)[R], float (&v)[R]) {
-  if constexpr (J >= R) {
-    constexpr int LJ = J / R;
-    const bool low = (lane() & LJ) == 0;
-    const bool up = ((lane() * R) & K) == 0;
+__device__ __forceinline__ void merge_regs(uint32_t (&key)[R], float (&v)[R], bool up) {
+  if constexpr (J > 0) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint32_t ok = __shfl_xor(key[r], LJ);
-      const float ov = __shfl_xor(v[r], LJ);
-      const bool take = (low == up) ? ok < key[r] : ok > key[r];
-      if (take) {
-        key[r] = ok;
-        v[r] = ov;
-      }
-    }
+    for (int r = 0; r < R; ++r)
+      if (!(r & J)) exchange_regs<R, J>(key, v, r, K < R ? (r & K) == 0 : up);
+    merge_regs<R, K, J / 2>(key, v, up);
+  }
+}
+// Blocks of 2, 4, .. R positions.
+template <int R, int K>
+__device__ __forceinline__ void sort_regs(uint32_t (&key)[R], float (&v)[R]) {
+  if constexpr (K <= R) {
+    merge_regs<R, K, K / 2>(key, v, (lane() * R & K) == 0);
+    sort_regs<R, 2 * K>(key, v);
+  }
+}
+template <int R, int LJ>
+__device__ __forceinline__ void merge_lanes(uint32_t (&key)[R], float (&v)[R], bool up) {
+  exchange_lanes<R, LJ>(key, v, up);
+  if constexpr (LJ > 1) merge_lanes<R, LJ / 2>(key, v, up);
+}
+// Blocks of 2 * R positions up to all 64 * R.  With up to 4 registers the
+// steps are unrolled; with more the straight code (~6000 instructions for 16)
+// would be fetched from memory for every segment, so the steps between lanes
+// are a loop over a switch of the six distances.
+template <int R, int LK>
+__device__ __forceinline__ void sort_lanes(uint32_t (&key)[R], float (&v)[R]) {
+  if constexpr (LK <= kWave) {
+    const bool up = (lane() & LK) == 0;  // LK = 64: all lanes
+    merge_lanes<R, LK / 2>(key, v, up);
+    merge_regs<R, R, R / 2>(key, v, up);
+    sort_lanes<R, 2 * LK>(key, v);
+  }
+}
+template <int R>
+__device__ __forceinline__ void bitonic_sort(uint32_t (&key)[R], float (&v)[R]) {
+  sort_regs<R, 2>(key, v);
+  if constexpr (R <= 4) {
+    sort_lanes<R, 2>(key, v);
   } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (r & J) continue;
-      const int q = r | J;
-      const bool up = K < R ? (r & K) == 0 : ((lane() * R) & K) == 0;
-      if (up ? key[r] > key[q] : key[r] < key[q]) {
-        const uint32_t tk = key[r];
-        key[r] = key[q];
-        key[q] = tk;
-        const float tv = v[r];
-        v[r] = v[q];
-        v[q] = tv;
+#pragma unroll 1
+    for (int b = 1; b <= 6; ++b) {
+      const bool up = (lane() >> b & 1) == 0;
+#pragma unroll 1
+      for (int d = b - 1; d >= 0; --d) {
+        switch (d) {
+          case 0: exchange_lanes<R, 1>(key, v, up); break;
+          case 1: exchange_lanes<R, 2>(key, v, up); break;
+          case 2: exchange_lanes<R, 4>(key, v, up); break;
+          case 3: exchange_lanes<R, 8>(key, v, up); break;
+          case 4: exchange_lanes<R, 16>(key, v, up); break;
+          default: exchange_lanes<R, 32>(key, v, up);
+        }
       }
+      merge_regs<R, R, R / 2>(key, v, up);
     }
   }
-  if constexpr (J > 1) bitonic_step<R, K, J / 2>(key, v);
-}
-// Blocks of size K, 2K, ... up to the whole 64 * R positions.
-template <int R, int K>
-__device__ __forceinline__ void bitonic_regs(uint32_t (&key)[R], float (&v)[R]) {
-  bitonic_step<R, K, K / 2>(key, v);
-  if constexpr (K < kWave * R) bitonic_regs<R, 2 * K>(key, v);
 }
 
-// Segments of 65 .. 64 * R entries in registers: lane L holds the R
+// Segments of at most 64 * R entries in registers: lane L holds the R
 // consecutive positions L * R .. L * R + R - 1 (keys padded with kKeyPad).
-// The bitonic network's exchanges at distance j < R stay inside a lane (the
-// register indices are compile-time constants once the loops are unrolled);
-// at distance j >= R the partner is lane L ^ (j / R), same register.  As
-// above, only strictly ordered pairs are exchanged.  The runs are then
-// summed in position order: each lane in order over its registers, the run
-// open at a lane's start taken from the lanes before it by a segmented scan
-// over the lanes (fixed tree).
+// The runs of the sorted keys are summed in position order: each lane in
+// order over its registers, the run open at a lane's start taken from the
+// lanes before it by a segmented scan over the lanes (fixed tree).
 template <int R>
-__device__ __forceinline__ void small_wide(const uint32_t *gkey, const float *gval, int64_t sb, int sl, int c,
+__device__ __forceinline__ void small_segment(const uint32_t *gkey, const float *gval, int64_t sb, int sl, int c,
                                            uint32_t *ukey, float *uval, double *u64, int32_t *rowlen, double *K) {
   uint32_t key[R];
   float v[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int e = lane() * R + r;
+    const int e = r * kWave + lane();  // any order: they are sorted next
     key[r] = kKeyPad;
     v[r] = 0.0f;
     if (e < sl) {
@@ -298,10 +254,10 @@ __device__ __forceinline__ void small_wide(const uint32_t *gkey, const float *gv
       v[r] = gval[sb + e];
     }
   }
-  bitonic_regs<R, 2>(key, v);
+  bitonic_sort<R>(key, v);
   // heads and run ends; position e = lane * R + r is valid below sl
-  const uint32_t prevk = __shfl_up(key[R - 1], 1);
-  const uint32_t nextk = __shfl_down(key[0], 1);
+  const uint32_t prevk = lane_before(key[R - 1]);
+  const uint32_t nextk = lane_after(key[0]);
   bool head[R], rend[R];
   int nh = 0;
 #pragma unroll
@@ -323,18 +279,11 @@ __device__ __forceinline__ void small_wide(const uint32_t *gkey, const float *gv
   }
   double t = tail;
   int f = nh > 0 ? 1 : 0;
-  seg_scan(t, f);  // t: run open at the end of this lane
-  double carry = __shfl_up(t, 1);
-  if (lane() == 0) carry = 0.0;
+  wave_seg_scan(t, f);  // t: run open at the end of this lane
+  const double carry = lane_before(t);  // 0 in lane 0
   // ranks: heads before this lane, then in register order
-  int hb = nh;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(hb, o);
-    if (lane() >= o) hb += y;
-  }
-  const int total = __shfl(hb, kWave - 1);
-  hb -= nh;
+  int total;
+  int hb = wave_scan(nh, &total) - nh;
   double acc = carry, kx = 0.0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -349,85 +298,25 @@ __device__ __forceinline__ void small_wide(const uint32_t *gkey, const float *gv
       kx += (double)wf;
     }
   }
-  kx = group_sum<kWave>(kx);
+  kx = wave_sum(kx);
   if (lane() == 0) {
     rowlen[c] = total;
     if (K) K[c] = kx;
   }
 }
 
-__device__ __forceinline__ void small_lds(const uint32_t *gkey, const float *gval, int64_t sb, int sl, int c,
-                                          uint32_t *sk, float *sv, uint32_t *ukey, float *uval, double *u64,
-                                          int32_t *rowlen, double *K) {
-  int P = 2 * kWave;
-  while (P < sl) P <<= 1;
-  wave_lds_fence();  // the previous segment's reads of this area are done
-  for (int p = lane(); p < P; p += kWave) {
-    sk[p] = p < sl ? gkey[sb + p] : kKeyPad;
-    sv[p] = p < sl ? gval[sb + p] : 0.0f;
-  }
-  wave_lds_fence();
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      // pair p: lower position i (bit j clear), upper i + j; every lane
-      // takes a pair in every round
-      for (int p = lane(); p < P / 2; p += kWave) {
-        const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1));
-        const int ix = i + j;
-        const uint32_t a = sk[i], b = sk[ix];
-        const bool up = (i & k) == 0;
-        if (up ? a > b : a < b) {
-          sk[i] = b;
-          sk[ix] = a;
-          const float t = sv[i];
-          sv[i] = sv[ix];
-          sv[ix] = t;
-        }
-      }
-      wave_lds_fence();
-    }
-  }
-  double carry = 0.0, kx = 0.0;
-  int heads = 0;
-  for (int base = 0; base < sl; base += kWave) {
-    const int p = base + lane();
-    const bool act = p < sl;
-    const uint32_t key = act ? sk[p] : kKeyPad;
-    const bool head = act && (p == 0 || sk[p - 1] != key);
-    const bool rend = act && (p == sl - 1 || sk[p + 1] != key);
-    double x = act ? (double)sv[p] : 0.0;
-    int f = head ? 1 : 0;
-    seg_scan(x, f);
-    if (!f) x += carry;  // the run open at the end of the previous chunk
-    const unsigned long long hm = __ballot(head);
-    const int rank = heads + __popcll(hm & ((2ull << lane()) - 1ull)) - 1;
-    if (rend) {
-      const float wf = (float)x;
-      ukey[sb + rank] = key;
-      uval[sb + rank] = wf;
-      if (u64) u64[sb + rank] = x;
-      kx += (double)wf;
-    }
-    carry = __shfl(x, kWave - 1);
-    heads += __popcll(hm);
-  }
-  kx = group_sum<kWave>(kx);
-  if (lane() == 0) {
-    rowlen[c] = heads;
-    if (K) K[c] = kx;
-  }
-}
-
+// LARGE: the segments of more than 4 * 64 entries (8 or 16 registers for the
+// keys and as many for the values: 2 wavefronts a SIMD instead of 8, so they
+// have a launch of their own).
+template <bool LARGE>
 __global__ __launch_bounds__(256) void k_agg_small(const int64_t *seg, int64_t ncomm, const uint32_t *gkey,
                                                    const float *gval, uint32_t *ukey, float *uval, double *u64,
                                                    int32_t *rowlen, double *K) {
   constexpr int W = 256 / kWave;
-  __shared__ uint32_t sk[W][kAggSmall];
-  __shared__ float sv[W][kAggSmall];
-  const int wid = (int)threadIdx.x / kWave;
+  constexpr int64_t lo = LARGE ? 4 * kWave : 0, hi = LARGE ? kAggSmall : 4 * kWave;
   // round r, wavefront w, lane q: community r * 64 * nw + q * nw + w
   const int64_t nw = (int64_t)gridDim.x * W;
-  const int64_t w = (int64_t)blockIdx.x * W + wid;
+  const int64_t w = (int64_t)blockIdx.x * W + threadIdx.x / kWave;
   for (int64_t base = 0; base < ncomm; base += nw * kWave) {
     const int64_t c = base + (int64_t)lane() * nw + w;
     int64_t b = 0, len = 0;
@@ -435,25 +324,30 @@ __global__ __launch_bounds__(256) void k_agg_small(const int64_t *seg, int64_t n
       b = seg[c];
       len = seg[c + 1] - b;
     }
-    unsigned long long todo = __ballot(len > 0 && len <= kAggSmall);
+    unsigned long long todo = __ballot(len > lo && len <= hi);
     while (todo) {
       const int k = __ffsll(todo) - 1;
       todo &= todo - 1ull;
-      const int64_t sb = __shfl(b, k);
-      const int sl = (int)__shfl(len, k);
-      const int ck = (int)__shfl(c, k);
-      if (sl <= kWave) small_regs(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
-      else if (sl <= 2 * kWave) small_wide<2>(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
-      else if (sl <= 4 * kWave) small_wide<4>(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
-      else small_lds(gkey, gval, sb, sl, ck, sk[wid], sv[wid], ukey, uval, u64, rowlen, K);
+      const int64_t sb = lane_value64(b, k);
+      const int sl = lane_value((int)len, k);
+      const int ck = lane_value((int)c, k);
+      if constexpr (LARGE) {
+        if (sl <= 8 * kWave) small_segment<8>(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
+        else small_segment<16>(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
+      } else {
+        if (sl <= kWave) small_segment<1>(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
+        else if (sl <= 2 * kWave) small_segment<2>(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
+        else small_segment<4>(gkey, gval, sb, sl, ck, ukey, uval, u64, rowlen, K);
+      }
     }
   }
 }
 void agg_small(const int64_t *seg, int64_t ncomm, const uint32_t *gkey, const float *gval, uint32_t *ukey,
                float *uval, double *u64, int32_t *rowlen, double *K, hipStream_t s) {
-  if (ncomm > 0)
-    hipLaunchKernelGGL(k_agg_small, flat_grid(ncomm, 4, 8192), 256, 0, s, seg, ncomm, gkey, gval, ukey, uval, u64,
-                       rowlen, K);
+  if (ncomm <= 0) return;
+  const int grid = flat_grid(ncomm, 4, 8192);
+  hipLaunchKernelGGL(k_agg_small<false>, grid, 256, 0, s, seg, ncomm, gkey, gval, ukey, uval, u64, rowlen, K);
+  hipLaunchKernelGGL(k_agg_small<true>, grid, 256, 0, s, seg, ncomm, gkey, gval, ukey, uval, u64, rowlen, K);
 }
 
 // ---- 5: large segments ----------------------------------------------------------
@@ -577,7 +471,7 @@ __global__ __launch_bounds__(256) void k_agg_lruns(const uint32_t *gkey, const f
   // open run at the end of each thread (inclusive), then exclusive carries
   double x = tail;
   int f = nh > 0 ? 1 : 0;
-  seg_scan(x, f);
+  wave_seg_scan(x, f);
   int hi = nh;
 #pragma unroll
   for (int o = 1; o < kWave; o <<= 1) {

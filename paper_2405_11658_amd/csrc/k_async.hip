@@ -445,11 +445,6 @@ __device__ __forceinline__ void best_move(const WaveTable &t, double M2, int d, 
 // single vertices (R-MAT scale 22, ten updates: 0.0703 and 0.0705, sd 1e-4).
 constexpr int kGroup = 4;
 
-__device__ __forceinline__ int64_t lane_value64(int64_t x, int l) {
-  const int lo = __builtin_amdgcn_readlane((int)x, l), hi = __builtin_amdgcn_readlane((int)(x >> 32), l);
-  return ((int64_t)hi << 32) | (unsigned int)lo;
-}
-
 // Maximum over the wavefront (uniform).
 __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
   x = max(x, (uint32_t)dpp_move<kDppXor1>((int)x));

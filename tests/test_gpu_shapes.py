@@ -61,3 +61,36 @@ def test_hub_degree_classes(degrees, slices):
     for mode, b in zip(("df", "nd", "ds"), gen.batch_stream(g, 200, 3, seed=3)):
         C, q, st, _ = L.leiden_update(h, dev_batch(b), mode)
         _check_state(h, _graph_of(h), C, q)
+
+
+@pytest.mark.parametrize("labels", [3, 50, 5000])
+@pytest.mark.parametrize("sizes", [
+    (1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 4096, 4097),
+    (300,) * 40 + (700,) * 30 + (1000,) * 10 + (5,) * 100,
+])
+def test_aggregate_segment_sizes(sizes, labels):
+    """Communities whose entries fill one wavefront's registers up to, and
+    one past, each size of the sorting network, with few and many equal
+    neighbour communities: rows equal to a sort in torch, weights within the
+    rounding of a float64 sum to float32 (2^-24 relative), and the same bits
+    on a second call."""
+    n, rows = 6000, len(sizes)
+    rng = np.random.default_rng(5)
+    cols = [np.sort(rng.permutation(n)[:z]) for z in sizes]
+    off = np.zeros(n + 1, np.int64)
+    off[1:rows + 1] = np.cumsum(sizes)
+    off[rows + 1:] = off[rows]
+    idx = np.concatenate(cols).astype(np.int32)
+    w = (rng.random(len(idx)) + 0.1).astype(np.float32)
+    k = max(labels, rows)
+    C = rng.integers(0, k, n).astype(np.int32)
+    C[:rows] = np.arange(rows)
+    say("aggregate segments", len(sizes), "labels", labels)
+    o, i, x = (to_np(t) for t in L.leiden_aggregate(off, idx, w, C, k))
+    key = np.repeat(C[:rows].astype(np.int64), sizes) * k + C[idx]
+    pair, inv = np.unique(key, return_inverse=True)
+    total = np.bincount(inv, weights=w.astype(np.float64))
+    assert np.array_equal(o, np.searchsorted(pair, np.arange(k + 1) * k))
+    assert np.array_equal(i, pair % k)
+    assert np.all(np.abs(x - total) <= 2.0 ** -24 * total * (1 + 1e-6))
+    assert np.array_equal(x, to_np(L.leiden_aggregate(off, idx, w, C, k)[2]))
