@@ -365,7 +365,10 @@ const char *leiden_fleet_last_error(const leiden_fleet *fleet);
 leiden_status leiden_fleet_destroy(leiden_fleet *fleet);
 
 /* Eq. 1 in FP64 for any CSR graph and membership (labels in [0, n));
- * q_out (host) is 0 when the graph has no edges.  Stateless. */
+ * q_out (host) is 0 when the graph has no edges.  Stateless; the working
+ * memory of this call and of leiden_aggregate is kept for their next calls
+ * (at most 2 GiB a device, none that 16 calls have left unused; given back
+ * when a handle is destroyed or an allocation of the library's fails). */
 leiden_status leiden_modularity(int64_t n, const int64_t *offsets, const int32_t *indices,
                                 const float *weights, const int32_t *membership, double *q_out,
                                 void *stream);

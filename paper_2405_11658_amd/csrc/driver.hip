@@ -207,9 +207,10 @@ struct Ctx {
     w->al.put(b.p, b.cap, s);
     b.p = nullptr;
     b.cap = 0;
-    void *p = w->al.get(want, s);
+    const size_t need = want;
+    void *p = w->al.get(&want, s);
     if (!p) {
-      w->err = "device allocation of " + std::to_string(want) + " bytes failed";
+      w->err = "device allocation of " + std::to_string(need) + " bytes failed";
       throw Fail{LEIDEN_ENOMEM};
     }
     b.p = p;
@@ -599,8 +600,15 @@ int64_t renumber_active_first(Ctx &x, int32_t *C, int64_t n, const int64_t *off,
 // rows' FP64 sums are kept too (*w64, one per stored entry).  Neighbour
 // labels are below nkey (ncomm when 0; fewer when the labels of communities
 // without edges come last, since no entry points to those).
+// out: arrays of the caller's for the result (idx and w of g.nnz entries),
+// instead of the level buffers; the level's crow is then left out.
+struct AggOut {
+  int64_t *off;
+  int32_t *idx;
+  float *w;
+};
 Level aggregate_level(Ctx &x, const Level &g, const int32_t *C, int64_t ncomm, int outbuf, double *Kout,
-                      double **w64 = nullptr, int64_t nkey = 0) {
+                      double **w64 = nullptr, int64_t nkey = 0, const AggOut *out = nullptr) {
   AggArgs a;
   memset(&a, 0, sizeof(a));
   a.n = g.n;
@@ -615,7 +623,7 @@ Level aggregate_level(Ctx &x, const Level &g, const int32_t *C, int64_t ncomm, i
   const Slot sw = outbuf == 2 ? L1_w : outbuf ? G1_w : G0_w;
   const Slot sc = outbuf == 2 ? L1_crow : outbuf ? G1_crow : G0_crow;
   double *v64 = (w64 && g.nnz > 0) ? x.get<double>(A_v64, g.nnz) : nullptr;
-  int64_t *out_off = x.get<int64_t>(so, ncomm + 1);
+  int64_t *out_off = out ? out->off : x.get<int64_t>(so, ncomm + 1);
   int32_t *rowlen = x.get<int32_t>(A_rowlen, ncomm + 1);
   x.zero(rowlen, ncomm + 1);
   if (Kout) x.zero(Kout, ncomm);
@@ -703,13 +711,18 @@ Level aggregate_level(Ctx &x, const Level &g, const int32_t *C, int64_t ncomm, i
   }
   scan_i32_i64(x, rowlen, out_off, ncomm + 1);
   const int64_t nu = g.nnz > 0 ? x.read(&out_off[ncomm]) : 0;
-  int32_t *out_idx = x.get<int32_t>(si, nu);
-  float *out_w = x.get<float>(sw, nu);
+  if (out && nu > 0 && (!out->idx || !out->w)) x.invalid("null output arrays");
+  int32_t *out_idx = out ? out->idx : x.get<int32_t>(si, nu);
+  float *out_w = out ? out->w : x.get<float>(sw, nu);
   double *out_w64 = v64 ? x.get<double>(L1_w64, nu) : nullptr;
   if (w64) *w64 = out_w64;
   if (g.nnz > 0)
     agg_compact(seg, ncomm, lc, lsb, tseg, ltn, ntl, rowlen, out_off, ukey, uval, lkey, lval, v64, out_idx, out_w,
                 out_w64, x.s);
+  if (out) {
+    x.launched("agg_rows");
+    return Level{ncomm, nu, out_off, out_idx, out_w, nullptr};
+  }
   int32_t *out_crow = x.get<int32_t>(sc, ceil_div(std::max<int64_t>(nu, 1), kChunk) + 2);
   chunk_start_rows(out_off, ncomm, nu, out_crow, x.s);
   x.launched("agg_rows");
@@ -1081,6 +1094,16 @@ leiden_status run_guarded(Workspace &w, const std::function<void()> &f) {
   }
 }
 
+// A stateless call keeps its working memory for the next one (ScratchCache).
+leiden_status run_stateless(Workspace &w, hipStream_t s, const std::function<void()> &f) {
+  w.al.scratch = true;
+  w.al.dev = stream_device(s);
+  const leiden_status st = run_guarded(w, f);
+  w.release(s);
+  w.al.end(s);
+  return st;
+}
+
 // Sort rows of a CSR in place (keys = neighbour ids, values = weights).
 void sort_rows(Ctx &x, int64_t n, int64_t nnz, int64_t *off, int32_t *idx, float *w, int32_t *idx2, float *w2) {
   if (nnz == 0) return;
@@ -1395,6 +1418,7 @@ leiden_status leiden_destroy(leiden_handle *h) {
   hipStream_t s = nullptr;
   if (h->used && h->order) (void)hipStreamWaitEvent(s, h->order, 0);
   h->release(s);
+  (void)scratch_cache().drop(stream_device(s), s);
   (void)hipGetLastError();
   delete h;
   return LEIDEN_OK;
@@ -1609,7 +1633,7 @@ leiden_status leiden_modularity(int64_t n, const int64_t *offsets, const int32_t
   if (n < 0 || !q_out || (n > 0 && (!offsets || !membership))) return LEIDEN_EINVAL;
   Workspace w;
   Ctx x{&w, (hipStream_t)stream};
-  const leiden_status st = run_guarded(w, [&] {
+  return run_stateless(w, x.s, [&] {
     if (n == 0) { *q_out = 0.0; return; }
     const int64_t nnz = x.read(offsets + n);
     if (nnz > 0 && (!indices || !weights)) x.invalid("null edge arrays");
@@ -1623,8 +1647,6 @@ leiden_status leiden_modularity(int64_t n, const int64_t *offsets, const int32_t
     Level g{n, nnz, offsets, indices, weights, crow};
     *q_out = modularity_dev(x, g, membership);
   });
-  w.release(x.s);
-  return st;
 }
 
 leiden_status leiden_aggregate(int64_t n, const int64_t *offsets, const int32_t *indices, const float *weights,
@@ -1633,7 +1655,7 @@ leiden_status leiden_aggregate(int64_t n, const int64_t *offsets, const int32_t 
   if (n < 0 || ncomm < 0 || !nnz_out || !out_offsets || (n > 0 && (!offsets || !membership))) return LEIDEN_EINVAL;
   Workspace w;
   Ctx x{&w, (hipStream_t)stream};
-  const leiden_status st = run_guarded(w, [&] {
+  return run_stateless(w, x.s, [&] {
     const int64_t nnz = (n > 0) ? x.read(offsets + n) : 0;
     DevScal *sc = x.scal();
     x.zero(&sc->err, 1);
@@ -1643,18 +1665,10 @@ leiden_status leiden_aggregate(int64_t n, const int64_t *offsets, const int32_t 
     int32_t *crow = x.get<int32_t>(Q_crow, ceil_div(std::max<int64_t>(nnz, 1), kChunk) + 2);
     chunk_start_rows(offsets, n, nnz, crow, x.s);
     Level g{n, nnz, offsets, indices, weights, crow};
-    const Level o = aggregate_level(x, g, membership, ncomm, 0, nullptr);
-    x.copy(out_offsets, o.off, ncomm + 1);
-    if (o.nnz > 0) {
-      if (!out_indices || !out_weights) x.invalid("null output arrays");
-      x.copy(out_indices, o.idx, o.nnz);
-      x.copy(out_weights, o.w, o.nnz);
-    }
-    *nnz_out = o.nnz;
+    const AggOut out{out_offsets, out_indices, out_weights};
+    *nnz_out = aggregate_level(x, g, membership, ncomm, 0, nullptr, nullptr, 0, &out).nnz;
     x.check(hipStreamSynchronize(x.s), "sync");
   });
-  w.release(x.s);
-  return st;
 }
 
 leiden_status leiden_get_graph(leiden_handle *h, int64_t *offsets, int32_t *indices, float *weights,

@@ -1,8 +1,11 @@
 """GPU: the launch shapes and table sizes of the kernels at the edges of their
 ranges, through the C ABI, against the CPU oracle (integer weights, so every
 comparison that is not said to be otherwise is exact)."""
+import threading
+
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2405_11658_amd import inputs as gen
@@ -94,3 +97,39 @@ def test_aggregate_segment_sizes(sizes, labels):
     assert np.array_equal(i, pair % k)
     assert np.all(np.abs(x - total) <= 2.0 ** -24 * total * (1 + 1e-6))
     assert np.array_equal(x, to_np(L.leiden_aggregate(off, idx, w, C, k)[2]))
+
+
+def test_stateless_calls_share_kept_memory():
+    """Working memory kept between stateless calls: growing and shrinking
+    sizes, several threads and streams, and what is kept stays under its
+    bound."""
+    graphs = []
+    for k in (40, 3000, 200000, 900):
+        n = 4 * k
+        rng = np.random.default_rng(k)
+        lab = rng.integers(0, k, n).astype(np.int32)
+        g = gen.from_edges(n, rng.integers(0, n, 4 * n), rng.integers(0, n, 4 * n))
+        t = [torch.from_numpy(np.asarray(x)).cuda() for x in (g.off, g.idx, g.w, lab)]
+        want = [x.clone() for x in L.leiden_aggregate(*t, k)]
+        graphs.append((t, k, want, L.leiden_modularity(*t)))
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(first):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for r in range(8):
+                t, k, want, q = graphs[(first + r) % len(graphs)]
+                got = L.leiden_aggregate(*t, k)
+                s.synchronize()
+                bad.extend(not torch.equal(x, y) for x, y in zip(got, want))
+                bad.append(abs(L.leiden_modularity(*t) - q) > 1e-12)
+
+    free = torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert len(bad) == 4 * 8 * 4 and not any(bad)
+    assert free - (torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()) < 2 << 30
