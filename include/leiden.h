@@ -331,7 +331,8 @@ leiden_status leiden_server_destroy(leiden_server *server);
  * job's result is determined by its graph and batch alone - equal to the
  * serial reading of the paper's algorithms, and independent of the launch
  * variant (leiden_fleet_set_variant: wavefronts per workgroup and LDS table
- * slots, a speed choice only; leiden_fleet_variant_info describes it).
+ * slots, a speed choice only; leiden_fleet_variant_info describes it; without
+ * one the library chooses by the number of jobs of a run).
  * params: as for leiden_create (sync_mode, nslices, async_waves, hub_slices
  * and profile are not used; max_passes <= 16).  alloc as for leiden_create.
  *

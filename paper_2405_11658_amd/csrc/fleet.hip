@@ -121,7 +121,7 @@ struct Fail {
 struct leiden_fleet {
   int32_t count = 0;
   leiden_params prm;
-  int variant = 0;
+  int variant = -1;                 // set by the caller; -1: by the size of a run
   Alloc al;
   std::string err;
   std::vector<FleetGraph> host;     // mirror of the device graph table
@@ -134,8 +134,7 @@ struct leiden_fleet {
   void *pin = nullptr;              // pinned staging (jobs up, results down)
   size_t pin_cap = 0;
   hipStream_t cap_stream = nullptr; // stream used to capture the launch
-  hipGraphExec_t exec = nullptr;
-  int exec_variant = -1;
+  hipGraphExec_t exec[kFleetLaunches] = {};  // captured launch per variant
   hipEvent_t t0 = nullptr, t1 = nullptr;
   hipStream_t last = nullptr;
   bool used = false;           // a call has enqueued work (recorded in `order`)
@@ -180,13 +179,15 @@ struct leiden_fleet {
     p.refine_variant = prm.refine_variant;
     return p;
   }
-  // (Re)builds the captured launch for the current variant and job capacity.
-  void capture() {
-    if (exec && exec_variant == variant) return;
-    if (exec) {
-      (void)hipGraphExecDestroy(exec);
-      exec = nullptr;
-    }
+  // Captured launch for a run of `jobs` jobs.  Without a caller's choice:
+  // workgroups of 8 wavefronts while that many fit the device about twice
+  // (24 graphs of 500 to 4000 vertices 6.3 ms, with 4 wavefronts 7.2; 512 of
+  // 1000 to 30000 85 and 99 ms), of 4 for more jobs, where the serial sweeps
+  // of four workgroups a compute unit count for more (1200 of 2000 to 4000:
+  // 20.3 and 19.6 ms; 4096 of 300 to 1500: 14.8 and 11.8 ms).
+  hipGraphExec_t capture(int64_t jobs_run) {
+    const int v = variant >= 0 ? variant : jobs_run <= 1024 ? kFleetWide : kFleetMany;
+    if (exec[v]) return exec[v];
     if (!cap_stream) check(hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking), "hipStreamCreate");
     FleetLaunch L;
     L.graphs = (FleetGraph *)table.p;
@@ -197,14 +198,21 @@ struct leiden_fleet {
     L.prm = params();
     hipGraph_t graph;
     check(hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    const hipError_t le = fleet_launch(L, variant, kFleetBlocks, cap_stream);
+    const hipError_t le = fleet_launch(L, v, kFleetBlocks, cap_stream);
     const hipError_t ce = hipStreamEndCapture(cap_stream, &graph);
     check(le, "fleet launch capture");
     check(ce, "hipStreamEndCapture");
-    const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    const hipError_t ie = hipGraphInstantiate(&exec[v], graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
+    if (ie != hipSuccess) exec[v] = nullptr;
     check(ie, "hipGraphInstantiate");
-    exec_variant = variant;
+    return exec[v];
+  }
+  void drop_captured() {
+    for (auto &e : exec) {
+      if (e) (void)hipGraphExecDestroy(e);
+      e = nullptr;
+    }
   }
   void release(hipStream_t s) {
     for (auto &b : arena) {
@@ -415,7 +423,7 @@ leiden_status leiden_fleet_destroy(leiden_fleet *f) {
   hipStream_t s = nullptr;
   if (f->used && f->order) (void)hipStreamWaitEvent(s, f->order, 0);
   f->release(s);
-  if (f->exec) (void)hipGraphExecDestroy(f->exec);
+  f->drop_captured();
   if (f->cap_stream) (void)hipStreamDestroy(f->cap_stream);
   if (f->t0) (void)hipEventDestroy(f->t0);
   if (f->t1) (void)hipEventDestroy(f->t1);
@@ -487,10 +495,7 @@ leiden_status leiden_fleet_run(leiden_fleet *f, int32_t count, const int32_t *gr
       f->ensure(f->jobs, 256 + sizeof(FleetJob) * cap, s);
       f->ensure(f->results, sizeof(FleetResult) * cap, s);
       f->jobs_cap = cap;
-      if (f->exec) {
-        (void)hipGraphExecDestroy(f->exec);
-        f->exec = nullptr;
-      }
+      f->drop_captured();
     }
     const size_t jbytes = 256 + sizeof(FleetJob) * count;
     const size_t rbytes = sizeof(FleetResult) * count + sizeof(FleetGraph) * f->count;
@@ -525,13 +530,13 @@ leiden_status leiden_fleet_run(leiden_fleet *f, int32_t count, const int32_t *gr
       j.out = membership_out ? membership_out[k] : nullptr;
     }
     f->check(hipMemcpyAsync(f->jobs.p, hp, jbytes, hipMemcpyHostToDevice, s), "H2D jobs");
-    f->capture();
+    hipGraphExec_t exec = f->capture(count);
     if (!f->t0) {
       f->check(hipEventCreate(&f->t0), "hipEventCreate");
       f->check(hipEventCreate(&f->t1), "hipEventCreate");
     }
     f->check(hipEventRecord(f->t0, s), "hipEventRecord");
-    f->check(hipGraphLaunch(f->exec, s), "hipGraphLaunch");
+    f->check(hipGraphLaunch(exec, s), "hipGraphLaunch");
     f->check(hipEventRecord(f->t1, s), "hipEventRecord");
     f->check(hipMemcpyAsync(hp, f->results.p, sizeof(FleetResult) * count, hipMemcpyDeviceToHost, s), "D2H");
     char *tp = hp + sizeof(FleetResult) * count;

@@ -13,8 +13,8 @@
 // Local moving and refinement follow the serial asynchronous reading of
 // Alg. "leidenMove" and "leidenRefine": the vertices of a level are visited
 // one at a time in ascending id order, each reading the state the previous
-// ones left; the workgroup's threads share the work of one vertex (its edges
-// and its table of neighbouring communities).  The result of a job therefore
+// ones left; one wavefront holds a vertex's edges, or the workgroup's threads
+// share a wide vertex's edges and its table of neighbouring communities.  The result of a job therefore
 // does not depend on timing, on the number of wavefronts per workgroup or on
 // the table size (the tuning parameters), only on the graph and the batch.
 #pragma once
@@ -99,8 +99,9 @@ struct FleetLaunch {
 };
 
 // Kernel variants: workgroup of 64 * waves threads, LDS table of `slots`
-// entries (vertices and communities of degree up to slots / 2 use it, higher
-// ones the graph's dense global table).
+// entries (vertices with up to slots / 2 neighbouring communities use it, by
+// their degree or the level's vertices, others the graph's dense global
+// table).
 constexpr int kFleetVariants = 6;
 struct FleetVariant {
   int waves;
@@ -108,6 +109,11 @@ struct FleetVariant {
 };
 constexpr FleetVariant kFleetVariant[kFleetVariants] = {{1, 512}, {2, 512}, {4, 512},
                                                         {1, 2048}, {2, 2048}, {4, 2048}};
+// The variants of a fleet that none was chosen for (workgroups of 8 wavefronts
+// with 2048 slots, beside the caller's variants, and one of those).
+constexpr int kFleetWide = kFleetVariants;
+constexpr int kFleetMany = 2;
+constexpr int kFleetLaunches = kFleetVariants + 1;
 // Enqueue the persistent launch with `blocks` workgroups of variant v.
 hipError_t fleet_launch(const FleetLaunch &L, int variant, int blocks, hipStream_t s);
 

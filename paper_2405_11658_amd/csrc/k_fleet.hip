@@ -36,7 +36,6 @@ struct FSh {
   int wide;             // the sweep's next vertex for the whole workgroup
   // radix sort
   int hist[256];
-  int base[256];
   int wcnt[W][256];
   // neighbour-community table
   int tkeys[SLOTS];
@@ -57,7 +56,7 @@ struct Blk {
   static __device__ int wid() { return (int)threadIdx.x / kWave; }
 
   static __device__ double sum_d(double v, Sh &s) {
-    v = group_sum<kWave>(v);
+    v = wave_sum(v);
     __syncthreads();
     if (lane() == 0) s.rd[wid()] = v;
     __syncthreads();
@@ -88,7 +87,7 @@ struct Blk {
   }
   // best (larger gain, then smaller id) over the block; valid in all threads
   static __device__ void argmax(double &g, int &c, Sh &s) {
-    group_argmax<kWave>(g, c);
+    wave_argmax(g, c);
     __syncthreads();
     if (lane() == 0) {
       s.rd[wid()] = g;
@@ -101,76 +100,143 @@ struct Blk {
       if (better(s.rd[k], s.ri[k], g, c)) { g = s.rd[k]; c = s.ri[k]; }
     __syncthreads();
   }
-  // exclusive prefix of x over the block (tile order); total in *tot
-  static __device__ long long excl(long long x, long long *tot, Sh &s) {
-    long long incl = x;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const long long y = __shfl_up(incl, off);
-      if (lane() >= off) incl += y;
-    }
+  // The items [lo, hi) of this wavefront when n items are split into W ranges
+  // of whole tiles of 64.  Passes over a graph's entries give each wavefront
+  // such a range, so that no barrier stands between its tiles: with one
+  // barrier a tile the passes ran at the latency of a load per T items.
+  static __device__ int64_t range_lo(int64_t n) {
+    const int64_t per = ((n + kWave - 1) / kWave + W - 1) / W * kWave;
+    return min(n, per * wid());
+  }
+  static __device__ int64_t range_hi(int64_t n) {
+    const int64_t per = ((n + kWave - 1) / kWave + W - 1) / W * kWave;
+    return min(n, per * (wid() + 1));
+  }
+  // Sum of x (uniform in each wavefront) over the wavefronts before this one;
+  // the total in *tot.
+  static __device__ long long before(long long x, long long *tot, Sh &s) {
     __syncthreads();
-    if (lane() == kWave - 1) s.rl[wid()] = incl;
+    if (lane() == 0) s.rl[wid()] = x;
     __syncthreads();
     long long pre = 0, all = 0;
     for (int k = 0; k < W; ++k) {
       if (k < wid()) pre += s.rl[k];
       all += s.rl[k];
     }
-    __syncthreads();
     *tot = all;
-    return pre + incl - x;
+    return pre;
   }
-  // out[k] = sum of in[0..k) for k in [0, n]; returns the total.  in and out
-  // may be the same array.
+  // out[k] = sum of in[0..k) for k in [0, n] (counts: below 2^31 in total);
+  // returns the total.  in and out may be the same array.
   template <class I, class O>
   static __device__ long long scan(const I *in, O *out, int64_t n, Sh &s) {
-    long long carry = 0;
-    for (int64_t b = 0; b < n + 1; b += T) {
-      const int64_t k = b + tid();
-      const long long x = (k < n) ? (long long)ldx(&in[k]) : 0;
-      long long tot;
-      const long long ex = excl(x, &tot, s);
-      if (k <= n) out[k] = (O)(carry + ex);
-      carry += tot;
-      __syncthreads();
+    const int64_t lo = range_lo(n), hi = range_hi(n);
+    long long mine = 0;
+    for (int64_t k = lo + lane(); k < hi; k += kWave) mine += (long long)ldx(&in[k]);
+    long long tot;
+    long long carry = before(group_sum_ll<kWave>(mine), &tot, s);
+    for (int64_t b = lo; b < hi; b += kWave) {
+      const int64_t k = b + lane();
+      const int x = k < hi ? (int)ldx(&in[k]) : 0;
+      int all;
+      const int incl = wave_scan(x, &all);
+      if (k < hi) out[k] = (O)(carry + (incl - x));
+      carry += all;
     }
-    return carry;
+    if (tid() == 0) out[n] = (O)tot;
+    __syncthreads();
+    return tot;
+  }
+
+  // f(width, u, e0, e1, first, there) for every row u of a CSR, called by
+  // `width` lanes that share the row's entries [e0, e1) (the calling lane's
+  // first is `first`): 8 lanes for rows of up to 64 entries, a wavefront for
+  // longer ones.  there: the lanes hold a row.  A wavefront a row, most rows
+  // being of a few dozen entries, waited out three loads a row: copying 30000
+  // rows 37 -> 5.7 ms, their modularity 40 -> 2.6 ms (8 rows at a time, and 8
+  // wavefronts).
+  template <class F>
+  static __device__ void rows(int64_t n, const int64_t *off, F f) {
+    constexpr int kSub = 8;
+    for (int64_t b = (int64_t)wid() * (kWave / kSub); b < n; b += (int64_t)W * (kWave / kSub)) {
+      const int64_t u = b + lane() / kSub;
+      int64_t e0 = 0, e1 = 0;
+      if (u < n) {
+        e0 = off[u];
+        e1 = off[u + 1];
+      }
+      const bool wide = e1 - e0 > kWave;
+      unsigned long long m = __ballot(wide && lane() % kSub == 0);
+      f(Const<kSub>{}, u, e0, e1, e0 + lane() % kSub, u < n && !wide);
+      for (; m; m &= m - 1) {
+        const int l = __ffsll(m) - 1;
+        const int64_t r0 = lane_value64(e0, l), r1 = lane_value64(e1, l);
+        f(Const<kWave>{}, b + l / kSub, r0, r1, r0 + lane(), true);
+      }
+    }
   }
 
   // Stable LSD radix sort of (key, payload) pairs by the low `bits` key bits;
-  // returns the buffer (0 / 1) holding the result.
+  // returns the buffer (0 / 1) holding the result.  Each wavefront counts and
+  // then places the pairs of its own range, in order, with its own counters.
   static __device__ int sort(unsigned long long *key[2], int32_t *pay[2], int64_t n, int bits, Sh &s) {
+    const int64_t lo = range_lo(n), hi = range_hi(n);
+    int *cnt = s.wcnt[wid()];
     int src = 0;
     for (int shift = 0; shift < bits; shift += 8) {
       const unsigned long long *ki = key[src];
       const int32_t *pi = pay[src];
       unsigned long long *ko = key[src ^ 1];
       int32_t *po = pay[src ^ 1];
-      for (int d = tid(); d < 256; d += T) s.hist[d] = 0;
+      for (int d = lane(); d < 256; d += kWave) cnt[d] = 0;
+      lds_fence();
+      for (int64_t k = lo + lane(); k < hi; k += kWave) atomicAdd(&cnt[(int)((ki[k] >> shift) & 255ull)], 1);
       __syncthreads();
-      for (int64_t k = tid(); k < n; k += T) atomicAdd(&s.hist[(int)((ki[k] >> shift) & 255ull)], 1);
+      // counts -> pairs of the digit in the wavefronts before; digit totals
+      for (int d = tid(); d < 256; d += T) {
+        int t = 0;
+        for (int k = 0; k < W; ++k) {
+          const int c = s.wcnt[k][d];
+          s.wcnt[k][d] = t;
+          t += c;
+        }
+        s.hist[d] = t;
+      }
       __syncthreads();
-      if (tid() == 0) {
-        int acc = 0;
-        for (int d = 0; d < 256; ++d) {
-          s.base[d] = acc;
-          acc += s.hist[d];
+      if (wid() == 0) {
+        int c[4], all, sum = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          c[q] = s.hist[4 * lane() + q];
+          sum += c[q];
+        }
+        int pre = wave_scan(sum, &all) - sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          s.hist[4 * lane() + q] = pre;
+          pre += c[q];
         }
       }
-      for (int d = tid(); d < 256 * W; d += T) (&s.wcnt[0][0])[d] = 0;
       __syncthreads();
-      for (int64_t b = 0; b < n; b += T) {
-        const int64_t k = b + tid();
-        const bool act = k < n;
-        unsigned long long key = 0;
-        int32_t p = 0;
-        int dg = 0;
-        if (act) {
-          key = ki[k];
-          p = pi[k];
-          dg = (int)((key >> shift) & 255ull);
+      for (int d = lane(); d < 256; d += kWave) cnt[d] += s.hist[d];
+      lds_fence();
+      // tiles of this range, the next one's pairs loaded ahead
+      unsigned long long nkey = 0;
+      int32_t npay = 0;
+      if (lo + lane() < hi) {
+        nkey = ki[lo + lane()];
+        npay = pi[lo + lane()];
+      }
+      for (int64_t b = lo; b < hi; b += kWave) {
+        const bool act = b + lane() < hi;
+        const unsigned long long kk = nkey;
+        const int32_t p = npay;
+        const int64_t nx = b + kWave + lane();
+        if (nx < hi) {
+          nkey = ki[nx];
+          npay = pi[nx];
         }
+        const int dg = (int)((kk >> shift) & 255ull);
         // lanes of this wavefront with the same digit
         unsigned long long same = __ballot(act);
 #pragma unroll
@@ -179,27 +245,17 @@ struct Blk {
           same &= ((dg >> bit) & 1) ? on : ~on;
         }
         const unsigned long long below = (lane() == 0) ? 0ull : (~0ull >> (64 - lane()));
-        const int rank_w = __popcll(same & below);
-        if (act && rank_w == 0) s.wcnt[wid()][dg] = __popcll(same);
-        __syncthreads();
+        const int rank = __popcll(same & below);
         if (act) {
-          int before = 0;
-          for (int w = 0; w < wid(); ++w) before += s.wcnt[w][dg];
-          const int64_t pos = s.base[dg] + before + rank_w;
-          ko[pos] = key;
-          po[pos] = p;
+          const int at = cnt[dg];
+          ko[at + rank] = kk;
+          po[at + rank] = p;
+          lds_fence();
+          if (rank == 0) cnt[dg] = at + __popcll(same);
         }
-        __syncthreads();
-        for (int d = tid(); d < 256; d += T) {
-          int t = 0;
-          for (int w = 0; w < W; ++w) {
-            t += s.wcnt[w][d];
-            s.wcnt[w][d] = 0;
-          }
-          s.base[d] += t;
-        }
-        __syncthreads();
+        lds_fence();
       }
+      __syncthreads();
       src ^= 1;
     }
     return src;
@@ -710,49 +766,67 @@ struct FleetRun {
   // ---------------- Alg. "leidenAggregate" ---------------------------------
   // Super-vertex CSR of L under dense labels Cl (< nc) into level buffer ob,
   // K' (row sums of the stored float weights, in row order) into Kl.
-  // Entries are sorted by (C[u], C[v]) with a stable sort, so the sums of a
-  // pair take its entries in member-then-CSR order.
+  // Entries are sorted by (C[u], C[v]) with a stable sort: a pair's entries
+  // in member-then-CSR order, summed in FP64 by each wavefront that holds some.
+  // Three passes of the sort, one to count the pairs, one to write them: 420k
+  // entries 160 -> 13 ms in 8 wavefronts, all levels of an update, at
+  // the latency of a few loads a wavefront.
   __device__ FLevel aggregate(const FLevel &L, int64_t nc, int ob) {
     unsigned long long *key[2] = {g.akey[0], g.akey[1]};
     int32_t *pay[2] = {g.apay[0], g.apay[1]};
-    for (int64_t u = B::wid(); u < L.n; u += B::W) {
-      const unsigned long long cu = (unsigned long long)g.Cl[u];
-      for (int64_t e = L.off[u] + lane(); e < L.off[u + 1]; e += kWave) {
-        key[0][e] = cu * (unsigned long long)nc + (unsigned long long)g.Cl[L.idx[e]];
+    const int32_t *Cl = g.Cl;
+    const int kb = bits_for((unsigned long long)max(nc - 1, (int64_t)1));
+    B::rows(L.n, L.off, [&](auto width, int64_t u, int64_t, int64_t e1, int64_t first, bool there) {
+      if (!there) return;
+      const unsigned long long cu = (unsigned long long)Cl[u] << kb;
+      for (int64_t e = first; e < e1; e += decltype(width)::value) {
+        key[0][e] = cu | (unsigned long long)Cl[L.idx[e]];
         pay[0][e] = (int32_t)e;
       }
-    }
+    });
     __syncthreads();
-    const unsigned long long top = (unsigned long long)nc * (unsigned long long)nc - 1ull;
-    const int r = B::sort(key, pay, L.nnz, nc > 1 ? bits_for(top) : 0, s);
+    const int r = B::sort(key, pay, L.nnz, nc > 1 ? 2 * kb : 0, s);
     const unsigned long long *sk = key[r];
     const int32_t *sp = pay[r];
-    // distinct keys: head flags, then output positions by a scan
-    int64_t *pos = (int64_t *)key[r ^ 1];
-    for (int64_t t = B::tid(); t < L.nnz; t += T) pos[t] = (t == 0 || sk[t] != sk[t - 1]) ? 1 : 0;
-    __syncthreads();
-    const int64_t nu = B::scan(pos, pos, L.nnz, s);
+    // distinct keys of this wavefront's range, and of those before it
+    const int64_t lo = B::range_lo(L.nnz), hi = B::range_hi(L.nnz);
+    auto head = [&](int64_t t) { return t < hi && (t == 0 || sk[t] != sk[t - 1]); };
+    long long heads = 0, nu;
+    for (int64_t b = lo; b < hi; b += kWave) heads += __popcll(__ballot(head(b + lane())));
+    int64_t at = B::before(heads, &nu, s);
     int64_t *off = g.loff[ob];
     int32_t *idx = g.lidx[ob];
     float *w = g.lw[ob];
-    int64_t *rc = g.mcnt;
     double *sum = g.asum;
-    for (int64_t c = B::tid(); c <= nc; c += T) rc[c] = 0;
     for (int64_t o = B::tid(); o < nu; o += T) sum[o] = 0.0;
     __syncthreads();
-    for (int64_t t = B::tid(); t < L.nnz; t += T) {
-      const bool head = t == 0 || sk[t] != sk[t - 1];
-      const int64_t o = ldx(&pos[t]) - (head ? 0 : 1);
-      unsafeAtomicAdd(&sum[o], (double)L.w[sp[t]]);
-      if (head) {
-        idx[o] = (int32_t)(sk[t] % (unsigned long long)nc);
-        atomicAdd((unsigned long long *)&rc[sk[t] / (unsigned long long)nc], 1ull);
+    // entries of the new rows: the wavefront's entries of a key summed in
+    // order, then added to its other wavefronts'
+    for (int64_t b = lo; b < hi; b += kWave) {
+      const int64_t t = b + lane();
+      const bool in = t < hi;
+      const unsigned long long kk = in ? sk[t] : 0ull;
+      double x = in ? (double)L.w[sp[t]] : 0.0;
+      const bool first = head(t);
+      const unsigned long long hm = __ballot(first);
+      const int64_t o = at + __popcll(hm & (~0ull >> (63 - lane()))) - 1;
+      if (first) {
+        idx[o] = (int32_t)(kk & ((1ull << kb) - 1ull));
+        const int64_t row = (int64_t)(kk >> kb);
+        for (int64_t c = t == 0 ? 0 : (int64_t)(sk[t - 1] >> kb) + 1; c <= row; ++c) off[c] = o;
       }
+      int f = first || lane() == 0;
+      wave_seg_scan(x, f);
+      const bool last = in && (lane() == kWave - 1 || t + 1 >= hi || ((hm >> (lane() + 1)) & 1ull));
+      if (last) unsafeAtomicAdd(&sum[o], x);
+      at += __popcll(hm);
     }
+    // rows after the last one with an entry
+    const int64_t past = L.nnz > 0 ? (int64_t)(sk[L.nnz - 1] >> kb) + 1 : 0;
+    for (int64_t c = past + B::tid(); c <= nc; c += T) off[c] = nu;
     __syncthreads();
     for (int64_t o = B::tid(); o < nu; o += T) w[o] = (float)ldx(&sum[o]);
     __syncthreads();
-    B::scan(rc, off, nc, s);
     for (int64_t c = B::tid(); c < nc; c += T) {
       double k = 0.0;
       for (int64_t e = off[c]; e < off[c + 1]; ++e) k += (double)w[e];
@@ -906,30 +980,30 @@ struct FleetRun {
     __syncthreads();
     const int64_t nnz_new = B::scan(g.mcnt, noff, n, s);
     // surviving old entries
-    for (int64_t u = B::wid(); u < n; u += B::W) {
-      const int64_t o0 = off[u], o1 = off[u + 1];
+    B::rows(n, off, [&](auto width, int64_t u, int64_t o0, int64_t o1, int64_t first, bool there) {
+      if (!there) return;
+      const int64_t to = noff[u];
       const int s0 = seg0[u];
       if (s0 < 0) {
-        for (int64_t e = o0 + lane(); e < o1; e += kWave) {
-          nidx[noff[u] + (e - o0)] = idx[e];
-          nw[noff[u] + (e - o0)] = w[e];
+        for (int64_t e = first; e < o1; e += decltype(width)::value) {
+          nidx[to + (e - o0)] = idx[e];
+          nw[to + (e - o0)] = w[e];
         }
-        continue;
+        return;
       }
-      int64_t s1 = s0;
       const unsigned long long lo = (unsigned long long)u * (unsigned long long)n;
-      s1 = lower_bound_u64(sk, s0, E, lo + (unsigned long long)n);
-      for (int64_t e = o0 + lane(); e < o1; e += kWave) {
+      const int64_t s1 = lower_bound_u64(sk, s0, E, lo + (unsigned long long)n);
+      for (int64_t e = first; e < o1; e += decltype(width)::value) {
         const int v = idx[e];
         const int64_t p = lower_bound_u64(sk, s0, s1, lo + (unsigned long long)v);
         const int64_t dels = pre[p] - pre[s0];
         const int64_t inss = (p - s0) - dels;
         if (p < s1 && sk[p] == lo + (unsigned long long)v) continue;  // deleted (an insertion cannot match)
-        const int64_t o = noff[u] + (e - o0) - dels + inss;
+        const int64_t o = to + (e - o0) - dels + inss;
         nidx[o] = v;
         nw[o] = w[e];
       }
-    }
+    });
     // inserted entries
     for (int64_t t = B::tid(); t < E; t += T) {
       if (sp[t] < 2 * nd) continue;
@@ -1017,10 +1091,10 @@ struct FleetRun {
         }
       }
       __syncthreads();
-      for (int64_t u = B::wid(); u < n; u += B::W) {
-        if (!g.dE[u]) continue;
-        for (int64_t e = off[u] + lane(); e < off[u + 1]; e += kWave) g.U[idx[e]] = 1;
-      }
+      B::rows(n, off, [&](auto width, int64_t u, int64_t, int64_t e1, int64_t first, bool there) {
+        if (!there || !g.dE[u]) return;
+        for (int64_t e = first; e < e1; e += decltype(width)::value) g.U[idx[e]] = 1;
+      });
       __syncthreads();
       for (int64_t i = B::tid(); i < n; i += T)
         if (g.dCm[g.C[i]]) g.U[i] = 1;
@@ -1058,14 +1132,23 @@ struct FleetRun {
     for (int64_t c = B::tid(); c < n; c += T) g.Sig[c] = 0.0;
     __syncthreads();
     for (int64_t i = B::tid(); i < n; i += T) unsafeAtomicAdd(&g.Sig[g.C[i]], ldx(&g.K[i]));
-    for (int64_t u = B::wid(); u < n; u += B::W) {
-      const int cu = g.C[u];
+    const int32_t *C = g.C;
+    B::rows(n, off, [&](auto width, int64_t u, int64_t, int64_t e1, int64_t first, bool there) {
+      constexpr int N = decltype(width)::value;
+      const int cu = there ? C[u] : 0;
       double in = 0.0;
-      for (int64_t e = off[u] + lane(); e < off[u + 1]; e += kWave)
-        if (g.C[idx[e]] == cu) in += (double)w[e];
-      in = group_sum<kWave>(in);
-      if (lane() == 0 && in != 0.0) unsafeAtomicAdd(&sig[cu], in);
-    }
+      if (there)
+        for (int64_t e = first; e < e1; e += N)
+          if (C[idx[e]] == cu) in += (double)w[e];
+      if constexpr (N == kWave) {
+        in = wave_sum(in);
+      } else {
+        in += dpp_move<kDppXor1>(in);
+        in += dpp_move<kDppXor2>(in);
+        in += dpp_move<kDppHalfMirror>(in);
+      }
+      if (there && lane() % N == 0 && in != 0.0) unsafeAtomicAdd(&sig[cu], in);
+    });
     __syncthreads();
     const double M2 = g.M2;
     double q = 0.0;
@@ -1154,8 +1237,9 @@ struct FleetRun {
   }
 };
 
+// Four wavefronts a SIMD, so that two workgroups of 8 share a compute unit.
 template <int T, int SLOTS>
-__global__ __launch_bounds__(T) void k_fleet(FleetLaunch a) {
+__global__ __launch_bounds__(T, 4) void k_fleet(FleetLaunch a) {
   __shared__ FSh<T, SLOTS> s;
   for (int k = threadIdx.x; k < SLOTS; k += T) {
     s.tkeys[k] = kEmpty;
@@ -1195,6 +1279,7 @@ __global__ __launch_bounds__(T) void k_fleet(FleetLaunch a) {
 
 hipError_t fleet_launch(const FleetLaunch &L, int variant, int blocks, hipStream_t s) {
   switch (variant) {
+    case kFleetWide: hipLaunchKernelGGL((k_fleet<512, 2048>), blocks, 512, 0, s, L); break;
     case 0: hipLaunchKernelGGL((k_fleet<64, 512>), blocks, 64, 0, s, L); break;
     case 1: hipLaunchKernelGGL((k_fleet<128, 512>), blocks, 128, 0, s, L); break;
     case 2: hipLaunchKernelGGL((k_fleet<256, 512>), blocks, 256, 0, s, L); break;

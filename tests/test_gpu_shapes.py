@@ -11,7 +11,7 @@ import oracle
 from paper_2405_11658_amd import inputs as gen
 from paper_2405_11658_amd import leiden as L
 
-from .gpu_common import dev_batch, og, say, to_np
+from .gpu_common import dev_batch, ob, og, say, to_np
 from .test_gpu_async import _check_state, _graph_of
 
 pytestmark = pytest.mark.gpu
@@ -133,3 +133,45 @@ def test_stateless_calls_share_kept_memory():
         t.join()
     assert len(bad) == 4 * 8 * 4 and not any(bad)
     assert free - (torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()) < 2 << 30
+
+
+@pytest.mark.parametrize("variant", [None, 0, 2])
+def test_fleet_row_and_degree_classes(variant):
+    """The fused engine's visits from registers (up to 64 and 256 edges) and by
+    the workgroup, rows of 8 lanes and of a wavefront, levels and batches of
+    few and of more than a tile, against the serial oracle."""
+    gs = [_stars((63, 64, 65, 255, 256, 257), seed=3), _stars((300, 1030, 2100), seed=4),
+          gen.from_edges(65, np.arange(64), np.arange(1, 65)), gen.from_edges(3, [0], [2])]
+    fl = L.Fleet([(g.off, g.idx, g.w) for g in gs])
+    if variant is not None:
+        fl.set_variant(variant)
+    res, _ = fl.run([(k, "static", None) for k in range(len(gs))])
+    states = []
+    for k, g in enumerate(gs):
+        ref, st = oracle.static(og(g))
+        assert np.array_equal(to_np(res[k][0]), ref.C) and res[k][3]["move_iters"] == st["move_iters"], k
+        states.append(ref)
+    jobs, bs = [], {}
+    for k, mode in ((0, "df"), (1, "ds"), (2, "nd")):
+        bs[k] = gen.random_batch(gs[k], 6, seed=k)
+        jobs.append((k, mode, dev_batch(bs[k])))
+    res, _ = fl.run(jobs)
+    for q, (k, mode, _) in enumerate(jobs):
+        new = oracle.update(states[k], ob(bs[k]), mode)[0]
+        assert np.array_equal(to_np(res[q][0]), new.C), (k, mode)
+        off, idx, w = fl.get_graph(k)
+        assert np.array_equal(to_np(off), new.g.off) and np.array_equal(to_np(idx), new.g.idx)
+        assert np.array_equal(to_np(w), new.g.w)
+    fl.close()
+
+
+def test_fleet_of_more_jobs_than_wide_workgroups():
+    """1030 jobs in one run, and fewer in the next: either launch of the fused
+    engine gives the serial oracle's result."""
+    kinds = [gen.clique_ring(6, 5), gen.gnp(60, 0.1, seed=2, weights="unit"), gen.from_edges(2, [0], [1])]
+    refs = [oracle.static(og(g))[0].C for g in kinds]
+    fl = L.Fleet([(g.off, g.idx, g.w) for g in (kinds[k % 3] for k in range(1030))])
+    for count in (1030, 1024, 5, 1025):
+        res, _ = fl.run([(k, "static", None) for k in range(count)])
+        assert all(np.array_equal(to_np(r[0]), refs[k % 3]) for k, r in enumerate(res)), count
+    fl.close()
