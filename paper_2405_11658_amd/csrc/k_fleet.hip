@@ -21,7 +21,7 @@ constexpr unsigned long long kNoKey = ~0ull;
 // Edges of a vertex that one wavefront visits from registers, and vertices
 // whose edges it holds at a time.
 constexpr int kWaveEdges = 256;
-constexpr int kGroup = 4;
+constexpr int kGroup = 2;
 
 // LDS of one workgroup.
 template <int T, int SLOTS>
@@ -52,10 +52,10 @@ struct Blk {
   using Sh = FSh<T, SLOTS>;
   static constexpr int W = T / kWave;
 
-  static __device__ int tid() { return (int)threadIdx.x; }
-  static __device__ int wid() { return (int)threadIdx.x / kWave; }
+  static __device__ __forceinline__ int tid() { return (int)threadIdx.x; }
+  static __device__ __forceinline__ int wid() { return (int)threadIdx.x / kWave; }
 
-  static __device__ double sum_d(double v, Sh &s) {
+  static __device__ __forceinline__ double sum_d(double v, Sh &s) {
     v = wave_sum(v);
     __syncthreads();
     if (lane() == 0) s.rd[wid()] = v;
@@ -65,7 +65,7 @@ struct Blk {
     __syncthreads();
     return t;
   }
-  static __device__ long long sum_l(long long v, Sh &s) {
+  static __device__ __forceinline__ long long sum_l(long long v, Sh &s) {
     v = group_sum_ll<kWave>(v);
     __syncthreads();
     if (lane() == 0) s.rl[wid()] = v;
@@ -75,7 +75,7 @@ struct Blk {
     __syncthreads();
     return t;
   }
-  static __device__ int or_i(int v, Sh &s) {
+  static __device__ __forceinline__ int or_i(int v, Sh &s) {
     __syncthreads();
     if (tid() == 0) s.flag = 0;
     __syncthreads();
@@ -86,7 +86,7 @@ struct Blk {
     return r;
   }
   // best (larger gain, then smaller id) over the block; valid in all threads
-  static __device__ void argmax(double &g, int &c, Sh &s) {
+  static __device__ __forceinline__ void argmax(double &g, int &c, Sh &s) {
     wave_argmax(g, c);
     __syncthreads();
     if (lane() == 0) {
@@ -104,17 +104,17 @@ struct Blk {
   // of whole tiles of 64.  Passes over a graph's entries give each wavefront
   // such a range, so that no barrier stands between its tiles: with one
   // barrier a tile the passes ran at the latency of a load per T items.
-  static __device__ int64_t range_lo(int64_t n) {
+  static __device__ __forceinline__ int64_t range_lo(int64_t n) {
     const int64_t per = ((n + kWave - 1) / kWave + W - 1) / W * kWave;
     return min(n, per * wid());
   }
-  static __device__ int64_t range_hi(int64_t n) {
+  static __device__ __forceinline__ int64_t range_hi(int64_t n) {
     const int64_t per = ((n + kWave - 1) / kWave + W - 1) / W * kWave;
     return min(n, per * (wid() + 1));
   }
   // Sum of x (uniform in each wavefront) over the wavefronts before this one;
   // the total in *tot.
-  static __device__ long long before(long long x, long long *tot, Sh &s) {
+  static __device__ __forceinline__ long long before(long long x, long long *tot, Sh &s) {
     __syncthreads();
     if (lane() == 0) s.rl[wid()] = x;
     __syncthreads();
@@ -129,7 +129,7 @@ struct Blk {
   // out[k] = sum of in[0..k) for k in [0, n] (counts: below 2^31 in total);
   // returns the total.  in and out may be the same array.
   template <class I, class O>
-  static __device__ long long scan(const I *in, O *out, int64_t n, Sh &s) {
+  static __device__ __forceinline__ long long scan(const I *in, O *out, int64_t n, Sh &s) {
     const int64_t lo = range_lo(n), hi = range_hi(n);
     long long mine = 0;
     for (int64_t k = lo + lane(); k < hi; k += kWave) mine += (long long)ldx(&in[k]);
@@ -156,7 +156,7 @@ struct Blk {
   // rows 37 -> 5.7 ms, their modularity 40 -> 2.6 ms (8 rows at a time, and 8
   // wavefronts).
   template <class F>
-  static __device__ void rows(int64_t n, const int64_t *off, F f) {
+  static __device__ __forceinline__ void rows(int64_t n, const int64_t *off, F f) {
     constexpr int kSub = 8;
     for (int64_t b = (int64_t)wid() * (kWave / kSub); b < n; b += (int64_t)W * (kWave / kSub)) {
       const int64_t u = b + lane() / kSub;
@@ -179,7 +179,7 @@ struct Blk {
   // Stable LSD radix sort of (key, payload) pairs by the low `bits` key bits;
   // returns the buffer (0 / 1) holding the result.  Each wavefront counts and
   // then places the pairs of its own range, in order, with its own counters.
-  static __device__ int sort(unsigned long long *key[2], int32_t *pay[2], int64_t n, int bits, Sh &s) {
+  static __device__ __forceinline__ int sort(unsigned long long *key[2], int32_t *pay[2], int64_t n, int bits, Sh &s) {
     const int64_t lo = range_lo(n), hi = range_hi(n);
     int *cnt = s.wcnt[wid()];
     int src = 0;
@@ -290,7 +290,7 @@ struct Tab {
   int32_t *df;   // dense taken flags
   int32_t *dl;   // dense list
 
-  __device__ void add(Sh &s, int key, double x) const {
+  __device__ __forceinline__ void add(Sh &s, int key, double x) const {
     if (dense) {
       unsafeAtomicAdd(&dv[key], x);
       if (atomicExch(&df[key], 1) == 0) dl[atomicAdd(&s.tcnt, 1)] = key;
@@ -313,7 +313,7 @@ struct Tab {
     }
   }
   // entry q < s.tcnt (after a barrier following the inserts)
-  __device__ void get(const Sh &s, int q, int &key, double &x) const {
+  __device__ __forceinline__ void get(const Sh &s, int q, int &key, double &x) const {
     if (dense) {
       key = dl[q];
       x = ldx(&dv[key]);
@@ -324,7 +324,7 @@ struct Tab {
     }
   }
   // clears what was taken; ends with the table empty and a barrier
-  __device__ void clear(Sh &s) const {
+  __device__ __forceinline__ void clear(Sh &s) const {
     const int n = s.tcnt;
     for (int q = (int)threadIdx.x; q < n; q += T) {
       if (dense) {
@@ -363,7 +363,7 @@ struct FleetRun {
   int br = 0;  // buffer of the sorted batch
 
   // of a vertex with `entries` entries in a level of n vertices
-  __device__ Tab<T, SLOTS> table(int64_t entries, int64_t n) const {
+  __device__ __forceinline__ Tab<T, SLOTS> table(int64_t entries, int64_t n) const {
     Tab<T, SLOTS> t;
     t.dense = min(entries, n) > SLOTS / 2;
     t.dv = g.dense;
@@ -386,10 +386,14 @@ struct FleetRun {
   // communities and those communities' Sigma: three rounds of loads a group
   // instead of six a vertex.  A move is written to memory and into these
   // registers, so that each visit sees what memory holds.  Refinement of the
-  // 20786 singletons of a graph of 29703 vertices: 79 -> 34 ms (3.8 ->
-  // 1.6 us a vertex); its first local moving, 12565 visits: 11.6 -> 5.1 ms.
+  // 20786 singletons of a graph of 29703 vertices: 79 -> 31 ms (3.8 -> 1.5 us
+  // a vertex: 0.8 for the loads, 0.5 for the choice); its first local moving,
+  // 12565 visits: 11.6 -> 5.3 ms.  Groups of 4 and 8 are no faster: what they
+  // save of the loads they lose on what a move writes into their registers.
+  // (Everything here is inlined: in a function of its own the tables are
+  // reached by generic addresses, 1.7 times the time.)
   template <bool REFINE>
-  __device__ int sweep(const FLevel &L, int pos, bool use_rng, double M2, bool track, double &gsum, long long &moves) {
+  __device__ __forceinline__ int sweep(const FLevel &L, int pos, bool use_rng, double M2, bool track, double &gsum, long long &moves) {
     const int64_t *off = L.off;
     const int32_t *idx = L.idx;
     const float *w = L.w;
@@ -423,7 +427,7 @@ struct FleetRun {
       if (REFINE) pend &= __ballot(Sd == Ki);
       const unsigned long long one = __ballot(deg <= kWave);
       // Visits the next G candidates of at most NU wavefronts of edges.
-      auto visits = [&](auto nu, auto ng) {
+      auto visits = [&](auto nu, auto ng) __attribute__((always_inline)) {
         constexpr int NU = decltype(nu)::value, G = decltype(ng)::value;
         int p[G];
         {
@@ -455,31 +459,41 @@ struct FleetRun {
             }
           }
         }
+        // (each round's loads are issued for the whole group before the first
+        // is used)
+        int aux[G][NU];  // refinement: community bound of the neighbour, then the community's own vertex's community
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+#pragma unroll
+          for (int u = 0; u < NU; ++u) {
+            if (j[q][u] == b0 + p[q]) j[q][u] = -1;  // self-loops do not count
+            c[q][u] = kEmpty;
+            aux[q][u] = 0;
+            if (j[q][u] >= 0) {
+              c[q][u] = Cl[j[q][u]];
+              if (REFINE) aux[q][u] = CB[j[q][u]];
+            }
+          }
 #pragma unroll
         for (int q = 0; q < G; ++q) {
           const int cbv = REFINE && p[q] >= 0 ? lane_value(cb, p[q]) : 0;
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
-            if (j[q][u] == b0 + p[q]) j[q][u] = -1;  // self-loops do not count
-            c[q][u] = kEmpty;
-            if (j[q][u] >= 0) {
-              c[q][u] = Cl[j[q][u]];
-              if (REFINE && CB[j[q][u]] != cbv) j[q][u] = -1;
+            if (REFINE && aux[q][u] != cbv) {
+              j[q][u] = -1;
+              c[q][u] = kEmpty;
             }
-            if (REFINE && j[q][u] < 0) c[q][u] = kEmpty;
+            S[q][u] = 0.0;
+            if (c[q][u] != kEmpty) {
+              S[q][u] = Sl[c[q][u]];
+              if (REFINE) aux[q][u] = Cl[c[q][u]];
+            }
           }
         }
 #pragma unroll
         for (int q = 0; q < G; ++q)
 #pragma unroll
-          for (int u = 0; u < NU; ++u) {
-            S[q][u] = 0.0;
-            ok[q][u] = true;
-            if (c[q][u] != kEmpty) {
-              S[q][u] = Sl[c[q][u]];
-              if (REFINE) ok[q][u] = Cl[c[q][u]] == c[q][u];
-            }
-          }
+          for (int u = 0; u < NU; ++u) ok[q][u] = !REFINE || aux[q][u] == c[q][u];
         bool live = true;
 #pragma unroll
         for (int q = 0; q < G; ++q) {
@@ -566,7 +580,7 @@ struct FleetRun {
   // ---------------- Alg. "leidenMove" (serial sweep) -----------------------
   // One wider vertex: best community by Eq. 2, applied at once.  Returns true
   // if it moved, with its gain in *gain.
-  __device__ bool move_vertex(const FLevel &L, int i, double M2, bool track, double *gain) {
+  __device__ __forceinline__ bool move_vertex(const FLevel &L, int i, double M2, bool track, double *gain) {
     const int64_t e0 = L.off[i], e1 = L.off[i + 1];
     const int d = g.Cl[i];
     const double Ki = g.Kl[i];
@@ -615,7 +629,7 @@ struct FleetRun {
   }
 
   // Iterations of the local-moving phase; returns l (iterations executed).
-  __device__ int move(const FLevel &L, bool use_rng, double M2, double Tp, bool track, long long &moves_out) {
+  __device__ __forceinline__ int move(const FLevel &L, bool use_rng, double M2, double Tp, bool track, long long &moves_out) {
     int l = 0;
     long long moves = 0;
     for (int it = 0; it < prm.max_iter; ++it) {
@@ -650,7 +664,7 @@ struct FleetRun {
   }
 
   // ---------------- Alg. "leidenRefine" (serial sweep) ---------------------
-  __device__ void refine_vertex(const FLevel &L, int i, double M2) {
+  __device__ __forceinline__ void refine_vertex(const FLevel &L, int i, double M2) {
     const int64_t e0 = L.off[i], e1 = L.off[i + 1];
     const int c = g.Cl[i];
     const int cb = g.CB[i];
@@ -690,7 +704,7 @@ struct FleetRun {
     __syncthreads();
   }
 
-  __device__ void refine(const FLevel &L, double M2) {
+  __device__ __forceinline__ void refine(const FLevel &L, double M2) {
     double gsum = 0.0;
     long long moves = 0;
     for (int pos = 0;;) {
@@ -708,7 +722,7 @@ struct FleetRun {
   }
 
   // ---------------- Alg. "leidenSubsetRenumber", break, renumber -----------
-  __device__ void subset_renumber(int64_t n) {
+  __device__ __forceinline__ void subset_renumber(int64_t n) {
     int32_t *rep = g.tmpi;
     for (int64_t c = B::tid(); c < n; c += T) rep[c] = INT_MAX;
     __syncthreads();
@@ -740,7 +754,7 @@ struct FleetRun {
     __syncthreads();
   }
 
-  __device__ void break_changed(int64_t n) {
+  __device__ __forceinline__ void break_changed(int64_t n) {
     for (int64_t i = B::tid(); i < n; i += T) {
       if (g.dC[g.Cl[i]]) {
         g.Cl[i] = (int)i;
@@ -751,7 +765,7 @@ struct FleetRun {
   }
 
   // Dense ascending relabel of lab[0..n) (labels < bound); returns the count.
-  __device__ int64_t renumber(int32_t *lab, int64_t n, int64_t bound) {
+  __device__ __forceinline__ int64_t renumber(int32_t *lab, int64_t n, int64_t bound) {
     int32_t *map = g.tmpi;
     for (int64_t c = B::tid(); c <= bound; c += T) map[c] = 0;
     __syncthreads();
@@ -771,7 +785,7 @@ struct FleetRun {
   // Three passes of the sort, one to count the pairs, one to write them: 420k
   // entries 160 -> 13 ms in 8 wavefronts, all levels of an update, at
   // the latency of a few loads a wavefront.
-  __device__ FLevel aggregate(const FLevel &L, int64_t nc, int ob) {
+  __device__ __forceinline__ FLevel aggregate(const FLevel &L, int64_t nc, int ob) {
     unsigned long long *key[2] = {g.akey[0], g.akey[1]};
     int32_t *pay[2] = {g.apay[0], g.apay[1]};
     const int32_t *Cl = g.Cl;
@@ -840,7 +854,7 @@ struct FleetRun {
   // ---------------- the pass loop of Alg. "leiden" --------------------------
   // On entry Cl, Kl, Sl, dC, U, rng hold the level-0 state; result: dense
   // labels in g.C.
-  __device__ void core(const FLevel &L0, double M2, bool track) {
+  __device__ __forceinline__ void core(const FLevel &L0, double M2, bool track) {
     const int64_t n0 = L0.n;
     for (int64_t i = B::tid(); i < n0; i += T) g.Ctop[i] = (int)i;
     if (prm.refine_variant == 1) {
@@ -904,7 +918,7 @@ struct FleetRun {
   // ---------------- graph update (Sec. 3.5, 5.1.4) ------------------------
   // Validates the batch against the current CSR and writes G^t into the other
   // buffer.  Returns the error bits (0: applied; the graph then switches).
-  __device__ int apply_batch() {
+  __device__ __forceinline__ int apply_batch() {
     const int64_t n = g.n;
     const int64_t nd = job.nd, ni = job.ni;
     const int64_t E = 2 * (nd + ni);
@@ -1029,7 +1043,7 @@ struct FleetRun {
   // ---------------- marking, changedCommunities, updateWeights -------------
   // On the sorted batch (key / payload buffer r) and G^t; previous C, K,
   // Sigma, M2.  Leaves U = affected, rng = in range, dC = changed.
-  __device__ void mark(int mode, int r) {
+  __device__ __forceinline__ void mark(int mode, int r) {
     const int64_t n = g.n;
     const int64_t nd = job.nd, ni = job.ni;
     const int64_t E = 2 * (nd + ni);
@@ -1123,7 +1137,7 @@ struct FleetRun {
   }
 
   // Eq. 1 of the current graph and g.C (dense labels); also Sigma^t.
-  __device__ double modularity() {
+  __device__ __forceinline__ double modularity() {
     const int64_t n = g.n;
     const int64_t *off = g.off[g.cur];
     const int32_t *idx = g.idx[g.cur];
@@ -1162,7 +1176,7 @@ struct FleetRun {
     return M2 > 0.0 ? q : 0.0;
   }
 
-  __device__ void run() {
+  __device__ __forceinline__ void run() {
     const int mode = job.mode;
     const int64_t n = g.n;
     if (B::tid() == 0) {
