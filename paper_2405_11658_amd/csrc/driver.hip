@@ -896,7 +896,7 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
           continue;
         }
         move_frontier(ma, x.s);
-        for (int b = 0; b + 1 < kNB; ++b) move_propose_bucket(ma, B.region.data(), b, x.s);
+        move_propose(ma, B.region.data(), x.s);
         if (ma.qend > ma.qbeg) {
           hipEvent_t t0 = x.kp ? x.kp->begin() : nullptr;
           move_hub_gather(ma, x.s);
@@ -1105,10 +1105,11 @@ leiden_status run_stateless(Workspace &w, hipStream_t s, const std::function<voi
 }
 
 // Sort rows of a CSR in place (keys = neighbour ids, values = weights).
-void sort_rows(Ctx &x, int64_t n, int64_t nnz, int64_t *off, int32_t *idx, float *w, int32_t *idx2, float *w2) {
+void sort_rows(Ctx &x, int64_t n, int64_t nnz, int64_t *off, int32_t *idx, float *w, int32_t *idx2, float *w2,
+               const int32_t *crow) {
   if (nnz == 0) return;
-  size_t tb = seg_sort_i32_f32(nullptr, 0, idx, idx2, w, w2, nnz, n, off, x.s);
-  seg_sort_i32_f32(x.tmp(tb), tb, idx, idx2, w, w2, nnz, n, off, x.s);
+  size_t tb = seg_sort_i32_f32(nullptr, 0, idx, idx2, w, w2, nnz, n, off, crow, x.s);
+  seg_sort_i32_f32(x.tmp(tb), tb, idx, idx2, w, w2, nnz, n, off, crow, x.s);
   x.launched("segmented sort");
   x.copy(idx, idx2, nnz);
   x.copy(w, w2, nnz);
@@ -1385,14 +1386,23 @@ leiden_status leiden_create(int64_t n, int64_t nnz, const int64_t *offsets, cons
     if (x.read(&sc->err)) x.invalid("offsets are not a valid CSR of nnz entries");
     x.ensure(h->t_idx, (size_t)std::max<int64_t>(nnz, 1) * sizeof(int32_t));
     x.ensure(h->t_w, (size_t)std::max<int64_t>(nnz, 1) * sizeof(float));
-    sort_rows(x, n, nnz, (int64_t *)h->g_off.p, (int32_t *)h->g_idx.p, (float *)h->g_w.p,
-              (int32_t *)h->t_idx.p, (float *)h->t_w.p);
+    // rows that came sorted are checked once and left as they are
     refresh_crow(x, h);
-    check_rows_chunked((const int64_t *)h->g_off.p, (const int32_t *)h->g_idx.p, (const float *)h->g_w.p, n,
-                       nnz, (const int32_t *)h->g_crow.p, &sc->err, x.s);
-    x.launched("check_rows");
-    if (x.read(&sc->err))
-      x.invalid("graph has an id out of range, a non-positive or non-finite weight, or a repeated entry");
+    const char *bad = "graph has an id out of range, a non-positive or non-finite weight, or a repeated entry";
+    auto check = [&] {
+      x.zero(&sc->err, 1);
+      check_rows_chunked((const int64_t *)h->g_off.p, (const int32_t *)h->g_idx.p, (const float *)h->g_w.p, n,
+                         nnz, (const int32_t *)h->g_crow.p, &sc->err, x.s);
+      x.launched("check_rows");
+      return x.read(&sc->err);
+    };
+    const int32_t err = check();
+    if (err & 1) x.invalid(bad);
+    if (err) {
+      sort_rows(x, n, nnz, (int64_t *)h->g_off.p, (int32_t *)h->g_idx.p, (float *)h->g_w.p,
+                (int32_t *)h->t_idx.p, (float *)h->t_w.p, (const int32_t *)h->g_crow.p);
+      if (check()) x.invalid(bad);
+    }
   });
   if (st != LEIDEN_OK) {
     h->release(x.s);

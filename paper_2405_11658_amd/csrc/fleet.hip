@@ -377,19 +377,20 @@ leiden_status leiden_fleet_create(int32_t count, const int64_t *n, const int64_t
           f->err = "graph " + std::to_string(k) + ": offsets are not a valid CSR of nnz entries";
           throw Fail{LEIDEN_EINVAL};
         }
+        const int64_t nch = ceil_div(std::max<int64_t>(nnz[k], 1), kChunk);
+        f->ensure(crow, (nch + 2) * sizeof(int32_t), s);
+        chunk_start_rows(g.off[0], n[k], nnz[k], (int32_t *)crow.p, s);
         if (nnz[k] > 0) {
           f->ensure(tidx, nnz[k] * sizeof(int32_t), s);
           f->ensure(tw, nnz[k] * sizeof(float), s);
           size_t tb = seg_sort_i32_f32(nullptr, 0, g.idx[0], (int32_t *)tidx.p, g.w[0], (float *)tw.p, nnz[k], n[k],
-                                       g.off[0], s);
+                                       g.off[0], (const int32_t *)crow.p, s);
           f->ensure(tmp, tb + 16, s);
-          seg_sort_i32_f32(tmp.p, tb, g.idx[0], (int32_t *)tidx.p, g.w[0], (float *)tw.p, nnz[k], n[k], g.off[0], s);
+          seg_sort_i32_f32(tmp.p, tb, g.idx[0], (int32_t *)tidx.p, g.w[0], (float *)tw.p, nnz[k], n[k], g.off[0],
+                           (const int32_t *)crow.p, s);
           f->check(hipMemcpyAsync(g.idx[0], tidx.p, nnz[k] * sizeof(int32_t), hipMemcpyDeviceToDevice, s), "copy");
           f->check(hipMemcpyAsync(g.w[0], tw.p, nnz[k] * sizeof(float), hipMemcpyDeviceToDevice, s), "copy");
         }
-        const int64_t nch = ceil_div(std::max<int64_t>(nnz[k], 1), kChunk);
-        f->ensure(crow, (nch + 2) * sizeof(int32_t), s);
-        chunk_start_rows(g.off[0], n[k], nnz[k], (int32_t *)crow.p, s);
         check_rows_chunked(g.off[0], g.idx[0], g.w[0], n[k], nnz[k], (const int32_t *)crow.p, e, s);
         f->check(hipGetLastError(), "validation kernels");
         f->check(hipMemcpyAsync(&he, e, sizeof(int32_t), hipMemcpyDeviceToHost, s), "D2H");

@@ -86,53 +86,67 @@ void slice_scatter(int64_t n, int S, const int32_t *slice_off, int32_t *slice_fi
 
 // Frontier of slice s: its unprocessed vertices become processed; in-range
 // ones with edges are bucketed by degree.  Proposals of the slice are reset.
-__device__ __forceinline__ int frontier_key(const MoveArgs &a, int i) {
-  if (!a.U[i] || !a.rng[i]) return -1;
-  const int64_t deg = a.off[i + 1] - a.off[i];
-  return deg > 0 ? bucket_of_d(deg, a.hubdeg) : -1;
-}
-
+// A thread's vertices of a tile stay in its registers between the count and
+// the placing.  The slices of small graphs are a tile or two, and a launch in
+// the chain of slices lasts as long as its longest workgroup (4096 vertices,
+// each read twice: 19 us, 1024: 6.5).
+constexpr int kFrontPer = 4;
+constexpr int kFrontTile = 256 * kFrontPer;
 __global__ __launch_bounds__(256) void k_frontier(MoveArgs a) {
   __shared__ int cnt[kNB];
   __shared__ int base[kNB];
   int32_t *counts = a.counts + a.s * kNB;
   const int32_t *region = a.region + a.s * kNB;
-  for (int64_t t0 = a.vbeg + (int64_t)blockIdx.x * kTile; t0 < a.vend; t0 += (int64_t)gridDim.x * kTile) {
-    const int64_t t1 = min(t0 + (int64_t)kTile, a.vend);
+  for (int64_t t0 = a.vbeg + (int64_t)blockIdx.x * kFrontTile; t0 < a.vend; t0 += (int64_t)gridDim.x * kFrontTile) {
     if (threadIdx.x < kNB) cnt[threadIdx.x] = 0;
+    int i[kFrontPer], key[kFrontPer], at[kFrontPer];
+    uint8_t u[kFrontPer], r[kFrontPer];
+    int64_t deg[kFrontPer];
+#pragma unroll
+    for (int k = 0; k < kFrontPer; ++k) {
+      const int64_t t = t0 + threadIdx.x + k * 256;
+      i[k] = t < a.vend ? a.vbyslice[t] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < kFrontPer; ++k) {
+      u[k] = i[k] >= 0 ? a.U[i[k]] : 0;
+      r[k] = i[k] >= 0 ? a.rng[i[k]] : 0;
+      deg[k] = i[k] >= 0 ? a.off[i[k] + 1] - a.off[i[k]] : 0;
+    }
     __syncthreads();
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
-      const int key = frontier_key(a, a.vbyslice[t]);
-      if (key >= 0) atomicAdd(&cnt[key], 1);
+#pragma unroll
+    for (int k = 0; k < kFrontPer; ++k) {
+      key[k] = u[k] && r[k] && deg[k] > 0 ? bucket_of_d(deg[k], a.hubdeg) : -1;
+      at[k] = key[k] >= 0 ? atomicAdd(&cnt[key[k]], 1) : 0;
     }
     __syncthreads();
     if (threadIdx.x < kNB) {
       const int c = cnt[threadIdx.x];
       base[threadIdx.x] = c ? atomicAdd(&counts[threadIdx.x], c) : 0;
-      cnt[threadIdx.x] = 0;
     }
     __syncthreads();
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
-      const int i = a.vbyslice[t];
-      const int key = frontier_key(a, i);
-      a.prop[i] = -1;
-      a.U[i] = 0;
-      if (a.act && a.off[i + 1] - a.off[i] > a.hubdeg) a.act[i] = key >= 0;
-      if (key >= 0) a.lists[region[key] + base[key] + atomicAdd(&cnt[key], 1)] = i;
+#pragma unroll
+    for (int k = 0; k < kFrontPer; ++k) {
+      if (i[k] < 0) continue;
+      a.prop[i[k]] = -1;
+      a.U[i[k]] = 0;
+      if (a.act && deg[k] > a.hubdeg) a.act[i[k]] = key[k] >= 0;
+      if (key[k] >= 0) a.lists[region[key[k]] + base[key[k]] + at[k]] = i[k];
     }
     __syncthreads();
   }
 }
 
 // ---- propose: small-degree groups (deg <= G), all-pairs combine in registers
+// (by workgroups blk of nblk, as in the other buckets)
 template <int G>
-__global__ __launch_bounds__(256) void k_propose_small(MoveArgs a, int b) {
+__device__ __forceinline__ void propose_small(const MoveArgs &a, int b, int blk, int nblk) {
   const int count = a.counts[a.s * kNB + b];
   const int32_t *list = a.lists + a.region[a.s * kNB + b];
   const int gl = threadIdx.x & (G - 1);
   // the loop runs in step for the whole wavefront (collectives stay uniform)
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nwave = (int64_t)gridDim.x * blockDim.x / kWave;
+  const int64_t wave = ((int64_t)blk * 256 + threadIdx.x) / kWave;
+  const int64_t nwave = (int64_t)nblk * 256 / kWave;
   const int gin = lane() / G;
   for (int64_t v0 = wave * (kWave / G); v0 < count; v0 += nwave * (kWave / G)) {
     const int64_t v = v0 + gin;
@@ -190,29 +204,34 @@ __device__ __forceinline__ uint32_t pow2_at_least(uint64_t x) {
 // ---- propose: a team (wavefront or workgroup) per vertex, hash table of T
 // slots per team in LDS.
 template <int TEAM, int T, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_propose_team(MoveArgs a, int b) {
+struct TeamLds {
+  static constexpr int NT = BLOCK / TEAM;
+  double svals[NT * T];
+  double sb[NT];
+  double rg[BLOCK / kWave];
+  int skeys[NT * T];
+  int rc[BLOCK / kWave];
+};
+template <int TEAM, int T, int BLOCK>
+__device__ __forceinline__ void propose_team(const MoveArgs &a, int b, int blk, int nblk,
+                                             TeamLds<TEAM, T, BLOCK> &l) {
   constexpr int NT = BLOCK / TEAM;
-  __shared__ int skeys[NT * T];
-  __shared__ double svals[NT * T];
-  __shared__ double sb[NT];
-  __shared__ double rg[BLOCK / kWave];
-  __shared__ int rc[BLOCK / kWave];
   const int team = threadIdx.x / TEAM;
   const int t = threadIdx.x % TEAM;
   const int count = a.counts[a.s * kNB + b];
   const int32_t *list = a.lists + a.region[a.s * kNB + b];
-  for (int64_t base = (int64_t)blockIdx.x * NT; base < count; base += (int64_t)gridDim.x * NT) {
+  for (int64_t base = (int64_t)blk * NT; base < count; base += (int64_t)nblk * NT) {
     const int64_t v = base + team;
     const bool valid = v < count;
     const int i = valid ? list[v] : 0;
     int64_t e0 = 0, e1 = 0;
     int d = 0;
     if (valid) { e0 = a.off[i]; e1 = a.off[i + 1]; d = a.C[i]; }
-    int *keys = skeys + team * T;
-    double *vals = svals + team * T;
+    int *keys = l.skeys + team * T;
+    double *vals = l.svals + team * T;
     const uint32_t mask = T - 1;
     for (uint32_t s = t; s <= mask; s += TEAM) { keys[s] = kEmpty; vals[s] = 0.0; }
-    if (t == 0) sb[team] = 0.0;
+    if (t == 0) l.sb[team] = 0.0;
     __syncthreads();
     if (valid) {
       for (int64_t e = e0 + t; e < e1; e += TEAM) {
@@ -223,12 +242,12 @@ __global__ __launch_bounds__(BLOCK) void k_propose_team(MoveArgs a, int b) {
     __syncthreads();
     if (valid)
       for (uint32_t s = t; s <= mask; s += TEAM)
-        if (keys[s] == d) sb[team] = vals[s];
+        if (keys[s] == d) l.sb[team] = vals[s];
     __syncthreads();
     double bg = 0.0;
     int bc = kNoComm;
     if (valid) {
-      const double bown = sb[team];
+      const double bown = l.sb[team];
       const double Ki = a.K[i];
       const double Sd = a.Sig[d];
       for (uint32_t s = t; s <= mask; s += TEAM) {
@@ -238,13 +257,44 @@ __global__ __launch_bounds__(BLOCK) void k_propose_team(MoveArgs a, int b) {
         if (x > 0.0 && better(x, c, bg, bc)) { bg = x; bc = c; }
       }
     }
-    team_argmax<TEAM, BLOCK>(bg, bc, rg, rc);
+    team_argmax<TEAM, BLOCK>(bg, bc, l.rg, l.rc);
     if (valid && t == 0) {
       a.from[i] = d;
       a.prop[i] = (bc == kNoComm) ? -1 : bc;
       a.gp[i] = bg;
     }
     __syncthreads();
+  }
+}
+
+template <int TEAM, int T, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_propose_team(MoveArgs a, int b) {
+  __shared__ TeamLds<TEAM, T, BLOCK> l;
+  propose_team<TEAM, T, BLOCK>(a, b, blockIdx.x, gridDim.x, l);
+}
+template <int G>
+__global__ __launch_bounds__(256) void k_propose_small(MoveArgs a, int b) {
+  propose_small<G>(a, b, blockIdx.x, gridDim.x);
+}
+// All buckets but the hubs in one launch.  Its workgroups all have the largest
+// table's LDS, three to a compute unit: for the slices whose workgroups all
+// run at once that way, a slice being a chain of launches of which each lasts
+// as long as its slowest workgroup (R-MAT scale 17, 1/32 of 100k vertices: five
+// launches 35 us, this one 12).
+__global__ __launch_bounds__(256) void k_propose_slice(MoveArgs a, BucketSpan sp) {
+  __shared__ union {
+    TeamLds<64, 512, 256> wave;
+    TeamLds<256, 4096, 256> block;
+  } l;
+  int b = 0;
+  while ((int)blockIdx.x >= sp.first[b + 1]) ++b;
+  const int blk = blockIdx.x - sp.first[b], nblk = sp.first[b + 1] - sp.first[b];
+  switch (b) {
+    case 0: propose_small<4>(a, b, blk, nblk); break;
+    case 1: propose_small<8>(a, b, blk, nblk); break;
+    case 2: propose_small<32>(a, b, blk, nblk); break;
+    case 3: propose_team<64, 512, 256>(a, b, blk, nblk, l.wave); break;
+    default: propose_team<256, 4096, 256>(a, b, blk, nblk, l.block); break;
   }
 }
 
@@ -369,37 +419,6 @@ __device__ __forceinline__ void hub_score_segment(const MoveArgs &a, int64_t q, 
   }
   team_argmax<256, 256>(bg, bc, rg, rc);
 }
-__global__ __launch_bounds__(256) void k_hub_score(MoveArgs a) {
-  const int64_t q = a.gbeg + blockIdx.x;
-  const int h = a.hp.shub[q];
-  const int i = a.hp.hubv[h];
-  if (!a.act[i]) return;
-  double bg;
-  int bc;
-  hub_score_segment(a, q, h, i, bg, bc);
-  if (threadIdx.x == 0) { a.hp.pg[q] = bg; a.hp.pc[q] = bc; }
-}
-
-// final: a wavefront per hub of the slice reduces the segment results.
-__global__ __launch_bounds__(256) void k_hub_final(MoveArgs a) {
-  const int64_t h = a.hbeg + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  if (h >= a.hend) return;  // uniform per wavefront
-  const int i = a.hp.hubv[h];
-  if (!a.act[i]) return;
-  double bg = 0.0;
-  int bc = kNoComm;
-  for (int64_t q = a.hp.hsg[h] + lane(); q < a.hp.hsg[h + 1]; q += kWave)
-    if (better(a.hp.pg[q], a.hp.pc[q], bg, bc)) { bg = a.hp.pg[q]; bc = a.hp.pc[q]; }
-  group_argmax<kWave>(bg, bc);
-  if (lane() == 0) {
-    a.from[i] = a.C[i];
-    a.prop[i] = (bc == kNoComm) ? -1 : bc;
-    a.gp[i] = bg;
-    a.hp.own[h] = 0.0;
-    a.hp.flag[h] = 0;
-  }
-}
-
 // ---- hub plan -------------------------------------------------------------------
 // Each workgroup takes a contiguous range of vertices, counts its hubs per
 // slice in LDS, reserves each slice's places with one global atomic and then
@@ -522,12 +541,12 @@ __device__ __forceinline__ void do_move(const MoveArgs &a, int i, int fi, int p,
 }
 
 template <int G>
-__global__ __launch_bounds__(256) void k_apply_small(MoveArgs a, int b) {
+__device__ __forceinline__ void apply_small(const MoveArgs &a, int b, int blk, int nblk) {
   const int count = a.counts[a.s * kNB + b];
   const int32_t *list = a.lists + a.region[a.s * kNB + b];
   const int gl = threadIdx.x & (G - 1);
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nwave = (int64_t)gridDim.x * blockDim.x / kWave;
+  const int64_t wave = ((int64_t)blk * 256 + threadIdx.x) / kWave;
+  const int64_t nwave = (int64_t)nblk * 256 / kWave;
   const int gin = lane() / G;
   double gsum = 0.0;
   long long mv = 0;
@@ -566,7 +585,7 @@ __global__ __launch_bounds__(256) void k_apply_small(MoveArgs a, int b) {
 }
 
 template <int TEAM, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_apply_team(MoveArgs a, int b) {
+__device__ __forceinline__ void apply_team(const MoveArgs &a, int b, int blk, int nblk) {
   constexpr int NT = BLOCK / TEAM;
   __shared__ int sany[NT];
   const int team = threadIdx.x / TEAM;
@@ -575,7 +594,7 @@ __global__ __launch_bounds__(BLOCK) void k_apply_team(MoveArgs a, int b) {
   const int32_t *list = a.lists + a.region[a.s * kNB + b];
   double gsum = 0.0;
   long long mv = 0;
-  for (int64_t base = (int64_t)blockIdx.x * NT; base < count; base += (int64_t)gridDim.x * NT) {
+  for (int64_t base = (int64_t)blk * NT; base < count; base += (int64_t)nblk * NT) {
     const int64_t v = base + team;
     const bool valid = v < count;
     const int i = valid ? list[v] : 0;
@@ -620,70 +639,6 @@ __global__ __launch_bounds__(BLOCK) void k_apply_team(MoveArgs a, int b) {
   flush_gain(a, gsum, mv);
 }
 
-// ---- launchers -----------------------------------------------------------------
-static int grid_for(int64_t cap, int per_block, int maxb = 4096) {
-  int64_t g = ceil_div(cap, per_block);
-  if (g < 1) g = 1;
-  return (int)(g < maxb ? g : maxb);
-}
-
-void move_frontier(const MoveArgs &a, hipStream_t s) {
-  if (a.vend > a.vbeg)
-    hipLaunchKernelGGL(k_frontier, flat_grid(ceil_div(a.vend - a.vbeg, kTile), 1, 2048), 256, 0, s, a);
-}
-
-void move_propose(const MoveArgs &a, const int64_t *region_h, hipStream_t s) {
-  for (int b = 0; b < kNB; ++b) move_propose_bucket(a, region_h, b, s);
-}
-
-void move_propose_bucket(const MoveArgs &a, const int64_t *region_h, int b, hipStream_t s) {
-  {
-    const int64_t cap = region_h[a.s * kNB + b + 1] - region_h[a.s * kNB + b];
-    if (cap <= 0) return;
-    switch (b) {
-      case 0: hipLaunchKernelGGL(k_propose_small<4>, grid_for(cap, 64), 256, 0, s, a, b); break;
-      case 1: hipLaunchKernelGGL(k_propose_small<8>, grid_for(cap, 32), 256, 0, s, a, b); break;
-      case 2: hipLaunchKernelGGL(k_propose_small<32>, grid_for(cap, 8), 256, 0, s, a, b); break;
-      case 3: hipLaunchKernelGGL((k_propose_team<64, 512, 256>), grid_for(cap, 4), 256, 0, s, a, b); break;
-      case 4: hipLaunchKernelGGL((k_propose_team<256, 4096, 256>), grid_for(cap, 1, 2048), 256, 0, s, a, b); break;
-      case 5:
-        move_hub_gather(a, s);
-        move_hub_score(a, s);
-        break;
-    }
-  }
-}
-
-void move_hub_gather(const MoveArgs &a, hipStream_t s) {
-  if (a.qend > a.qbeg) hipLaunchKernelGGL(k_hub_gather, (int)(a.qend - a.qbeg), 256, 0, s, a);
-}
-
-void move_hub_score(const MoveArgs &a, hipStream_t s) {
-  if (a.qend > a.qbeg) {
-    hipLaunchKernelGGL(k_hub_score, (int)(a.gend - a.gbeg), 256, 0, s, a);
-    hipLaunchKernelGGL(k_hub_final, (int)ceil_div(a.hend - a.hbeg, (int64_t)4), 256, 0, s, a);
-  }
-}
-
-void move_apply(const MoveArgs &a, const int64_t *region_h, hipStream_t s) {
-  for (int b = 0; b < kNB; ++b) move_apply_bucket(a, region_h, b, s);
-}
-
-void move_hub_apply(const MoveArgs &a, hipStream_t s);
-
-void move_apply_bucket(const MoveArgs &a, const int64_t *region_h, int b, hipStream_t s) {
-  const int64_t cap = region_h[a.s * kNB + b + 1] - region_h[a.s * kNB + b];
-  if (cap <= 0) return;
-  switch (b) {
-    case 0: hipLaunchKernelGGL(k_apply_small<4>, grid_for(cap, 64), 256, 0, s, a, b); break;
-    case 1: hipLaunchKernelGGL(k_apply_small<8>, grid_for(cap, 32), 256, 0, s, a, b); break;
-    case 2: hipLaunchKernelGGL(k_apply_small<32>, grid_for(cap, 8), 256, 0, s, a, b); break;
-    case 3: hipLaunchKernelGGL((k_apply_team<64, 256>), grid_for(cap, 4), 256, 0, s, a, b); break;
-    case 4: hipLaunchKernelGGL((k_apply_team<256, 256>), grid_for(cap, 1, 2048), 256, 0, s, a, b); break;
-    case 5: move_hub_apply(a, s); break;
-  }
-}
-
 // ---- apply for hubs, chunk-parallel --------------------------------------------
 // The same rule as the other buckets, with the hub's edge chunks spread over
 // workgroups: (1) a chunk that finds a same-slice neighbour proposing the
@@ -707,7 +662,26 @@ __device__ __forceinline__ void hub_rev_chunk(const MoveArgs &a, int64_t q) {
   }
   if (blocked) a.hp.flag[h] = 1;
 }
-__global__ __launch_bounds__(256) void k_hub_rev(MoveArgs a) { hub_rev_chunk(a, a.qbeg + blockIdx.x); }
+// All buckets of a slice but the hubs, and the reverse checks of the hubs'
+// chunks (the first `chunks` workgroups): nothing that one of them reads is
+// written by another.
+__global__ __launch_bounds__(256) void k_apply_slice(MoveArgs a, BucketSpan sp, int chunks) {
+  if ((int)blockIdx.x < chunks) {
+    hub_rev_chunk(a, a.qbeg + blockIdx.x);
+    return;
+  }
+  const int at = blockIdx.x - chunks;
+  int b = 0;
+  while (at >= sp.first[b + 1]) ++b;
+  const int blk = at - sp.first[b], nblk = sp.first[b + 1] - sp.first[b];
+  switch (b) {
+    case 0: apply_small<4>(a, b, blk, nblk); break;
+    case 1: apply_small<8>(a, b, blk, nblk); break;
+    case 2: apply_small<32>(a, b, blk, nblk); break;
+    case 3: apply_team<64, 256>(a, b, blk, nblk); break;
+    default: apply_team<256, 256>(a, b, blk, nblk); break;
+  }
+}
 
 __global__ __launch_bounds__(256) void k_hub_mark(MoveArgs a) {
   const int64_t q = a.qbeg + blockIdx.x;
@@ -734,12 +708,6 @@ __global__ __launch_bounds__(256) void k_hub_mark(MoveArgs a) {
     const int j = a.idx[e];
     if (j != i) a.U[j] = 1;
   }
-}
-
-void move_hub_apply(const MoveArgs &a, hipStream_t s) {
-  if (a.qend <= a.qbeg) return;
-  hipLaunchKernelGGL(k_hub_rev, (int)(a.qend - a.qbeg), 256, 0, s, a);
-  hipLaunchKernelGGL(k_hub_mark, (int)(a.qend - a.qbeg), 256, 0, s, a);
 }
 
 // ---- the hub slices of the asynchronous mode -------------------------------------
@@ -870,6 +838,48 @@ __global__ __launch_bounds__(256) void k_hub_apply(MoveArgs a, int chunks, int64
     const int j = a.idx[e];
     if (j != i) a.U[j] = 1;
   }
+}
+
+// ---- launchers -----------------------------------------------------------------
+void move_frontier(const MoveArgs &a, hipStream_t s) {
+  if (a.vend > a.vbeg)
+    hipLaunchKernelGGL(k_frontier, flat_grid(ceil_div(a.vend - a.vbeg, kFrontTile), 1, 2048), 256, 0, s, a);
+}
+
+void move_propose(const MoveArgs &a, const int64_t *region_h, hipStream_t s) {
+  const BucketSpan sp = bucket_span(region_h + a.s * kNB);
+  if (sp.first[kNB - 1] == 0) return;
+  if (sp.first[kNB - 1] <= kShareLaunch) {
+    hipLaunchKernelGGL(k_propose_slice, sp.first[kNB - 1], 256, 0, s, a, sp);
+    return;
+  }
+  for (int b = 0; b + 1 < kNB; ++b) {
+    const int g = sp.first[b + 1] - sp.first[b];
+    if (g == 0) continue;
+    switch (b) {
+      case 0: hipLaunchKernelGGL(k_propose_small<4>, g, 256, 0, s, a, b); break;
+      case 1: hipLaunchKernelGGL(k_propose_small<8>, g, 256, 0, s, a, b); break;
+      case 2: hipLaunchKernelGGL(k_propose_small<32>, g, 256, 0, s, a, b); break;
+      case 3: hipLaunchKernelGGL((k_propose_team<64, 512, 256>), g, 256, 0, s, a, b); break;
+      default: hipLaunchKernelGGL((k_propose_team<256, 4096, 256>), g, 256, 0, s, a, b); break;
+    }
+  }
+}
+
+void move_hub_gather(const MoveArgs &a, hipStream_t s) {
+  if (a.qend > a.qbeg) hipLaunchKernelGGL(k_hub_gather, (int)(a.qend - a.qbeg), 256, 0, s, a);
+}
+
+void move_hub_score(const MoveArgs &a, hipStream_t s) {
+  if (a.qend > a.qbeg) hipLaunchKernelGGL(k_hub_score_final, (int)(a.gend - a.gbeg), 256, 0, s, a);
+}
+
+void move_apply(const MoveArgs &a, const int64_t *region_h, hipStream_t s) {
+  const BucketSpan sp = bucket_span(region_h + a.s * kNB);
+  const int nq = (int)(a.qend - a.qbeg);
+  if (nq + sp.first[kNB - 1] > 0)
+    hipLaunchKernelGGL(k_apply_slice, nq + sp.first[kNB - 1], 256, 0, s, a, sp, nq);
+  if (nq > 0) hipLaunchKernelGGL(k_hub_mark, nq, 256, 0, s, a);
 }
 
 void move_hubs(const MoveArgs &a, bool wide, hipStream_t s) {

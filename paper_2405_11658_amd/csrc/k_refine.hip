@@ -103,13 +103,14 @@ void refine_break(const RefineArgs &a, hipStream_t s) {
 }
 
 // ---- refine propose ------------------------------------------------------------
+// (by workgroups blk of nblk, as in the other buckets)
 template <int G>
-__global__ __launch_bounds__(256) void k_rprop_small(RefineArgs a, int b) {
+__device__ __forceinline__ void rprop_small(const RefineArgs &a, int b, int blk, int nblk) {
   const int count = a.counts[a.s * kNB + b];
   const int32_t *list = a.lists + a.region[a.s * kNB + b];
   const int gl = threadIdx.x & (G - 1);
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nwave = (int64_t)gridDim.x * blockDim.x / kWave;
+  const int64_t wave = ((int64_t)blk * 256 + threadIdx.x) / kWave;
+  const int64_t nwave = (int64_t)nblk * 256 / kWave;
   const int gin = lane() / G;
   for (int64_t v0 = wave * (kWave / G); v0 < count; v0 += nwave * (kWave / G)) {
     const int64_t v = v0 + gin;
@@ -157,18 +158,23 @@ __global__ __launch_bounds__(256) void k_rprop_small(RefineArgs a, int b) {
 
 
 template <int TEAM, int T, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_rprop_team(RefineArgs a, int b) {
+struct RTeamLds {
+  static constexpr int NT = BLOCK / TEAM;
+  double svals[NT * T];
+  double sb[NT];
+  double rg[BLOCK / kWave];
+  int skeys[NT * T];
+  int rc[BLOCK / kWave];
+};
+template <int TEAM, int T, int BLOCK>
+__device__ __forceinline__ void rprop_team(const RefineArgs &a, int b, int blk, int nblk,
+                                           RTeamLds<TEAM, T, BLOCK> &l) {
   constexpr int NT = BLOCK / TEAM;
-  __shared__ int skeys[NT * T];
-  __shared__ double svals[NT * T];
-  __shared__ double sb[NT];
-  __shared__ double rg[BLOCK / kWave];
-  __shared__ int rc[BLOCK / kWave];
   const int team = threadIdx.x / TEAM;
   const int t = threadIdx.x % TEAM;
   const int count = a.counts[a.s * kNB + b];
   const int32_t *list = a.lists + a.region[a.s * kNB + b];
-  for (int64_t base = (int64_t)blockIdx.x * NT; base < count; base += (int64_t)gridDim.x * NT) {
+  for (int64_t base = (int64_t)blk * NT; base < count; base += (int64_t)nblk * NT) {
     const int64_t v = base + team;
     const bool valid = v < count;
     const int i = valid ? list[v] : 0;
@@ -176,11 +182,11 @@ __global__ __launch_bounds__(BLOCK) void k_rprop_team(RefineArgs a, int b) {
     int64_t e0 = 0, e1 = 0;
     int cbi = 0;
     if (active) { e0 = a.off[i]; e1 = a.off[i + 1]; cbi = a.CB[i]; }
-    int *keys = skeys + team * T;
-    double *vals = svals + team * T;
+    int *keys = l.skeys + team * T;
+    double *vals = l.svals + team * T;
     const uint32_t mask = T - 1;
     for (uint32_t s = t; s <= mask; s += TEAM) { keys[s] = kEmpty; vals[s] = 0.0; }
-    if (t == 0) sb[team] = 0.0;
+    if (t == 0) l.sb[team] = 0.0;
     __syncthreads();
     if (active) {
       for (int64_t e = e0 + t; e < e1; e += TEAM) {
@@ -191,12 +197,12 @@ __global__ __launch_bounds__(BLOCK) void k_rprop_team(RefineArgs a, int b) {
     __syncthreads();
     if (active)
       for (uint32_t s = t; s <= mask; s += TEAM)
-        if (keys[s] == i) sb[team] = vals[s];
+        if (keys[s] == i) l.sb[team] = vals[s];
     __syncthreads();
     double bg = 0.0;
     int bc = kNoComm;
     if (active) {
-      const double bown = sb[team];
+      const double bown = l.sb[team];
       const double Ki = a.K[i];
       const double Sd = a.Sig[i];
       for (uint32_t s = t; s <= mask; s += TEAM) {
@@ -209,11 +215,11 @@ __global__ __launch_bounds__(BLOCK) void k_rprop_team(RefineArgs a, int b) {
     group_argmax<kWave>(bg, bc);
     if (TEAM > kWave) {
       const int w = threadIdx.x / kWave;
-      if (lane() == 0) { rg[w] = bg; rc[w] = bc; }
+      if (lane() == 0) { l.rg[w] = bg; l.rc[w] = bc; }
       __syncthreads();
       if (t == 0)
         for (int k = 1; k < TEAM / kWave; ++k)
-          if (better(rg[w + k], rc[w + k], bg, bc)) { bg = rg[w + k]; bc = rc[w + k]; }
+          if (better(l.rg[w + k], l.rc[w + k], bg, bc)) { bg = l.rg[w + k]; bc = l.rc[w + k]; }
       __syncthreads();
     }
     if (valid && t == 0) {
@@ -223,11 +229,32 @@ __global__ __launch_bounds__(BLOCK) void k_rprop_team(RefineArgs a, int b) {
     __syncthreads();
   }
 }
-
-static int rgrid(int64_t cap, int per_block, int maxb = 4096) {
-  int64_t g = ceil_div(cap, per_block);
-  if (g < 1) g = 1;
-  return (int)(g < maxb ? g : maxb);
+template <int TEAM, int T, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_rprop_team(RefineArgs a, int b) {
+  __shared__ RTeamLds<TEAM, T, BLOCK> l;
+  rprop_team<TEAM, T, BLOCK>(a, b, blockIdx.x, gridDim.x, l);
+}
+template <int G>
+__global__ __launch_bounds__(256) void k_rprop_small(RefineArgs a, int b) {
+  rprop_small<G>(a, b, blockIdx.x, gridDim.x);
+}
+// All buckets but the hubs in one launch, for the slices whose workgroups all
+// run at once with the largest table's LDS (as in local moving).
+__global__ __launch_bounds__(256) void k_rprop_slice(RefineArgs a, BucketSpan sp) {
+  __shared__ union {
+    RTeamLds<64, 512, 256> wave;
+    RTeamLds<256, 4096, 256> block;
+  } l;
+  int b = 0;
+  while ((int)blockIdx.x >= sp.first[b + 1]) ++b;
+  const int blk = blockIdx.x - sp.first[b], nblk = sp.first[b + 1] - sp.first[b];
+  switch (b) {
+    case 0: rprop_small<4>(a, b, blk, nblk); break;
+    case 1: rprop_small<8>(a, b, blk, nblk); break;
+    case 2: rprop_small<32>(a, b, blk, nblk); break;
+    case 3: rprop_team<64, 512, 256>(a, b, blk, nblk, l.wave); break;
+    default: rprop_team<256, 4096, 256>(a, b, blk, nblk, l.block); break;
+  }
 }
 
 // ---- refine propose for hubs: several workgroups per candidate -------------------
@@ -361,58 +388,6 @@ __device__ __forceinline__ void rhub_score_segment(const RefineArgs &a, int64_t 
   }
   team_argmax<256, 256>(bg, bc, rg, rc);
 }
-__global__ __launch_bounds__(256) void k_rhub_score(RefineArgs a) {
-  const int64_t q = a.gbeg + blockIdx.x;
-  const int h = a.hp.shub[q];
-  const int i = a.hp.hubv[h];
-  if (!a.act[i]) return;
-  double bg;
-  int bc;
-  rhub_score_segment(a, q, h, i, bg, bc);
-  if (threadIdx.x == 0) { a.hp.pg[q] = bg; a.hp.pc[q] = bc; }
-}
-
-__global__ __launch_bounds__(256) void k_rhub_final(RefineArgs a) {
-  const int64_t h = a.hbeg + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  if (h >= a.hend) return;  // uniform per wavefront
-  const int i = a.hp.hubv[h];
-  if (!a.act[i]) return;
-  double bg = 0.0;
-  int bc = kNoComm;
-  for (int64_t q = a.hp.hsg[h] + lane(); q < a.hp.hsg[h + 1]; q += kWave)
-    if (better(a.hp.pg[q], a.hp.pc[q], bg, bc)) { bg = a.hp.pg[q]; bc = a.hp.pc[q]; }
-  group_argmax<kWave>(bg, bc);
-  if (lane() == 0) {
-    a.prop[i] = (bc == kNoComm) ? -1 : bc;
-    a.gp[i] = bg;
-    a.hp.own[h] = 0.0;
-  }
-}
-
-static void refine_hubs_sync(const RefineArgs &a, hipStream_t s) {
-  if (a.hend <= a.hbeg || a.qend <= a.qbeg) return;  // every hub has edge chunks
-  hipLaunchKernelGGL(k_rhub_gather, (int)(a.qend - a.qbeg), 256, 0, s, a);
-  hipLaunchKernelGGL(k_rhub_score, (int)(a.gend - a.gbeg), 256, 0, s, a);
-  hipLaunchKernelGGL(k_rhub_final, (int)ceil_div(a.hend - a.hbeg, (int64_t)4), 256, 0, s, a);
-}
-
-void refine_propose(const RefineArgs &a, const int64_t *region_h, hipStream_t s) {
-  for (int b = 0; b < kNB; ++b) refine_propose_bucket(a, region_h, b, s);
-}
-
-void refine_propose_bucket(const RefineArgs &a, const int64_t *region_h, int b, hipStream_t s) {
-  const int64_t cap = region_h[a.s * kNB + b + 1] - region_h[a.s * kNB + b];
-  if (cap <= 0) return;
-  switch (b) {
-    case 0: hipLaunchKernelGGL(k_rprop_small<4>, rgrid(cap, 64), 256, 0, s, a, b); break;
-    case 1: hipLaunchKernelGGL(k_rprop_small<8>, rgrid(cap, 32), 256, 0, s, a, b); break;
-    case 2: hipLaunchKernelGGL(k_rprop_small<32>, rgrid(cap, 8), 256, 0, s, a, b); break;
-    case 3: hipLaunchKernelGGL((k_rprop_team<64, 512, 256>), rgrid(cap, 4), 256, 0, s, a, b); break;
-    case 4: hipLaunchKernelGGL((k_rprop_team<256, 4096, 256>), rgrid(cap, 1, 2048), 256, 0, s, a, b); break;
-    case 5: refine_hubs_sync(a, s); break;
-  }
-}
-
 // Accept the proposals of slice s.  p "is proposing" only if p belongs to
 // slice s and proposed in it.  One thread per list slot of the slice.
 __global__ void k_raccept(RefineArgs a, int64_t beg, int64_t end) {
@@ -508,6 +483,31 @@ __global__ __launch_bounds__(256) void k_rhub_score_final(RefineArgs a) {
   if (threadIdx.x == 0) {
     a.prop[i] = bc == kNoComm ? -1 : bc;
     a.gp[i] = bg;
+  }
+}
+
+// The synchronous mode's proposals of a slice.
+void refine_propose(const RefineArgs &a, const int64_t *region_h, hipStream_t s) {
+  const BucketSpan sp = bucket_span(region_h + a.s * kNB);
+  const int n = sp.first[kNB - 1];
+  if (n > 0 && n <= kShareLaunch) {
+    hipLaunchKernelGGL(k_rprop_slice, n, 256, 0, s, a, sp);
+  } else {
+    for (int b = 0; b + 1 < kNB; ++b) {
+      const int g = sp.first[b + 1] - sp.first[b];
+      if (g == 0) continue;
+      switch (b) {
+        case 0: hipLaunchKernelGGL(k_rprop_small<4>, g, 256, 0, s, a, b); break;
+        case 1: hipLaunchKernelGGL(k_rprop_small<8>, g, 256, 0, s, a, b); break;
+        case 2: hipLaunchKernelGGL(k_rprop_small<32>, g, 256, 0, s, a, b); break;
+        case 3: hipLaunchKernelGGL((k_rprop_team<64, 512, 256>), g, 256, 0, s, a, b); break;
+        default: hipLaunchKernelGGL((k_rprop_team<256, 4096, 256>), g, 256, 0, s, a, b); break;
+      }
+    }
+  }
+  if (a.qend > a.qbeg) {  // every hub has edge chunks
+    hipLaunchKernelGGL(k_rhub_gather, (int)(a.qend - a.qbeg), 256, 0, s, a);
+    hipLaunchKernelGGL(k_rhub_score_final, (int)(a.gend - a.gbeg), 256, 0, s, a);
   }
 }
 

@@ -166,8 +166,8 @@ void check_offsets(const int64_t *off, int64_t n, int64_t nnz, int32_t *err, hip
   hipLaunchKernelGGL(k_check_offsets, flat_grid(n > 0 ? n : 1), 256, 0, s, off, n, nnz, err);
 }
 
-// Rows must be strictly ascending (sorted, no duplicate entries), ids in
-// range, weights finite and > 0.  Chunked over positions.
+// Ids in range, weights finite and > 0 (else bit 1 of *err); rows strictly
+// ascending: sorted, no duplicate entries (else bit 2).  Chunked over positions.
 __global__ __launch_bounds__(256) void k_check_rows(const int64_t *off, const int32_t *idx, const float *w,
                                                     int64_t n, int64_t nnz, const int32_t *crow,
                                                     int32_t *err) {
@@ -181,9 +181,10 @@ __global__ __launch_bounds__(256) void k_check_rows(const int64_t *off, const in
     const int r = rowof[t];
     const int j = idx[q];
     const float x = w[q];
-    bool bad = j < 0 || (int64_t)j >= n || !(x > 0.0f) || !isfinite(x);
-    if (q > off[r] && idx[q - 1] >= j) bad = true;
-    if (bad) atomicOr(err, 1);
+    if (j < 0 || (int64_t)j >= n || !(x > 0.0f) || !isfinite(x)) atomicOr(err, 1);
+    const bool unsorted = q > off[r] && idx[q - 1] >= j;
+    // one add a wavefront: rows out of order are ordinary input
+    if (__ballot(unsorted) && unsorted && __ffsll(__ballot(unsorted)) - 1 == lane()) atomicOr(err, 2);
   }
 }
 void check_rows_chunked(const int64_t *off, const int32_t *idx, const float *w, int64_t n, int64_t nnz,

@@ -3,6 +3,8 @@
 // the driver checks hipGetLastError after each phase.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <stdint.h>
 #include <stddef.h>
 
@@ -81,7 +83,8 @@ size_t sort_pairs_u64_f64(void *temp, size_t tbytes, const unsigned long long *k
                           hipStream_t s);
 size_t seg_sort_i32_f32(void *temp, size_t tbytes, const int32_t *kin, int32_t *kout,
                         const float *vin, float *vout, int64_t nnz, int64_t nseg,
-                        const int64_t *off, hipStream_t s);
+                        const int64_t *off, const int32_t *crow,
+                        hipStream_t s);
 
 constexpr int kPT = 256;                  // threads of a primitive workgroup
 constexpr int kPR = 16;                   // rounds of kPT items per tile
@@ -150,6 +153,23 @@ constexpr int kWideAll = 256;
 // workgroups a CU holds, not by the chain of launches, and get launches with
 // the LDS that each kind needs (hubs of at most kSmallHubDeg edges: 12 KB).
 constexpr int kShareLaunch = 768;
+// Workgroups of a launch that serves several degree buckets of a slice:
+// bucket b has [first[b], first[b + 1]).
+struct BucketSpan {
+  int first[kNB];
+};
+// For the degree buckets (hubs left out) of a slice whose lists lie at
+// region[0..kNB]: a group of 4, 8, 32 or 64 lanes, or a workgroup, a vertex.
+inline BucketSpan bucket_span(const int64_t *region) {
+  constexpr int kPer[kNB - 1] = {64, 32, 8, 4, 1};
+  BucketSpan sp;
+  sp.first[0] = 0;
+  for (int b = 0; b + 1 < kNB; ++b) {
+    const int64_t g = (region[b + 1] - region[b] + kPer[b] - 1) / kPer[b];
+    sp.first[b + 1] = sp.first[b] + (int)std::min<int64_t>(g, kPer[b] == 1 ? 2048 : 4096);
+  }
+  return sp;
+}
 constexpr int64_t kSmallHubDeg = 512;
 constexpr int kHubEC = 512;        // edges per gather workgroup
 constexpr int kHubSeg = 4096;      // table slots per scoring workgroup
@@ -241,9 +261,7 @@ void hub_rel(int64_t *htab, int64_t nhub, const int32_t *hub_soff, int S, const 
 void gather_bounds(const int64_t *arr, const int32_t *at, int count, int64_t *out, hipStream_t s);
 // region_h: host copy of the region starts of this level.
 void move_frontier(const MoveArgs &a, hipStream_t s);
-void move_propose(const MoveArgs &a, const int64_t *region_h, hipStream_t s);
-void move_propose_bucket(const MoveArgs &a, const int64_t *region_h, int b, hipStream_t s);
-void move_apply_bucket(const MoveArgs &a, const int64_t *region_h, int b, hipStream_t s);
+void move_propose(const MoveArgs &a, const int64_t *region_h, hipStream_t s);  // all buckets but the hubs
 // the two halves of bucket kNB-1 (hubs): chunk gather, then segment scoring + final argmax
 void move_hub_gather(const MoveArgs &a, hipStream_t s);
 void move_hub_score(const MoveArgs &a, hipStream_t s);
@@ -295,7 +313,6 @@ struct RefineArgs {
   int64_t hubdeg;
 };
 void refine_break(const RefineArgs &a, hipStream_t s);
-void refine_propose_bucket(const RefineArgs &a, const int64_t *region_h, int b, hipStream_t s);
 void refine_propose(const RefineArgs &a, const int64_t *region_h, hipStream_t s);
 void refine_accept(const RefineArgs &a, const int64_t *region_h, hipStream_t s);
 // Asynchronous mode: the hub candidates of the slice, proposed and accepted.

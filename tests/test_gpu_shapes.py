@@ -175,3 +175,44 @@ def test_fleet_of_more_jobs_than_wide_workgroups():
         res, _ = fl.run([(k, "static", None) for k in range(count)])
         assert all(np.array_equal(to_np(r[0]), refs[k % 3]) for k, r in enumerate(res)), count
     fl.close()
+
+
+@pytest.mark.parametrize("nslices,n,mult", [(1, 6000, 24), (4, 6000, 24), (64, 6000, 24), (1, 40, 3), (2, 3100, 300)])
+def test_sync_slice_launches(nslices, n, mult):
+    """Synchronous slices whose buckets share a launch and slices with a
+    launch for each (above 768 workgroups), with and without hubs, tiles of
+    the frontier and their remainders: the oracle's synchronous mode."""
+    rng = np.random.default_rng(n + mult)
+    u, v = rng.integers(0, n, n * mult // 2), rng.integers(0, n, n * mult // 2)
+    near = rng.integers(0, 40, n * mult // 2)
+    g = gen.from_edges(n, np.concatenate([u, u]), np.concatenate([v, np.minimum(u // 40 * 40 + near, n - 1)]))
+    g = gen.from_edges(n, np.repeat(np.arange(n), np.diff(g.off)).tolist() + [0] * (n // 2),
+                       g.idx.tolist() + list(range(1, n // 2 + 1)))
+    ref, st = oracle.static(og(g), oracle.make_params(sync=True, nslices=nslices))
+    h = L.leiden_create(*(torch.from_numpy(np.asarray(x)).cuda() for x in (g.off, g.idx, g.w)),
+                        L.leiden_default_params(sync_mode=1, nslices=nslices, hub_degree=512))
+    C, q, stats = L.leiden_static(h)[:3]
+    assert np.array_equal(to_np(C), ref.C)
+    assert stats["move_iters"] == st["move_iters"]
+
+
+@pytest.mark.parametrize("where", ["none", "first", "last", "one"])
+def test_create_sorts_only_what_is_unsorted(where):
+    """Rows given in order are left as they are; one row out of order (the
+    first, the last, one in between of a chunk) sorts them; a repeated entry
+    is refused either way."""
+    g = gen.planted_partition(2048, 32, 0.1, 0.002, seed=2, permute=True)
+    idx, w = g.idx.copy(), np.arange(1, g.idx.size + 1, dtype=np.float32)
+    r = {"none": None, "first": 0, "last": g.n - 1, "one": 1000}[where]
+    if r is not None:
+        a, b = g.off[r], g.off[r + 1]
+        assert b - a > 2
+        idx[a:b], w[a:b] = idx[a:b][::-1], w[a:b][::-1].copy()
+    dev = lambda *xs: [torch.from_numpy(np.asarray(x)).cuda() for x in xs]
+    off2, idx2, w2 = L.leiden_get_graph(L.leiden_create(*dev(g.off, idx, w)))
+    assert np.array_equal(to_np(idx2), g.idx)
+    assert np.array_equal(to_np(w2), np.arange(1, g.idx.size + 1, dtype=np.float32))
+    bad = idx.copy()
+    bad[g.off[7] + 1] = bad[g.off[7]]
+    with pytest.raises(L.LeidenError):
+        L.leiden_create(*dev(g.off, bad, w))
