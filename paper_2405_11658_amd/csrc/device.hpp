@@ -137,6 +137,21 @@ __device__ __forceinline__ int wave_scan(int x, int *tot) {
   return x + (r == 0 ? 0 : r == 1 ? a : r == 2 ? b : c);
 }
 template <int CTRL>
+__device__ __forceinline__ int64_t dpp_move(int64_t x) {
+  const int lo = dpp_move<CTRL>((int)x), hi = dpp_move<CTRL>((int)(x >> 32));
+  return ((int64_t)hi << 32) | (unsigned int)lo;
+}
+__device__ __forceinline__ int64_t wave_scan(int64_t x, int64_t *tot) {
+  x += dpp_move<kDppRowShr1>(x);
+  x += dpp_move<kDppRowShr2>(x);
+  x += dpp_move<kDppRowShr4>(x);
+  x += dpp_move<kDppRowShr8>(x);
+  const int64_t a = lane_value64(x, 15), b = a + lane_value64(x, 31), c = b + lane_value64(x, 47);
+  *tot = c + lane_value64(x, 63);
+  const int r = lane() >> 4;
+  return x + (r == 0 ? 0 : r == 1 ? a : r == 2 ? b : c);
+}
+template <int CTRL>
 __device__ __forceinline__ void dpp_seg_add(double &x, int &f) {
   const double y = dpp_move<CTRL>(x);
   const int yf = dpp_move<CTRL>(f);

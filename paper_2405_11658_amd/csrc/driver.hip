@@ -1147,11 +1147,20 @@ bool batch_pointers_ok(const leiden_batch *batch) {
   return true;
 }
 
-// Validates the batch against G^{t-1} (the handle's graph) and builds G^t,
-// rows sorted, in the handle's spare CSR (t_off, t_idx, t_w); the handle's
-// graph and state are not modified.  Returns |E^t|; b keeps the sorted
-// directed batch for the marking.
-int64_t stage_batch(Ctx &x, leiden_handle *h, const leiden_batch &batch, BatchArgs &b) {
+// Sorts pairs by keys of two ids (high and low word, each < n, or ~0 for a key
+// that comes last) into (sk, sv), which may change places with (k, v).
+template <class V>
+void sort_ids(Ctx &x, int64_t n, int64_t E, unsigned long long *&k, V *&v, unsigned long long *&sk, V *&sv) {
+  const RsSeg g = rs_plain(E);
+  const int low = key_bits((unsigned long long)n);  // every id is below 2^low - 1
+  if (rsort<unsigned long long, V>(k, v, sk, sv, g, 2 * low, x.tmp(rs_tmp_bytes(g.ntiles)), x.s, low)) return;
+  std::swap(k, sk);
+  std::swap(v, sv);
+}
+
+// Validates the batch against G^{t-1} (the handle's graph); b keeps the sorted
+// directed batch for the new graph and the marking.
+void sort_batch(Ctx &x, leiden_handle *h, const leiden_batch &batch, BatchArgs &b) {
   const int64_t n = h->n;
   DevScal *sc = x.scal();
   memset(&b, 0, sizeof(b));
@@ -1187,8 +1196,7 @@ int64_t stage_batch(Ctx &x, leiden_handle *h, const leiden_batch &batch, BatchAr
   batch_build(b, x.s);
   x.launched("batch_build");
   if (E > 0) {
-    size_t tb = sort_pairs_u64_i32(nullptr, 0, b.keys, b.skeys, b.vals, b.svals, E, x.s);
-    sort_pairs_u64_i32(x.tmp(tb), tb, b.keys, b.skeys, b.vals, b.svals, E, x.s);
+    sort_ids(x, n, E, b.keys, b.vals, b.skeys, b.svals);
     x.launched("batch sort");
   }
   batch_dups_rows(b, x.s);
@@ -1204,6 +1212,13 @@ int64_t stage_batch(Ctx &x, leiden_handle *h, const leiden_batch &batch, BatchAr
     if (err & 32) why += " non-positive or non-finite weight;";
     x.invalid("invalid batch:" + why);
   }
+}
+
+// Builds G^t of the sorted batch, rows sorted, in the handle's spare CSR
+// (t_off, t_idx, t_w); the handle's graph and state are not modified.  Returns
+// |E^t|.
+int64_t stage_batch(Ctx &x, leiden_handle *h, BatchArgs &b) {
+  const int64_t n = h->n, E = b.E;
   x.ensure(h->t_off, (size_t)(n + 1) * sizeof(int64_t));
   b.newoff = (int64_t *)h->t_off.p;
   batch_newdeg(b, x.s);
@@ -1271,10 +1286,7 @@ void mark_batch(Ctx &x, leiden_handle *h, int32_t mode, const BatchArgs &b, cons
     x.zero(m.count, 1);
     mark_ds_del(m, x.s);
     mark_ds_keys(m, x.s);
-    if (E > 0) {
-      size_t tb = sort_pairs_u64_f64(nullptr, 0, m.k2, m.k2s, m.v2, m.v2s, E, x.s);
-      sort_pairs_u64_f64(x.tmp(tb), tb, m.k2, m.k2s, m.v2, m.v2s, E, x.s);
-    }
+    if (E > 0) sort_ids(x, n, E, m.k2, m.v2, m.k2s, m.v2s);
     mark_ds_best(m, x.s);
     mark_ds_expand(m, x.s);
   }
@@ -1521,7 +1533,8 @@ leiden_status leiden_update(leiden_handle *h, const leiden_batch *batch, int32_t
     DevScal *sc = x.scal();
     // ---- validate the batch and build G^t in the spare CSR ----
     BatchArgs b;
-    const int64_t nnz_new = stage_batch(x, h, *batch, b);
+    sort_batch(x, h, *batch, b);
+    const int64_t nnz_new = stage_batch(x, h, b);
     const int64_t E = b.E;
     std::swap(h->g_off, h->t_off);
     std::swap(h->g_idx, h->t_idx);
@@ -1618,14 +1631,15 @@ leiden_status leiden_mark_affected(leiden_handle *h, const leiden_batch *batch, 
   return run_handle(h, x, [&] {
     const int64_t n = h->n;
     BatchArgs b;
-    const int64_t nnz_new = stage_batch(x, h, *batch, b);
-    // G^t lives in the spare CSR; the handle's graph and state are untouched
-    const int64_t nch = ceil_div(std::max<int64_t>(nnz_new, 1), kChunk);
-    int32_t *crow = x.get<int32_t>(Q_crow, nch + 2);
-    chunk_start_rows((const int64_t *)h->t_off.p, n, nnz_new, crow, x.s);
-    x.launched("chunk_start_rows");
-    const Level gt{n, nnz_new, (const int64_t *)h->t_off.p, (const int32_t *)h->t_idx.p,
-                   (const float *)h->t_w.p, crow};
+    sort_batch(x, h, *batch, b);
+    // delta-screening alone reads G^t; it lives in the spare CSR, the handle's
+    // graph and state are untouched
+    Level gt{};
+    if (mode == LEIDEN_DS) {
+      gt.nnz = stage_batch(x, h, b);
+      gt.off = (const int64_t *)h->t_off.p;
+      gt.idx = (const int32_t *)h->t_idx.p;
+    }
     uint8_t *dV = x.get<uint8_t>(L_U, n);
     uint8_t *rng = x.get<uint8_t>(L_rng, n);
     uint8_t *dC = x.get<uint8_t>(L_dC, n);

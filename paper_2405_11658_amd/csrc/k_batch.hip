@@ -2,7 +2,7 @@
 //   build/validate: each undirected batch edge becomes two directed entries
 //     keyed (src, dst); a deletion must exist in G^{t-1} (its weight is read
 //     there), an insertion must not; ids, self-loops and weights are checked;
-//   the entries are radix-sorted (rocPRIM) so duplicates are adjacent and
+//   the entries are radix-sorted so duplicates are adjacent and
 //     every row's batch entries form one segment ordered by dst;
 //   apply: the new CSR keeps rows sorted - every surviving old entry and every
 //     insertion gets its merged position from binary searches in the row's

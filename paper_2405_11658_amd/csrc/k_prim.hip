@@ -4,8 +4,8 @@
 // vendor primitive library is used.
 //
 // Scan: tile totals (one workgroup per tile), a scan of the totals (the same
-// routine, recursively), then each tile scans its items in 16 rounds of 256
-// with the tile's prefix as carry.  In-place use (in == out) is allowed.
+// routine, recursively), then each tile scans its items with the tile's prefix
+// as carry, a wavefront 16 rounds of 64.  In-place use (in == out) is allowed.
 //
 // Radix sort: per pass (digits of at most 9 bits) a digit histogram per tile,
 // an exclusive scan of the histograms laid out segment-major, digit-major,
@@ -50,29 +50,58 @@ template <class I, class O>
 __global__ __launch_bounds__(kPT) void k_scan_reduce(const I *in, int64_t n, O *tsum) {
   __shared__ O sw[kPT / kWave];
   const int64_t b = (int64_t)blockIdx.x * kPTile;
-  O s = 0;
-  for (int k = threadIdx.x; k < kPTile; k += kPT) {
-    const int64_t p = b + k;
-    if (p < n) s += (O)in[p];
+  O x[kPR];
+#pragma unroll
+  for (int r = 0; r < kPR; ++r) {
+    const int64_t p = b + r * kPT + threadIdx.x;
+    x[r] = p < n ? (O)in[p] : (O)0;
   }
+  O s = 0;
+#pragma unroll
+  for (int r = 0; r < kPR; ++r) s += x[r];
   O tot;
-  (void)blk_excl<O>(s, &tot, sw);
-  if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
+  (void)wave_scan(s, &tot);
+  if (lane() == 0) sw[threadIdx.x / kWave] = tot;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    tot = 0;
+#pragma unroll
+    for (int w = 0; w < kPT / kWave; ++w) tot += sw[w];
+    tsum[blockIdx.x] = tot;
+  }
 }
 
+// Most scans here are of one tile or a few and lie in a chain of launches: the
+// items are loaded together and the rounds' prefixes taken with lane moves,
+// with one barrier (16 rounds of 256 one after another, two barriers each and
+// the prefix through LDS permutes: 12 us a tile, now 4.5).
 template <class I, class O>
 __global__ __launch_bounds__(kPT) void k_scan_apply(const I *in, O *out, int64_t n, const O *tpre) {
   __shared__ O sw[kPT / kWave];
-  const int64_t b = (int64_t)blockIdx.x * kPTile;
-  O carry = tpre ? tpre[blockIdx.x] : (O)0;
+  const int wv = threadIdx.x / kWave;
+  const int64_t b = (int64_t)blockIdx.x * kPTile + wv * (kPTile / (kPT / kWave));
+  O x[kPR], ex[kPR], tot[kPR], sum = 0;
+#pragma unroll
   for (int r = 0; r < kPR; ++r) {
-    const int64_t p = b + (int64_t)r * kPT + threadIdx.x;
-    if (b + (int64_t)r * kPT >= n) break;  // uniform
-    const O x = p < n ? (O)in[p] : (O)0;
-    O tot;
-    const O ex = blk_excl<O>(x, &tot, sw);
-    if (p < n) out[p] = carry + ex;
-    carry += tot;
+    const int64_t p = b + r * kWave + lane();
+    x[r] = p < n ? (O)in[p] : (O)0;
+  }
+#pragma unroll
+  for (int r = 0; r < kPR; ++r) {
+    ex[r] = wave_scan(x[r], &tot[r]) - x[r];
+    sum += tot[r];
+  }
+  if (lane() == 0) sw[wv] = sum;
+  __syncthreads();
+  O carry = tpre ? tpre[blockIdx.x] : (O)0;
+#pragma unroll
+  for (int w = 0; w < kPT / kWave; ++w)
+    if (w < wv) carry += sw[w];
+#pragma unroll
+  for (int r = 0; r < kPR; ++r) {
+    const int64_t p = b + r * kWave + lane();
+    if (p < n) out[p] = carry + ex[r];
+    carry += tot[r];
   }
 }
 
@@ -123,15 +152,22 @@ constexpr int kRadixBits = 9;            // digits of at most 9 bits
 constexpr int kDig = 1 << kRadixBits;    // 512 digit values
 constexpr int kDPT = kDig / kPT;         // digits per thread
 
+// Sorted are the key's `low` low bits and, above them, its bits from 32 on
+// (keys of two ids of fewer bits each; low = 32: the whole key).
+template <class K>
+__device__ __forceinline__ int rs_digit(K key, int low, int shift, int bits) {
+  if constexpr (sizeof(K) == 8) key = ((key >> 32) << low) | (key & (((K)1 << low) - 1));
+  return (int)((key >> shift) & (K)((1u << bits) - 1u));
+}
+
 // hist: scan layout (segment, digit, tile) over the pass's 2^bits digits.
 template <class K>
-__global__ __launch_bounds__(kPT) void k_rs_hist(const K *keys, RsSeg g, int shift, int bits, int64_t *hist) {
+__global__ __launch_bounds__(kPT) void k_rs_hist(const K *keys, RsSeg g, int low, int shift, int bits, int64_t *hist) {
   __shared__ int h[kDig];
   const int64_t t = blockIdx.x;
   const TileSpan ts = tile_span(g, t);
   for (int d = threadIdx.x; d < kDig; d += kPT) h[d] = 0;
   __syncthreads();
-  const K mask = (K)((1u << bits) - 1u);
   // all of the thread's loads issued together, then the counts
   K kr[kPR];
 #pragma unroll
@@ -141,7 +177,7 @@ __global__ __launch_bounds__(kPT) void k_rs_hist(const K *keys, RsSeg g, int shi
   }
 #pragma unroll
   for (int r = 0; r < kPR; ++r)
-    if (ts.lo + r * kPT + threadIdx.x < ts.hi) atomicAdd(&h[(int)((kr[r] >> shift) & mask)], 1);
+    if (ts.lo + r * kPT + threadIdx.x < ts.hi) atomicAdd(&h[rs_digit(kr[r], low, shift, bits)], 1);
   __syncthreads();
   const int nd = 1 << bits;
   for (int d = threadIdx.x; d < nd; d += kPT) hist[nd * ts.f0 + (int64_t)d * ts.nt + (t - ts.f0)] = h[d];
@@ -149,15 +185,16 @@ __global__ __launch_bounds__(kPT) void k_rs_hist(const K *keys, RsSeg g, int shi
 
 // Each tile ranks its items stably by digit into a local digit-sorted copy in
 // LDS, then writes it out in order: the items of one digit go to consecutive
-// places, so consecutive threads write consecutive addresses.  Each
+// places, so consecutive threads write consecutive addresses.  hs: the scanned
+// histograms (null: the sort is of this one tile, whose order is final).  Each
 // wavefront ranks its own contiguous quarter of the tile (16 rounds of 64
 // items, in order) against digit counters that only it uses, so the rounds
 // need no workgroup barrier; one prefix over the digits and the four
 // wavefronts' counts then gives every item its place.  Items are ordered by
 // (wavefront, round, lane), which is their order in the tile: stable.
 template <class K, class V>
-__global__ __launch_bounds__(kPT) void k_rs_scatter(const K *ki, const V *vi, K *ko, V *vo, RsSeg g, int shift,
-                                                    int bits, const int64_t *hs) {
+__global__ __launch_bounds__(kPT) void k_rs_scatter(const K *ki, const V *vi, K *ko, V *vo, RsSeg g, int low,
+                                                    int shift, int bits, const int64_t *hs) {
   constexpr int W = kPT / kWave;
   constexpr int QW = kPTile / W;  // items per wavefront
   __shared__ K sk[kPTile];
@@ -168,7 +205,7 @@ __global__ __launch_bounds__(kPT) void k_rs_scatter(const K *ki, const V *vi, K 
   const int64_t t = blockIdx.x;
   const TileSpan ts = tile_span(g, t);
   const int nd = 1 << bits;
-  const int64_t seg0 = hs[nd * ts.f0];
+  const int64_t seg0 = hs ? hs[nd * ts.f0] : 0;
   const int wid = (int)threadIdx.x / kWave;
   for (int d = threadIdx.x; d < kDig; d += kPT) {
 #pragma unroll
@@ -189,14 +226,13 @@ __global__ __launch_bounds__(kPT) void k_rs_scatter(const K *ki, const V *vi, K 
     }
   }
   __syncthreads();  // counters cleared
-  const K mask = (K)((1u << bits) - 1u);
   const unsigned long long below = lane() == 0 ? 0ull : (~0ull >> (64 - lane()));
   int rk[kPR];
 #pragma unroll
   for (int r = 0; r < kPR; ++r) {
     const int64_t p = q0 + r * kWave + lane();
     const bool act = p < ts.hi;
-    const int dg = act ? (int)((kr[r] >> shift) & mask) : 0;
+    const int dg = act ? rs_digit(kr[r], low, shift, bits) : 0;
     unsigned long long same = __ballot(act);
     for (int bit = 0; bit < bits; ++bit) {
       const unsigned long long on = __ballot(act && ((dg >> bit) & 1));
@@ -230,7 +266,7 @@ __global__ __launch_bounds__(kPT) void k_rs_scatter(const K *ki, const V *vi, K 
 #pragma unroll
     for (int k = 0; k < kDPT; ++k) {
       const int d = threadIdx.x * kDPT + k;
-      if (d < nd) gbase[d] = ts.sb + (hs[nd * ts.f0 + (int64_t)d * ts.nt + (t - ts.f0)] - seg0) - pre;
+      if (d < nd) gbase[d] = ts.sb + (hs ? hs[nd * ts.f0 + (int64_t)d * ts.nt + (t - ts.f0)] - seg0 - pre : 0);
 #pragma unroll
       for (int w = 0; w < W; ++w) {
         cnt[w][d] = pre;
@@ -243,7 +279,7 @@ __global__ __launch_bounds__(kPT) void k_rs_scatter(const K *ki, const V *vi, K 
   for (int r = 0; r < kPR; ++r) {
     const int64_t p = q0 + r * kWave + lane();
     if (p < ts.hi) {
-      const int dg = (int)((kr[r] >> shift) & mask);
+      const int dg = rs_digit(kr[r], low, shift, bits);
       const int q = cnt[wid][dg] + rk[r];
       sk[q] = kr[r];
       sv[q] = vr[r];
@@ -253,7 +289,7 @@ __global__ __launch_bounds__(kPT) void k_rs_scatter(const K *ki, const V *vi, K 
   const int m = (int)(ts.hi - ts.lo);
   for (int j = threadIdx.x; j < m; j += kPT) {
     const K key = sk[j];
-    const int dg = (int)((key >> shift) & mask);
+    const int dg = rs_digit(key, low, shift, bits);
     const int64_t q = gbase[dg] + j;
     ko[q] = key;
     vo[q] = sv[j];
@@ -268,7 +304,7 @@ size_t rs_tmp_bytes(int64_t ntiles) {
 }
 
 template <class K, class V>
-int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipStream_t s) {
+int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipStream_t s, int low) {
   const int np = rs_passes(bits);
   if (np == 0 || g.ntiles <= 0) return 0;
   const int wd = (bits + np - 1) / np;
@@ -280,11 +316,13 @@ int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipSt
   int shift = 0;
   for (int p = 0; p < np; ++p) {
     const int b = std::min(wd, bits - shift);
-    const int64_t nh = ((int64_t)1 << b) * g.ntiles;
-    hipLaunchKernelGGL((k_rs_hist<K>), (int)g.ntiles, kPT, 0, s, (const K *)ks, g, shift, b, hist);
-    scan_rec<int64_t, int64_t>(hist, hist, nh, stmp, s);
+    const bool one = g.ntiles == 1;
+    if (!one) {
+      hipLaunchKernelGGL((k_rs_hist<K>), (int)g.ntiles, kPT, 0, s, (const K *)ks, g, low, shift, b, hist);
+      scan_rec<int64_t, int64_t>(hist, hist, ((int64_t)1 << b) * g.ntiles, stmp, s);
+    }
     hipLaunchKernelGGL((k_rs_scatter<K, V>), (int)g.ntiles, kPT, 0, s, (const K *)ks, (const V *)vs, kd, vd, g,
-                       shift, b, (const int64_t *)hist);
+                       low, shift, b, one ? (const int64_t *)nullptr : (const int64_t *)hist);
     std::swap(ks, kd);
     std::swap(vs, vd);
     shift += b;
@@ -293,9 +331,9 @@ int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipSt
 }
 
 template int rsort<uint32_t, int32_t>(uint32_t *, int32_t *, uint32_t *, int32_t *, const RsSeg &, int, void *,
-                                      hipStream_t);
+                                      hipStream_t, int);
 template int rsort<uint32_t, float>(uint32_t *, float *, uint32_t *, float *, const RsSeg &, int, void *,
-                                    hipStream_t);
+                                    hipStream_t, int);
 
 RsSeg rs_plain(int64_t n) {
   RsSeg g;
@@ -314,43 +352,12 @@ int key_bits(unsigned long long x) {
   return b;
 }
 
-// Sorted copies (kout, vout) of (kin, vin) by the low `bits` key bits.  The
-// temporary area holds the second key / value buffers, the histograms and the
-// scan space.
-template <class K, class V>
-static size_t sort_copy(void *temp, size_t tbytes, const K *kin, K *kout, const V *vin, V *vout, int64_t n,
-                        int bits, hipStream_t s) {
-  const RsSeg g = rs_plain(n);
-  const size_t kb = ((size_t)std::max<int64_t>(n, 1) * sizeof(K) + 255) & ~(size_t)255;
-  const size_t vb = ((size_t)std::max<int64_t>(n, 1) * sizeof(V) + 255) & ~(size_t)255;
-  const size_t need = kb + vb + rs_tmp_bytes(g.ntiles);
-  if (!temp || tbytes < need || n <= 0) return need;
-  char *t = (char *)temp;
-  K *tk = (K *)t;
-  V *tv = (V *)(t + kb);
-  // an odd number of passes ends in the second buffers: start there
-  const bool odd = rs_passes(bits) & 1;
-  (void)hipMemcpyAsync(odd ? tk : kout, kin, sizeof(K) * n, hipMemcpyDeviceToDevice, s);
-  (void)hipMemcpyAsync(odd ? tv : vout, vin, sizeof(V) * n, hipMemcpyDeviceToDevice, s);
-  if (odd) rsort<K, V>(tk, tv, kout, vout, g, bits, t + kb + vb, s);
-  else rsort<K, V>(kout, vout, tk, tv, g, bits, t + kb + vb, s);
-  return need;
-}
 template int rsort<unsigned long long, int32_t>(unsigned long long *, int32_t *, unsigned long long *, int32_t *,
-                                                 const RsSeg &, int, void *, hipStream_t);
+                                                 const RsSeg &, int, void *, hipStream_t, int);
 template int rsort<unsigned long long, double>(unsigned long long *, double *, unsigned long long *, double *,
-                                                const RsSeg &, int, void *, hipStream_t);
+                                                const RsSeg &, int, void *, hipStream_t, int);
 template int rsort<unsigned long long, float>(unsigned long long *, float *, unsigned long long *, float *,
-                                               const RsSeg &, int, void *, hipStream_t);
-
-size_t sort_pairs_u64_i32(void *temp, size_t tbytes, const unsigned long long *kin, unsigned long long *kout,
-                          const int32_t *vin, int32_t *vout, int64_t n, hipStream_t s) {
-  return sort_copy<unsigned long long, int32_t>(temp, tbytes, kin, kout, vin, vout, n, 64, s);
-}
-size_t sort_pairs_u64_f64(void *temp, size_t tbytes, const unsigned long long *kin, unsigned long long *kout,
-                          const double *vin, double *vout, int64_t n, hipStream_t s) {
-  return sort_copy<unsigned long long, double>(temp, tbytes, kin, kout, vin, vout, n, 64, s);
-}
+                                               const RsSeg &, int, void *, hipStream_t, int);
 
 // Rows sorted by column id: (row << 32 | column) keys over the bits in use.
 // By chunks of positions: with a row a thread, the longest row's thread was the
@@ -380,11 +387,11 @@ size_t seg_sort_i32_f32(void *temp, size_t tbytes, const int32_t *kin, int32_t *
   unsigned long long *k0 = (unsigned long long *)t, *k1 = (unsigned long long *)(t + kb);
   float *v1 = (float *)(t + 2 * kb);
   hipLaunchKernelGGL(k_row_keys, (int)ceil_div(nnz, (int64_t)kChunk), 256, 0, s, off, nnz, crow, kin, k0);
-  const int bits = 32 + key_bits((unsigned long long)std::max<int64_t>(nseg - 1, 0));
+  const int low = key_bits((unsigned long long)std::max<int64_t>(nseg - 1, 0)), bits = 2 * low;
   const bool odd = rs_passes(bits) & 1;  // values end in vout either way
   (void)hipMemcpyAsync(odd ? v1 : vout, vin, sizeof(float) * nnz, hipMemcpyDeviceToDevice, s);
-  const int r = odd ? rsort<unsigned long long, float>(k0, v1, k1, vout, g, bits, t + 2 * kb + vb, s)
-                    : rsort<unsigned long long, float>(k0, vout, k1, v1, g, bits, t + 2 * kb + vb, s);
+  const int r = odd ? rsort<unsigned long long, float>(k0, v1, k1, vout, g, bits, t + 2 * kb + vb, s, low)
+                    : rsort<unsigned long long, float>(k0, vout, k1, v1, g, bits, t + 2 * kb + vb, s, low);
   hipLaunchKernelGGL(k_low_words, flat_grid(nnz), 256, 0, s, r ? k1 : k0, nnz, kout);
   return need;
 }

@@ -75,12 +75,6 @@ size_t scan_excl_i32_to_i64(void *temp, size_t tbytes, const int32_t *in, int64_
                             hipStream_t s);
 void reset_iter(int32_t *counts, int n, double *d0, unsigned long long *u0, unsigned long long *u1,
                 hipStream_t s);
-size_t sort_pairs_u64_i32(void *temp, size_t tbytes, const unsigned long long *kin,
-                          unsigned long long *kout, const int32_t *vin, int32_t *vout, int64_t n,
-                          hipStream_t s);
-size_t sort_pairs_u64_f64(void *temp, size_t tbytes, const unsigned long long *kin,
-                          unsigned long long *kout, const double *vin, double *vout, int64_t n,
-                          hipStream_t s);
 size_t seg_sort_i32_f32(void *temp, size_t tbytes, const int32_t *kin, int32_t *kout,
                         const float *vin, float *vout, int64_t nnz, int64_t nseg,
                         const int64_t *off, const int32_t *crow,
@@ -128,11 +122,12 @@ int rs_passes(int bits);
 size_t rs_tmp_bytes(int64_t ntiles);
 int key_bits(unsigned long long x);  // bits needed for x (0 for 0)
 // Stable sort of every segment by the low `bits` key bits (rs_passes(bits)
-// passes); (k1, v1) are second buffers covering the same items.  Returns 0 if
+// passes; 64-bit keys: the bits [low, 32) are left out); (k1, v1) are second buffers covering the same items.  Returns 0 if
 // the result is in (k0, v0), 1 if in (k1, v1) (odd pass count).  tmp:
 // rs_tmp_bytes(g.ntiles) bytes.
 template <class K, class V>
-int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipStream_t s);
+int rsort(K *k0, V *v0, K *k1, V *v1, const RsSeg &g, int bits, void *tmp, hipStream_t s,
+          int low = 32);
 
 // ---- k_move.hip -------------------------------------------------------------
 // Hub plan of a level: the vertices of the largest degree bucket grouped by

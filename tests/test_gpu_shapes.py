@@ -216,3 +216,37 @@ def test_create_sorts_only_what_is_unsorted(where):
     bad[g.off[7] + 1] = bad[g.off[7]]
     with pytest.raises(L.LeidenError):
         L.leiden_create(*dev(g.off, bad, w))
+
+
+@pytest.mark.parametrize("n,batch", [(2, 1), (3, 1), (255, 20), (256, 20), (257, 20), (512, 40), (1024, 1023),
+                                     (1024, 1024), (1025, 1025), (4096, 3000)])
+@pytest.mark.parametrize("mode", ["df", "ds", "nd"])
+def test_batch_sort_bits_and_tiles(n, batch, mode):
+    """Batches sorted by the bits that the ids use (n at and beside powers of
+    two, the last vertex and community among them) in one tile of 4096 entries
+    and in several: marking and the new graph against the oracle."""
+    rng = np.random.default_rng(n)
+    k = 4 * n if n > 3 else 0
+    g = gen.from_edges(n, np.concatenate([np.arange(n - 1), rng.integers(0, n, k)]),
+                       np.concatenate([np.arange(1, n), rng.integers(0, n, k)]))
+    b = gen.random_batch(g, batch, seed=n, ins_frac=0.8 if n > 3 else 0.0)
+    dev = [torch.from_numpy(np.asarray(x)).cuda() for x in (g.off, g.idx, g.w)]
+    h = L.leiden_create(*dev, L.leiden_default_params(sync_mode=1))
+    # singleton communities: community n - 1 is in use
+    C = np.arange(n, dtype=np.int32)
+    L.leiden_set_state(h, torch.from_numpy(C).cuda())
+    K = np.bincount(np.repeat(C, np.diff(g.off)), weights=g.w.astype(np.float64), minlength=n)
+    gt, _ = oracle.apply_batch(og(g), ob(b))
+    want = oracle.mark(mode, gt, ob(b), C, K, K, float(K.sum()))
+    got = L.leiden_mark_affected(h, dev_batch(b), mode)
+    for x, y in zip((got["affected"], got["in_range"], got["changed"]), want):
+        assert np.array_equal(to_np(x), y[:n])
+    # marking has left the graph; a batch that is no batch is refused in every mode
+    assert np.array_equal(to_np(L.leiden_get_graph(h)[1]), g.idx)
+    for u, v in ((0, n), (-1, 1), (n - 1, n - 1)):
+        with pytest.raises(L.LeidenError):
+            L.leiden_mark_affected(h, L.make_batch([], [], [u], [v], [1.0]), mode)
+    res = L.leiden_update(h, dev_batch(b), mode)
+    off, idx, w = L.leiden_get_graph(h)
+    assert np.array_equal(to_np(off), gt.off) and np.array_equal(to_np(idx), gt.idx)
+    assert np.array_equal(to_np(w), gt.w) and res[2]["affected"] == int(want[0].sum())
