@@ -250,3 +250,26 @@ def test_batch_sort_bits_and_tiles(n, batch, mode):
     off, idx, w = L.leiden_get_graph(h)
     assert np.array_equal(to_np(off), gt.off) and np.array_equal(to_np(idx), gt.idx)
     assert np.array_equal(to_np(w), gt.w) and res[2]["affected"] == int(want[0].sum())
+
+
+@pytest.mark.parametrize("n,nlab,mult", [(5, 5, 1), (700, 3, 40), (40000, 40000, 1), (300000, 200000, 4),
+                                         (300000, 5, 4)])
+def test_modularity_merge_table(n, nlab, mult):
+    """Sums by community merged per workgroup: tables that never fill, that
+    fill in every chunk, rows longer than a chunk; weights that are sums of
+    powers of two, so Eq. 1 follows from exact sums (each of its terms rounded
+    once or twice: 4 ulp of 1 a community, added pairwise)."""
+    rng = np.random.default_rng(n + nlab)
+    u, v = rng.integers(0, n, n * mult), rng.integers(0, n, n * mult)
+    if n == 300000:
+        u[:5000] = 7  # a row of several chunks
+    g = gen.from_edges(n, np.append(u, 0), np.append(v, 1))
+    lab = rng.integers(0, nlab, n).astype(np.int32)
+    row = np.repeat(np.arange(n), np.diff(g.off))
+    w = (1.0 + ((row + g.idx) % 4)).astype(np.float32)
+    inside = float(w[lab[row] == lab[g.idx]].sum(dtype=np.float64))
+    S = np.bincount(lab[row], weights=w.astype(np.float64), minlength=n)
+    m2 = float(S.sum())
+    want = inside / m2 - float(np.sum((S / m2) ** 2))
+    got = L.leiden_modularity(*(torch.from_numpy(np.asarray(x)).cuda() for x in (g.off, g.idx, w, lab)))
+    assert abs(got - want) <= 4 * np.finfo(np.float64).eps * (1 + np.log2(n))
