@@ -422,19 +422,19 @@ struct Layout {
   int64_t nhub;
 };
 
-Layout level_layout(Ctx &x, const Level &g, int S, int64_t hubdeg, int32_t *region_dev, int32_t *counts_tmp,
-                    int32_t *scnt,
+// counts: S*kNB bucket counts, then S slice counts; the grouping by slice
+// (vbyslice) is the synchronous mode's.
+constexpr size_t kPinLayout = 32768;  // staging of the layout's upload, beside that of small reads
+Layout level_layout(Ctx &x, const Level &g, int S, int64_t hubdeg, bool async, int32_t *region_dev, int32_t *counts,
                     int32_t *soff_dev, int32_t *sfill, int32_t *vbyslice) {
   Layout L;
   L.S = S;
   const int nb = S * kNB;
-  x.zero(counts_tmp, nb);
-  x.zero(scnt, S);
-  slice_hist(g.off, g.n, S, hubdeg, counts_tmp, scnt, x.s);
+  x.zero(counts, nb + S);
+  slice_hist(g.off, g.n, S, hubdeg, counts, counts + nb, x.s);
   x.launched("slice_hist");
   int32_t *hp = (int32_t *)x.pin();
-  x.check(hipMemcpyAsync(hp, counts_tmp, sizeof(int32_t) * nb, hipMemcpyDeviceToHost, x.s), "D2H");
-  x.check(hipMemcpyAsync(hp + nb, scnt, sizeof(int32_t) * S, hipMemcpyDeviceToHost, x.s), "D2H");
+  x.check(hipMemcpyAsync(hp, counts, sizeof(int32_t) * (nb + S), hipMemcpyDeviceToHost, x.s), "D2H");
   x.check(hipStreamSynchronize(x.s), "sync");
   L.region.assign(nb + 1, 0);
   L.soff.assign(S + 1, 0);
@@ -442,15 +442,17 @@ Layout level_layout(Ctx &x, const Level &g, int S, int64_t hubdeg, int32_t *regi
   for (int k = 0; k < S; ++k) L.soff[k + 1] = L.soff[k] + hp[nb + k];
   L.nhub = 0;
   for (int s = 0; s < S; ++s) L.nhub += hp[s * kNB + kNB - 1];
-  int32_t *up = hp + nb + S;
+  // the upload has a part of the staging block of its own: the next layout,
+  // which writes it again, waits for its own counts first
+  int32_t *up = (int32_t *)((char *)x.pin() + kPinLayout);
   for (int k = 0; k <= nb; ++k) up[k] = (int32_t)L.region[k];
-  for (int k = 0; k <= S; ++k) up[nb + 1 + k] = (int32_t)L.soff[k];
   x.check(hipMemcpyAsync(region_dev, up, sizeof(int32_t) * (nb + 1), hipMemcpyHostToDevice, x.s), "H2D");
+  if (async) return L;
+  for (int k = 0; k <= S; ++k) up[nb + 1 + k] = (int32_t)L.soff[k];
   x.check(hipMemcpyAsync(soff_dev, up + nb + 1, sizeof(int32_t) * (S + 1), hipMemcpyHostToDevice, x.s), "H2D");
   x.zero(sfill, S);
   slice_scatter(g.n, S, soff_dev, sfill, vbyslice, x.s);
   x.launched("slice_scatter");
-  x.check(hipStreamSynchronize(x.s), "sync");  // the pinned staging area is reused
   return L;
 }
 
@@ -794,7 +796,6 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
   int32_t *lists = x.get<int32_t>(L_lists, n);
   int32_t *region = x.get<int32_t>(L_region, NS * kNB + 1);
   int32_t *counts = x.get<int32_t>(L_scnt, NS * kNB + NS);
-  int32_t *scnt = counts + NS * kNB;
   int32_t *vbs = x.get<int32_t>(L_vbs, n);
   int32_t *soff = x.get<int32_t>(L_soff, NS + 1);
   int32_t *sfill = x.get<int32_t>(L_sfill, NS);
@@ -838,20 +839,23 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     tm.pass = pass;
     const int64_t nl = g.n;
     const int64_t nfull = nl + niso;
-    const Layout B = level_layout(x, g, NS, hubdeg, region, counts, scnt, soff, sfill, vbs);
+    const Layout B = level_layout(x, g, NS, hubdeg, async, region, counts, soff, sfill, vbs);
     const HubHost hh = hub_plan(x, g, NS, hubdeg, async, B);
     const int64_t alen = B.region[NS * kNB];  // vertices with edges
     int32_t *alist = nullptr;
     if (async && alen > 0) {
-      int32_t *flags = x.get<int32_t>(L_flags, nl + 1);
-      int32_t *pos = x.get<int32_t>(L_map, nl + 1);
       alist = x.get<int32_t>(W_list, alen);
-      edge_flags(g.off, nl, flags, x.s);
-      scan_i32(x, flags, pos, nl);
-      edge_list(g.off, nl, pos, alist, x.s);
+      if (alen == nl) {
+        iota_i32(alist, nl, x.s);
+      } else {
+        int32_t *flags = x.get<int32_t>(L_flags, nl + 1);
+        int32_t *pos = x.get<int32_t>(L_map, nl + 1);
+        edge_flags(g.off, nl, flags, x.s);
+        scan_i32(x, flags, pos, nl);
+        edge_list(g.off, nl, pos, alist, x.s);
+      }
       x.launched("edge list");
     }
-    if (pass > 0) fill_u8(rng, 1, nl, x.s);
     const double Tp = tau * M2 * M2 / 2.0;
 
     MoveArgs ma;
@@ -1060,10 +1064,7 @@ void run_core(Ctx &x, const leiden_params &p, const Level &g0, double M2, bool t
     }
     if (l1 && pass == 0) l1->g = g;
     tm.mark(CAT_AGG);
-    x.copy(S, K, nact);
-    fill_u8(U, 1, nact, x.s);
-    iota_i32(C, nact, x.s);
-    fill_u8(dC, 1, nact, x.s);
+    pass_reset(nact, K, S, C, U, dC, rng, x.s);
     x.launched("pass reset");
     tau = tau / p.tol_drop;
   }

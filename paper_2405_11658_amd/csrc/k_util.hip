@@ -33,6 +33,22 @@ void iota_i32(int32_t *p, int64_t n, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(k_iota, flat_grid(n), 256, 0, s, p, n);
 }
 
+// State of an aggregated level: every vertex alone, unprocessed and in range.
+__global__ void k_pass_reset(int64_t n, const double *K, double *Sig, int32_t *C, uint8_t *U, uint8_t *dC,
+                             uint8_t *rng) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    Sig[i] = K[i];
+    C[i] = (int32_t)i;
+    U[i] = 1;
+    dC[i] = 1;
+    rng[i] = 1;
+  }
+}
+void pass_reset(int64_t n, const double *K, double *Sig, int32_t *C, uint8_t *U, uint8_t *dC, uint8_t *rng,
+                hipStream_t s) {
+  if (n > 0) hipLaunchKernelGGL(k_pass_reset, flat_grid(n), 256, 0, s, n, K, Sig, C, U, dC, rng);
+}
+
 __global__ void k_chunk_start_rows(const int64_t *off, int64_t nrows, int64_t nnz, int32_t *out) {
   const int64_t nchunks = ceil_div(nnz, kChunk);
   if (blockIdx.x == 0 && threadIdx.x == 0) out[nchunks] = (int32_t)(nrows > 0 ? nrows - 1 : 0);

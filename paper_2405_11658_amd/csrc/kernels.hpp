@@ -40,6 +40,8 @@ void fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s);
 void fill_f64(double *p, double v, int64_t n, hipStream_t s);
 void fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t s);
 void iota_i32(int32_t *p, int64_t n, hipStream_t s);
+void pass_reset(int64_t n, const double *K, double *Sig, int32_t *C, uint8_t *U, uint8_t *dC, uint8_t *rng,
+                hipStream_t s);
 // out[b] = row owning position b*kChunk (b < nchunks); out[nchunks] = nrows-1.
 void chunk_start_rows(const int64_t *off, int64_t nrows, int64_t nnz, int32_t *out, hipStream_t s);
 // K[r] = sum of w over row r (FP64); K must be zeroed.
