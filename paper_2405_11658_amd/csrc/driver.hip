@@ -1097,11 +1097,14 @@ leiden_status run_guarded(Workspace &w, const std::function<void()> &f) {
 
 // A stateless call keeps its working memory for the next one (ScratchCache).
 leiden_status run_stateless(Workspace &w, hipStream_t s, const std::function<void()> &f) {
-  w.al.scratch = true;
+  // (a stream under capture is refused below, at the call's first wait)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  w.al.scratch = cap == hipStreamCaptureStatusNone;
   w.al.dev = stream_device(s);
   const leiden_status st = run_guarded(w, f);
   w.release(s);
-  w.al.end(s);
+  if (w.al.scratch) w.al.end(s);
   return st;
 }
 
