@@ -433,10 +433,13 @@ __device__ __forceinline__ void best_move(const WaveTable &t, double M2, int d, 
 // so that their atomics wait for memory together.  (One wavefront alone
 // follows the serial sweep exactly: one vertex at a time.)  On a level of 4096
 // vertices and 4 wavefronts: refinement 2.7 -> 0.9 us a vertex (1.25 with
-// groups of 1, 0.98 of 8), local moving 1.1 -> 0.6 us; 4096 wavefronts end at
-// the rate of their random reads, ~45e9 a second.  The modularity is that of
-// single vertices (R-MAT scale 22, ten updates: 0.0703 and 0.0705, sd 1e-4).
-constexpr int kGroup = 4;
+// groups of 1, 0.98 of 8), local moving 1.1 -> 0.6 us, both in groups of 4;
+// 4096 wavefronts end at the rate of their random reads, ~45e9 a second.  The
+// modularity is that of single vertices (R-MAT scale 22, ten updates: 0.0703
+// and 0.0705, sd 1e-4) also where a batch changes a tenth of the edges (R-MAT
+// scale 20: 0.127 to 0.128, sd 0.0015 to 0.0018, for groups of 1 and 2); there
+// groups of 4 ended below 0.115 in 9 of 144 runs, of 1 and 2 in none of 96.
+constexpr int kGroup = 2;
 
 // A wavefront takes kGrabChunks chunks of kAsyncChunk list positions at a
 // time from the global counter (one atomic per 256 vertices: every wavefront
