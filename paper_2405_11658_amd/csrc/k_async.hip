@@ -18,11 +18,11 @@
 // Refinement follows the same scheme: an isolated vertex of a changed bound
 // (Sigma of its community equal to its own K) looks for the best community
 // inside its bound, claims its own community with a compare-and-swap of
-// Sigma from K_i to 0, and joins the target if the target's representative
-// still holds its label (checked only while the target may still be a
-// singleton).
+// Sigma from K_i to 0, and joins the target: with another compare-and-swap
+// while the target may still be a singleton (refine_join.hpp).
 #include "device.hpp"
 #include "kernels.hpp"
+#include "refine_join.hpp"
 #include "wave_move.hpp"
 
 namespace lk {
@@ -726,6 +726,21 @@ void move_async(const MoveArgs &a, int waves, bool wide, hipStream_t s) {
 
 constexpr int kRefineTries = 4;  // evaluations of a refinement candidate whose target emptied
 
+// The community totals as join_singleton works on them.
+struct SigmaMem {
+  double *Sig;
+  __device__ __forceinline__ double load(int c) const { return ld_dbl(&Sig[c]); }
+  __device__ __forceinline__ double swap(int c, double from, double to) const {
+    return __longlong_as_double((long long)atomicCAS((unsigned long long *)&Sig[c],
+                                                     (unsigned long long)__double_as_longlong(from),
+                                                     (unsigned long long)__double_as_longlong(to)));
+  }
+  __device__ __forceinline__ void store(int c, double x) const {
+    __hip_atomic_store(&Sig[c], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void add(int c, double x) const { unsafeAtomicAdd(&Sig[c], x); }
+};
+
 template <int WPB, int LDSCAP, bool CA>
 __global__ __launch_bounds__(256) void k_refine_async(RefineArgs a) {
   __shared__ WaveLds<LDSCAP> lds[WPB];
@@ -767,35 +782,22 @@ __global__ __launch_bounds__(256) void k_refine_async(RefineArgs a) {
     const unsigned long long small = __ballot(e1v - e0v <= kWave);
     const unsigned long long mid = __ballot(e1v - e0v <= kUnroll * kWave);
     // The singletons of the lanes with to != kNoComm join `to` (Sigma ts as
-    // scored; held: another vertex than `to` itself has been seen there).
-    // Every vertex of a changed bound starts alone, so such a vertex has joined
-    // `to`; then its representative is no longer isolated, can never leave, and
-    // `to` can never empty: the join needs no look at the old total.  Otherwise
-    // the join is made together with the claim (one round trip for both) and
-    // taken back when `to` had emptied or someone has joined the vertex
-    // meanwhile.  Returns the lanes whose target had emptied (they look again,
-    // with fresh labels; alone, with one wavefront, this never happens).
+    // scored; held: another vertex than `to` itself has been seen there, so
+    // that `to` never empties).  Returns the lanes whose target had emptied:
+    // they look again, with fresh labels (alone, with one wavefront, this never
+    // happens).
     auto join = [&](int to, double ts, bool held) {
       const bool go = to != kNoComm && ts != 0.0;
       bool empty = to != kNoComm && ts == 0.0, done = false;
       if (go) {
-        // claim the singleton: Sigma[cv] K -> 0 fails if someone joined it
-        unsigned long long *sc = (unsigned long long *)&a.Sig[cv];
-        const unsigned long long want = __double_as_longlong(kv);
-        const double old = held ? 1.0 : unsafeAtomicAdd(&a.Sig[to], kv);
-        const bool mine = atomicCAS(sc, want, 0ull) == want;
-        done = mine && old != 0.0;
+        SigmaMem mem{a.Sig};
+        const Join end = join_singleton(mem, cv, kv, to, a.K[to], held, ts >= hot);
+        done = end == Join::kDone;
+        empty = end == Join::kEmpty;
         if (done) {
-          if (held && ts < hot) unsafeAtomicAdd(&a.Sig[to], kv);
           st_int(&a.C[v], to);
           __hip_atomic_store(&a.CP[v], ((unsigned long long)(uint32_t)cbv << 32) | (uint32_t)to, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
-        } else if (!held) {
-          unsafeAtomicAdd(&a.Sig[to], -kv);
-          if (mine) {
-            unsafeAtomicAdd(&a.Sig[cv], kv);
-            empty = true;
-          }
         }
       }
       for (unsigned long long r = __ballot(done && held && ts >= hot); r; r &= r - 1) {
