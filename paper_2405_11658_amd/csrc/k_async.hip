@@ -785,8 +785,8 @@ __global__ __launch_bounds__(256) void k_refine_async(RefineArgs a) {
     // scored; held: another vertex than `to` itself has been seen there, so
     // that `to` never empties).  Returns the lanes whose target had emptied:
     // they look again, with fresh labels (alone, with one wavefront, this never
-    // happens).
-    auto join = [&](int to, double ts, bool held) {
+    // happens); came: the lanes that have joined.
+    auto join = [&](int to, double ts, bool held, unsigned long long &came) {
       const bool go = to != kNoComm && ts != 0.0;
       bool empty = to != kNoComm && ts == 0.0, done = false;
       if (go) {
@@ -804,9 +804,19 @@ __global__ __launch_bounds__(256) void k_refine_async(RefineArgs a) {
         const int k = __ffsll(r) - 1;
         pend_add(pd, a.Sig, lane_value(to, k), lane_value(kv, k), lane_value(ts, k) * eps);
       }
+      came = __ballot(done);
       return __ballot(empty);
     };
     int tries = 0;  // of the lane's vertex
+    // A vertex taken from m that is not decided after all has its turn later.
+    auto put_back = [&](int k) {
+      m |= 1ull << k;
+      if (lane() == k) {
+        tries -= 1;
+        nv -= 1;
+        ne -= (unsigned long long)(e1v - e0v);
+      }
+    };
     // Handles the next G candidates of at most NU wavefronts of edges, up to the
     // first larger one.
     auto group = [&](auto nu, auto ng) {
@@ -861,7 +871,8 @@ __global__ __launch_bounds__(256) void k_refine_async(RefineArgs a) {
           S[g][u] = c[g][u] != kEmpty ? ld_s<CA>(&a.Sig[c[g][u]]) : 0.0;
         }
       }
-      unsigned joined = 0;  // group members that an earlier one joins
+      unsigned joined = 0;  // group members that an earlier one joins, or sees again later
+      unsigned chosen = 0;  // those that are the earlier one's target
       int to = kNoComm;
       double ts = 0.0;
       bool held = false;
@@ -897,17 +908,29 @@ __global__ __launch_bounds__(256) void k_refine_async(RefineArgs a) {
               near |= j[h][u] == i && cb[h] == cb[g];
               if (c[h][u] == bc) S[h][u] += Ki;
             }
-            if (lane_value(cv, kk[h]) == bc) joined |= 1u << h;
-            else if (__ballot(near)) {
+            if (joined & (1u << h)) continue;
+            if (lane_value(cv, kk[h]) == bc) {
               joined |= 1u << h;
-              m |= 1ull << kk[h];
-              if (lane() == kk[h]) tries -= 1;
+              chosen |= 1u << h;
+            } else if (__ballot(near)) {
+              joined |= 1u << h;
+              put_back(kk[h]);
             }
           }
         }
       }
       if (!__ballot(to != kNoComm)) return;
-      m |= join(to, ts, held) & __ballot(tries < kRefineTries);
+      unsigned long long came;
+      const unsigned long long again = join(to, ts, held, came);
+      m |= again & __ballot(tries < kRefineTries);
+      // a target that its group member has not joined after all (another
+      // wavefront's vertex had joined that one) is still to be decided
+#pragma unroll
+      for (int h = 1; h < G; ++h)
+        if ((chosen >> h) & 1u) {
+          const int ch = lane_value(cv, kk[h]);
+          if (!(came & __ballot(to == ch))) put_back(kk[h]);
+        }
       if (!a.defer) wave_fence();  // one wavefront alone reads its own moves next
     };
     while (m) {
@@ -946,7 +969,9 @@ __global__ __launch_bounds__(256) void k_refine_async(RefineArgs a) {
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) seen |= eb.c[u] == bc && eb.j[u] != bc;
       const bool held = __ballot(seen) != 0;
-      m |= join(lane() == k ? bc : kNoComm, bs, held) & __ballot(tries < kRefineTries);
+      unsigned long long came;
+      const unsigned long long again = join(lane() == k ? bc : kNoComm, bs, held, came);
+      m |= again & __ballot(tries < kRefineTries);
       if (!a.defer) wave_fence();
     }
   }
