@@ -369,7 +369,8 @@ leiden_status leiden_fleet_destroy(leiden_fleet *fleet);
  * q_out (host) is 0 when the graph has no edges.  Stateless; the working
  * memory of this call and of leiden_aggregate is kept for their next calls
  * (at most 2 GiB a device, none that 16 calls have left unused; given back
- * when a handle is destroyed or an allocation of the library's fails). */
+ * when a handle is destroyed or an allocation fails, the library's own or a
+ * leiden_allocator's, which is then asked once more). */
 leiden_status leiden_modularity(int64_t n, const int64_t *offsets, const int32_t *indices,
                                 const float *weights, const int32_t *membership, double *q_out,
                                 void *stream);

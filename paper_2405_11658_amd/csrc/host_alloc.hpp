@@ -35,7 +35,8 @@ struct ScratchBlock {
 // its stream, so its blocks are idle then and any thread and stream of the
 // device may use them next.  Kept are at most kScratchKeep bytes and
 // kScratchBlocks blocks, none that the last kScratchAge calls left unused;
-// all of a device's go when an allocation fails on it or a handle is destroyed.
+// all of a device's go when an allocation fails on it (scratch_make_room) or a
+// handle is destroyed.
 constexpr size_t kScratchKeep = (size_t)2 << 30;
 constexpr int kScratchBlocks = 256;
 constexpr uint64_t kScratchAge = 16;
@@ -107,6 +108,20 @@ inline int stream_device(hipStream_t s) {
   return dev;
 }
 
+// Gives the kept blocks of the stream's device back to the system, for an
+// allocation that has failed, a caller's allocator's too.  False when there
+// were none, or when the stream is being captured (a release recorded there
+// would be made at each replay).
+inline bool scratch_make_room(int dev, hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap != hipStreamCaptureStatusNone || !scratch_cache().drop(dev, s)) return false;
+  if (hipStreamSynchronize(s) != hipSuccess) return false;
+  hipMemPool_t pool;
+  if (hipDeviceGetMemPool(&pool, dev) != hipSuccess || hipMemPoolTrimTo(pool, 0) != hipSuccess) (void)hipGetLastError();
+  return true;
+}
+
 // Device memory of a handle or of a stateless call: obtained from the
 // caller's allocator when one is given (leiden_allocator), else from HIP's
 // stream-ordered allocator (a stateless call: from its kept blocks first);
@@ -129,7 +144,11 @@ struct Alloc {
   }
   // *bytes: what is needed, then what the block holds
   void *get(size_t *bytes, hipStream_t s) {
-    if (custom) return a.alloc(a.ctx, *bytes, (void *)s);
+    if (custom) {
+      void *p = a.alloc(a.ctx, *bytes, (void *)s);
+      if (!p && scratch_make_room(stream_device(s), s)) p = a.alloc(a.ctx, *bytes, (void *)s);
+      return p;
+    }
     const bool list = scratch && dev >= 0 && nmine < kScratchBlocks / 2;
     ScratchBlock k;
     if (list && scratch_cache().take(dev, *bytes, &k)) {
@@ -138,9 +157,7 @@ struct Alloc {
       return k.p;
     }
     void *p = raw(*bytes, s);
-    // kept blocks of other calls make room
-    if (!p && scratch_cache().drop(scratch ? dev : stream_device(s), s) && hipStreamSynchronize(s) == hipSuccess)
-      p = raw(*bytes, s);
+    if (!p && scratch_make_room(scratch ? dev : stream_device(s), s)) p = raw(*bytes, s);
     if (p && list) mine[nmine++] = ScratchBlock{p, *bytes, dev, 0};
     return p;
   }

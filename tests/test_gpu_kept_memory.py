@@ -1,0 +1,93 @@
+"""GPU: the working memory that stateless calls keep is given back: to an
+allocation that fails (of the library's own or of a caller's allocator), when
+a handle is destroyed, and when later calls leave it unused."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2405_11658_amd import inputs as gen
+from paper_2405_11658_amd import leiden as L
+
+from .gpu_common import say, to_np
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+class _Scarce(L.TorchAllocator):
+    """torch's allocator, but it has no memory for the next `refuse` requests."""
+    refuse = 0
+
+    def _alloc(self, ctx, nbytes, stream):
+        if self.refuse > 0:
+            self.refuse -= 1
+            return None
+        return super()._alloc(ctx, nbytes, stream)
+
+
+def _free():
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _small():
+    g = gen.planted_partition(512, 8, 0.15, 0.01, seed=3)
+    return [torch.from_numpy(np.asarray(x)).cuda() for x in (g.off, g.idx, g.w)]
+
+
+def _keep():
+    """An aggregation that leaves working memory kept; the bytes kept."""
+    L.leiden_destroy(L.leiden_create(*_small()))  # nothing is kept now
+    n, deg = 1 << 16, 64
+    off = torch.arange(n + 1, device="cuda") * deg
+    idx = torch.randint(0, n, (n * deg,), device="cuda", dtype=torch.int32)
+    w = torch.ones(n * deg, device="cuda")
+    C = torch.arange(n, device="cuda", dtype=torch.int32) // 8
+    _free()
+    L.leiden_aggregate(off, idx, w, C, n // 8)
+    before = _free()
+    L.leiden_destroy(L.leiden_create(*_small()))
+    kept = _free() - before
+    L.leiden_aggregate(off, idx, w, C, n // 8)
+    assert kept > 16 * MIB  # 16 bytes an entry at least
+    return kept
+
+
+@pytest.fixture
+def scarce(monkeypatch):
+    al = _Scarce()
+    monkeypatch.setattr(L, "_torch_alloc", al)
+    yield al
+
+
+@pytest.mark.parametrize("what", ["handle", "fleet"])
+def test_a_callers_allocator_gets_the_kept_memory(scarce, what):
+    """A caller's allocator that has no memory is asked once more after the
+    kept blocks have gone, for a handle as for a fleet; with nothing kept its
+    refusal is the call's error."""
+    make = {"handle": lambda: L.leiden_create(*_small()), "fleet": lambda: L.Fleet([tuple(_small())])}[what]
+    kept = _keep()
+    free = _free()
+    scarce.refuse = 1
+    h = make()
+    assert scarce.refuse == 0
+    gone = _free() - free
+    say("kept", kept, "given back", gone)
+    assert gone > kept - 8 * MIB  # the new handle or fleet holds a few MiB
+    scarce.refuse = 1
+    with pytest.raises(L.LeidenError):
+        make()
+    del h
+
+
+def test_kept_memory_is_given_back_when_unused():
+    """Blocks that 16 calls have left unused go with the next one."""
+    kept = _keep()
+    small = _small()
+    C = torch.zeros(512, device="cuda", dtype=torch.int32)
+    free = _free()
+    for k in range(18):
+        L.leiden_modularity(*small, C)
+    assert _free() - free > kept - 8 * MIB
