@@ -1102,9 +1102,19 @@ leiden_status run_stateless(Workspace &w, hipStream_t s, const std::function<voi
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
   w.al.scratch = cap == hipStreamCaptureStatusNone;
   w.al.dev = stream_device(s);
-  const leiden_status st = run_guarded(w, f);
+  leiden_status st = run_guarded(w, f);
   w.release(s);
-  if (w.al.scratch) w.al.end(s);
+  if (!w.al.scratch) return st;
+  w.al.end(s);
+  // A kept block may be twice as large as what it holds, and a buffer that
+  // grows during the call leaves its old block listed: a call that found no
+  // memory is made once more with blocks of its own (nothing of the caller's
+  // is written before the last allocation)
+  if (st == LEIDEN_ENOMEM && scratch_make_room(w.al.dev, s)) {
+    w.al.scratch = false;
+    st = run_guarded(w, f);
+    w.release(s);
+  }
   return st;
 }
 

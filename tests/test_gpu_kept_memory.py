@@ -1,6 +1,8 @@
 """GPU: the working memory that stateless calls keep is given back: to an
 allocation that fails (of the library's own or of a caller's allocator), when
 a handle is destroyed, and when later calls leave it unused."""
+import ctypes as ct
+
 import numpy as np
 import pytest
 import torch
@@ -91,3 +93,47 @@ def test_kept_memory_is_given_back_when_unused():
     for k in range(18):
         L.leiden_modularity(*small, C)
     assert _free() - free > kept - 8 * MIB
+
+
+def test_kept_blocks_do_not_use_up_the_memory():
+    """A call whose kept blocks are larger than what it needs, and that has no
+    room for the rest beside them, gives them back and succeeds, as with
+    blocks of its own.  (Blocks of 131M entries for 125M, four of 4 bytes an
+    entry, and ~120 MiB of counters for the large communities' sort beside
+    them: 2030 MiB where kept blocks and free memory are ~2110.)"""
+    n, k = 1 << 16, 4096
+    nnz = 2000 * n
+    gen_ = torch.Generator(device="cuda").manual_seed(1)
+    idx = torch.randint(0, n, (nnz,), device="cuda", dtype=torch.int32, generator=gen_)
+    w = torch.ones(nnz, device="cuda")
+    C = (torch.arange(n, device="cuda") % k).to(torch.int32)
+    out = [torch.zeros(k + 1, dtype=torch.int64, device="cuda"),
+           torch.empty(nnz, dtype=torch.int32, device="cuda"), torch.empty(nnz, device="cuda")]
+    off = {d: torch.arange(n + 1, device="cuda") * d for d in (2000, 1900)}
+
+    def run(d):
+        got = ct.c_int64(0)
+        st = L.load().leiden_aggregate(n, *(L._ptr(x) for x in (off[d], idx, w, C)), k, *(L._ptr(x) for x in out),
+                                       ct.byref(got), L._stream())
+        torch.cuda.synchronize()
+        return st, got.value
+
+    st, m = run(1900)
+    assert st == L.OK
+    want = [out[0].clone(), out[1][:m].clone(), out[2][:m].clone()]
+    L.leiden_destroy(L.leiden_create(*_small()))
+    assert run(2000)[0] == L.OK
+    hold = [torch.empty(_free() - 512 * MIB, dtype=torch.uint8, device="cuda")]
+    try:  # all but the last few MiB, whatever the report said
+        while True:
+            hold.append(torch.empty(16 * MIB, dtype=torch.uint8, device="cuda"))
+    except torch.OutOfMemoryError:
+        pass
+    del hold[-6:]
+    torch.cuda.empty_cache()
+    say("free", torch.cuda.mem_get_info()[0] // MIB, "MiB")
+    st, m = run(1900)
+    del hold
+    torch.cuda.empty_cache()
+    assert st == L.OK
+    assert all(torch.equal(x, y) for x, y in zip(want, (out[0], out[1][:m], out[2][:m])))
