@@ -23,6 +23,15 @@ constexpr unsigned long long kNoKey = ~0ull;
 constexpr int kWaveEdges = 256;
 constexpr int kGroup = 2;
 
+// Sums of weights are taken in an order that follows from the graph and the
+// batch alone, not from the number of wavefronts or their timing, so that the
+// last bits of K, Sigma and the aggregated weights are the same on every run
+// and in every launch variant also where sums in 64 bits are rounded: passes
+// over items are split into kParts ranges for any number of wavefronts (a
+// divisor of kParts), and sums by community are added by one wavefront (one a
+// community), in the items' order.
+constexpr int kParts = 8;
+
 // LDS of one workgroup.
 template <int T, int SLOTS>
 struct FSh {
@@ -31,6 +40,8 @@ struct FSh {
   double rd[W];
   int ri[W];
   long long rl[W];
+  double partd[kParts];
+  long long partl[kParts];
   int flag;
   int cnt;
   int wide;             // the sweep's next vertex for the whole workgroup
@@ -42,6 +53,7 @@ struct FSh {
   double tvals[SLOTS];
   int tlist[SLOTS];
   int tcnt;
+  uint16_t mine[W][T];  // a wavefront's entries of a wide vertex's T
   // job state broadcast
   FleetJob job;
   FleetGraph g;
@@ -111,6 +123,44 @@ struct Blk {
   static __device__ __forceinline__ int64_t range_hi(int64_t n) {
     const int64_t per = ((n + kWave - 1) / kWave + W - 1) / W * kWave;
     return min(n, per * (wid() + 1));
+  }
+  // The parts of n items (of whole tiles of 64 too), this wavefront's being
+  // [kParts / W * wid(), kParts / W * (wid() + 1)).
+  static constexpr int kOwnParts = kParts / W;
+  static __device__ __forceinline__ int64_t part_lo(int64_t n, int p) {
+    const int64_t per = ((n + kWave - 1) / kWave + kParts - 1) / kParts * kWave;
+    return min(n, per * p);
+  }
+  // Sum of f(k) over k in [0, n), in every thread: each part by the lanes of
+  // one wavefront, then the parts in order.
+  template <class F>
+  static __device__ __forceinline__ double ordered_sum(int64_t n, Sh &s, F f) {
+    __syncthreads();
+    for (int p = kOwnParts * wid(); p < kOwnParts * (wid() + 1); ++p) {
+      double v = 0.0;
+      for (int64_t k = part_lo(n, p) + lane(); k < part_lo(n, p + 1); k += kWave) v += f(k);
+      v = wave_sum(v);
+      if (lane() == 0) s.partd[p] = v;
+    }
+    __syncthreads();
+    double t = 0.0;
+    for (int p = 0; p < kParts; ++p) t += s.partd[p];
+    __syncthreads();
+    return t;
+  }
+  // add(k, get(k)) for k in [0, n) in order, by the calling wavefront: four
+  // tiles' reads are issued together.
+  template <class G, class A>
+  static __device__ __forceinline__ void in_order(int64_t n, G get, A add) {
+    constexpr int kAhead = 4;
+    for (int64_t b = 0; b < n; b += kAhead * kWave) {
+      decltype(get((int64_t)0)) x[kAhead];
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q) x[q] = get(min(b + q * kWave + lane(), n - 1));
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q)
+        if (b + q * kWave + lane() < n) add(x[q]);
+    }
   }
   // Sum of x (uniform in each wavefront) over the wavefronts before this one;
   // the total in *tot.
@@ -322,6 +372,18 @@ struct Tab {
       key = s.tkeys[h];
       x = s.tvals[h];
     }
+  }
+  // the sum of a key (after a barrier following the inserts)
+  __device__ __forceinline__ double find(const Sh &s, int key) const {
+    if (dense) return ldx(&dv[key]);
+    uint32_t h = mix32((uint32_t)key) & (uint32_t)(SLOTS - 1);
+    for (int probe = 0; probe < SLOTS; ++probe) {
+      const int k = s.tkeys[h];
+      if (k == key) return s.tvals[h];
+      if (k == kEmpty) return 0.0;
+      h = (h + 1) & (uint32_t)(SLOTS - 1);
+    }
+    return 0.0;
   }
   // clears what was taken; ends with the table empty and a barrier
   __device__ __forceinline__ void clear(Sh &s) const {
@@ -577,6 +639,53 @@ struct FleetRun {
     return -1;
   }
 
+  // Weights of a wide vertex's edges by the neighbours' communities into the
+  // table (REFINE: of the neighbours inside the bound cb); returns the weight
+  // to d.  The workgroup loads T edges at a time and leaves them in LDS, where
+  // each wavefront lists those of its communities and adds them in order: a
+  // community's sum is one wavefront's.
+  template <bool REFINE>
+  __device__ __forceinline__ double table_row(const FLevel &L, const Tab<T, SLOTS> &t, int64_t e0, int64_t e1, int i,
+                                              int d, int cb) {
+    constexpr int W = T / kWave;
+    static_assert(sizeof(s.wcnt) >= 2 * T * sizeof(int), "staging");
+    int *sc = &s.wcnt[0][0];
+    float *sx = (float *)(sc + T);
+    const unsigned long long below = lane() == 0 ? 0ull : (~0ull >> (64 - lane()));
+    for (int64_t b = e0; b < e1; b += T) {
+      const int64_t e = b + B::tid();
+      int c = kEmpty;
+      float x = 0.0f;
+      if (e < e1) {
+        const int j = L.idx[e];
+        if (j != i && (!REFINE || g.CB[j] == cb)) {
+          c = g.Cl[j];
+          x = L.w[e];
+        }
+      }
+      sc[B::tid()] = c;
+      sx[B::tid()] = x;
+      __syncthreads();
+      int cnt = 0;
+#pragma unroll
+      for (int r = 0; r < W; ++r) {
+        const int k = r * kWave + lane();
+        const int ck = sc[k];
+        const bool mine = ck != kEmpty && (int)((mix32((uint32_t)ck) >> 16) % W) == B::wid();
+        const unsigned long long m = __ballot(mine);
+        if (mine) s.mine[B::wid()][cnt + __popcll(m & below)] = (uint16_t)k;
+        cnt += __popcll(m);
+      }
+      lds_fence();
+      for (int q = lane(); q < cnt; q += kWave) {
+        const int k = s.mine[B::wid()][q];
+        t.add(s, sc[k], (double)sx[k]);
+      }
+      __syncthreads();
+    }
+    return t.find(s, d);
+  }
+
   // ---------------- Alg. "leidenMove" (serial sweep) -----------------------
   // One wider vertex: best community by Eq. 2, applied at once.  Returns true
   // if it moved, with its gain in *gain.
@@ -585,16 +694,7 @@ struct FleetRun {
     const int d = g.Cl[i];
     const double Ki = g.Kl[i];
     const Tab<T, SLOTS> t = table(e1 - e0, L.n);
-    double own = 0.0;
-    for (int64_t e = e0 + B::tid(); e < e1; e += T) {
-      const int j = L.idx[e];
-      if (j == i) continue;
-      const int c = g.Cl[j];
-      const double x = (double)L.w[e];
-      t.add(s, c, x);
-      if (c == d) own += x;
-    }
-    const double b = B::sum_d(own, s);  // barrier: inserts complete
+    const double b = table_row<false>(L, t, e0, e1, i, d, 0);
     const int nk = s.tcnt;
     const double Sd = g.Sl[d];
     double bg = 0.0;
@@ -670,16 +770,7 @@ struct FleetRun {
     const int cb = g.CB[i];
     const double Ki = g.Kl[i];
     const Tab<T, SLOTS> t = table(e1 - e0, L.n);
-    double own = 0.0;
-    for (int64_t e = e0 + B::tid(); e < e1; e += T) {
-      const int j = L.idx[e];
-      if (j == i || g.CB[j] != cb) continue;
-      const int cj = g.Cl[j];
-      const double x = (double)L.w[e];
-      t.add(s, cj, x);
-      if (cj == c) own += x;
-    }
-    const double b = B::sum_d(own, s);
+    const double b = table_row<true>(L, t, e0, e1, i, c, cb);
     const int nk = s.tcnt;
     const double Sd = g.Sl[c];
     double bg = 0.0;
@@ -781,10 +872,10 @@ struct FleetRun {
   // Super-vertex CSR of L under dense labels Cl (< nc) into level buffer ob,
   // K' (row sums of the stored float weights, in row order) into Kl.
   // Entries are sorted by (C[u], C[v]) with a stable sort: a pair's entries
-  // in member-then-CSR order, summed in FP64 by each wavefront that holds some.
-  // Three passes of the sort, one to count the pairs, one to write them: 420k
-  // entries 160 -> 13 ms in 8 wavefronts, all levels of an update, at
-  // the latency of a few loads a wavefront.
+  // in member-then-CSR order, summed in FP64.  The entries are read five times
+  // (three passes of the sort, one to count the pairs, one to write them), each
+  // time at the latency of a few loads a wavefront: all levels of an update of
+  // 420k entries 160 -> 13 ms with 8 wavefronts.
   __device__ __forceinline__ FLevel aggregate(const FLevel &L, int64_t nc, int ob) {
     unsigned long long *key[2] = {g.akey[0], g.akey[1]};
     int32_t *pay[2] = {g.apay[0], g.apay[1]};
@@ -802,39 +893,63 @@ struct FleetRun {
     const int r = B::sort(key, pay, L.nnz, nc > 1 ? 2 * kb : 0, s);
     const unsigned long long *sk = key[r];
     const int32_t *sp = pay[r];
-    // distinct keys of this wavefront's range, and of those before it
-    const int64_t lo = B::range_lo(L.nnz), hi = B::range_hi(L.nnz);
-    auto head = [&](int64_t t) { return t < hi && (t == 0 || sk[t] != sk[t - 1]); };
-    long long heads = 0, nu;
-    for (int64_t b = lo; b < hi; b += kWave) heads += __popcll(__ballot(head(b + lane())));
-    int64_t at = B::before(heads, &nu, s);
+    // distinct keys of each part, and of those before it
+    auto head = [&](int64_t t, int64_t hi) { return t < hi && (t == 0 || sk[t] != sk[t - 1]); };
+    const int p0 = B::kOwnParts * B::wid(), p1 = p0 + B::kOwnParts;
+    for (int p = p0; p < p1; ++p) {
+      const int64_t hi = B::part_lo(L.nnz, p + 1);
+      long long heads = 0;
+      for (int64_t b = B::part_lo(L.nnz, p); b < hi; b += kWave) heads += __popcll(__ballot(head(b + lane(), hi)));
+      if (lane() == 0) s.partl[p] = heads;
+    }
+    __syncthreads();
+    auto heads_before = [&](int p) {
+      int64_t k = 0;
+      for (int q = 0; q < p; ++q) k += s.partl[q];
+      return k;
+    };
+    const int64_t nu = heads_before(kParts);
     int64_t *off = g.loff[ob];
     int32_t *idx = g.lidx[ob];
     float *w = g.lw[ob];
     double *sum = g.asum;
     for (int64_t o = B::tid(); o < nu; o += T) sum[o] = 0.0;
     __syncthreads();
-    // entries of the new rows: the wavefront's entries of a key summed in
-    // order, then added to its other wavefronts'
-    for (int64_t b = lo; b < hi; b += kWave) {
-      const int64_t t = b + lane();
-      const bool in = t < hi;
-      const unsigned long long kk = in ? sk[t] : 0ull;
-      double x = in ? (double)L.w[sp[t]] : 0.0;
-      const bool first = head(t);
-      const unsigned long long hm = __ballot(first);
-      const int64_t o = at + __popcll(hm & (~0ull >> (63 - lane()))) - 1;
-      if (first) {
-        idx[o] = (int32_t)(kk & ((1ull << kb) - 1ull));
-        const int64_t row = (int64_t)(kk >> kb);
-        for (int64_t c = t == 0 ? 0 : (int64_t)(sk[t - 1] >> kb) + 1; c <= row; ++c) off[c] = o;
+    // entries of the new rows: a part's entries of a key are summed in order;
+    // the key that a part goes on with is left to the end
+    for (int p = p0; p < p1; ++p) {
+      const int64_t hi = B::part_lo(L.nnz, p + 1), first_own = heads_before(p);
+      int64_t at = first_own;
+      double lead = 0.0;
+      for (int64_t b = B::part_lo(L.nnz, p); b < hi; b += kWave) {
+        const int64_t t = b + lane();
+        const bool in = t < hi;
+        const unsigned long long kk = in ? sk[t] : 0ull;
+        double x = in ? (double)L.w[sp[t]] : 0.0;
+        const bool first = head(t, hi);
+        const unsigned long long hm = __ballot(first);
+        const int64_t o = at + __popcll(hm & (~0ull >> (63 - lane()))) - 1;
+        if (first) {
+          idx[o] = (int32_t)(kk & ((1ull << kb) - 1ull));
+          const int64_t row = (int64_t)(kk >> kb);
+          for (int64_t c = t == 0 ? 0 : (int64_t)(sk[t - 1] >> kb) + 1; c <= row; ++c) off[c] = o;
+        }
+        int f = first || lane() == 0;
+        wave_seg_scan(x, f);
+        const bool last = in && (lane() == kWave - 1 || t + 1 >= hi || ((hm >> (lane() + 1)) & 1ull));
+        if (last) {
+          if (o < first_own) lead += x;
+          else unsafeAtomicAdd(&sum[o], x);
+        }
+        at += __popcll(hm);
       }
-      int f = first || lane() == 0;
-      wave_seg_scan(x, f);
-      const bool last = in && (lane() == kWave - 1 || t + 1 >= hi || ((hm >> (lane() + 1)) & 1ull));
-      if (last) unsafeAtomicAdd(&sum[o], x);
-      at += __popcll(hm);
+      lead = wave_sum(lead);
+      if (lane() == 0) s.partd[p] = lead;
     }
+    __syncthreads();
+    if (B::tid() == 0)
+      for (int p = 1; p < kParts; ++p)
+        if (s.partd[p] != 0.0) unsafeAtomicAdd(&sum[heads_before(p) - 1], s.partd[p]);
     // rows after the last one with an entry
     const int64_t past = L.nnz > 0 ? (int64_t)(sk[L.nnz - 1] >> kb) + 1 : 0;
     for (int64_t c = past + B::tid(); c <= nc; c += T) off[c] = nu;
@@ -1116,17 +1231,24 @@ struct FleetRun {
     __syncthreads();
     for (int64_t i = B::tid(); i < n; i += T) g.rng[i] = (mode == 2) ? g.U[i] : 1;
     // updateWeights: K and Sigma of the previous membership, and 2m
-    double dm = 0.0;
-    for (int64_t t = B::tid(); t < E; t += T) {
-      const int u = (int)(sk[t] / (unsigned long long)n);
-      const bool del = sp[t] < 2 * nd;
-      const double x = (double)job.bw[sp[t]];
-      unsafeAtomicAdd(&g.K[u], del ? -x : x);
-      unsafeAtomicAdd(&g.Sig[g.C[u]], del ? -x : x);
-      dm += del ? -x : x;
+    auto change = [&](int64_t t) { return sp[t] < 2 * nd ? -(double)job.bw[sp[t]] : (double)job.bw[sp[t]]; };
+    if (B::wid() == 0) {
+      struct Item {
+        int u, c;
+        double x;
+      };
+      B::in_order(
+          E,
+          [&](int64_t t) {
+            const int u = (int)(sk[t] / (unsigned long long)n);
+            return Item{u, g.C[u], change(t)};
+          },
+          [&](const Item &m) {
+            unsafeAtomicAdd(&g.K[m.u], m.x);
+            unsafeAtomicAdd(&g.Sig[m.c], m.x);
+          });
     }
-    dm = B::sum_d(dm, s);
-    __syncthreads();
+    const double dm = B::ordered_sum(E, s, change);
     if (B::tid() == 0) g.M2 = g.M2 + dm;
     __syncthreads();
     long long aff = 0;
@@ -1143,9 +1265,8 @@ struct FleetRun {
     const int32_t *idx = g.idx[g.cur];
     const float *w = g.w[g.cur];
     double *sig = g.dense;   // holds 0 between uses
+    double *inside = g.S2;   // of each row (free after the pass loop)
     for (int64_t c = B::tid(); c < n; c += T) g.Sig[c] = 0.0;
-    __syncthreads();
-    for (int64_t i = B::tid(); i < n; i += T) unsafeAtomicAdd(&g.Sig[g.C[i]], ldx(&g.K[i]));
     const int32_t *C = g.C;
     B::rows(n, off, [&](auto width, int64_t u, int64_t, int64_t e1, int64_t first, bool there) {
       constexpr int N = decltype(width)::value;
@@ -1161,18 +1282,31 @@ struct FleetRun {
         in += dpp_move<kDppXor2>(in);
         in += dpp_move<kDppHalfMirror>(in);
       }
-      if (there && lane() % N == 0 && in != 0.0) unsafeAtomicAdd(&sig[cu], in);
+      if (there && lane() % N == 0) inside[u] = in;
     });
     __syncthreads();
+    // the communities' sums: two wavefronts where there are two
+    struct Item {
+      int c;
+      double x;
+    };
+    if (B::wid() == 0)
+      B::in_order(
+          n, [&](int64_t i) { return Item{C[i], ldx(&g.K[i])}; },
+          [&](const Item &m) { unsafeAtomicAdd(&g.Sig[m.c], m.x); });
+    if (B::wid() == (B::W > 1 ? 1 : 0))
+      B::in_order(
+          n, [&](int64_t i) { return Item{C[i], ldx(&inside[i])}; },
+          [&](const Item &m) {
+            if (m.x != 0.0) unsafeAtomicAdd(&sig[m.c], m.x);
+          });
     const double M2 = g.M2;
-    double q = 0.0;
-    for (int64_t c = B::tid(); c < n; c += T) {
+    const double q = B::ordered_sum(n, s, [&](int64_t c) {
       const double sc = ldx(&sig[c]);
       const double a = ldx(&g.Sig[c]) / M2;
-      if (M2 > 0.0) q += sc / M2 - a * a;
       sig[c] = 0.0;
-    }
-    q = B::sum_d(q, s);
+      return M2 > 0.0 ? sc / M2 - a * a : 0.0;
+    });
     return M2 > 0.0 ? q : 0.0;
   }
 
@@ -1211,9 +1345,7 @@ struct FleetRun {
         g.U[i] = 1;
         g.rng[i] = 1;
       }
-      double m2 = 0.0;
-      for (int64_t i = B::tid(); i < n; i += T) m2 += g.K[i];
-      m2 = B::sum_d(m2, s);
+      const double m2 = B::ordered_sum(n, s, [&](int64_t i) { return g.K[i]; });
       if (B::tid() == 0) g.M2 = m2;
       __syncthreads();
       M2 = m2;
