@@ -332,7 +332,7 @@ leiden_status leiden_server_destroy(leiden_server *server);
  * serial reading of the paper's algorithms, and independent of the launch
  * variant (leiden_fleet_set_variant: wavefronts per workgroup and LDS table
  * slots, a speed choice only; leiden_fleet_variant_info describes it; without
- * one the library chooses by the number of jobs of a run).
+ * one, and with -1, the library chooses by the number of jobs of a run).
  * params: as for leiden_create (sync_mode, nslices, async_waves, hub_slices
  * and profile are not used; max_passes <= 16).  alloc as for leiden_create.
  *
@@ -359,7 +359,7 @@ leiden_status leiden_fleet_get_graph(leiden_fleet *fleet, int32_t graph, int64_t
                                      float *weights, int64_t *nnz /* host */, void *stream);
 leiden_status leiden_fleet_get_state(leiden_fleet *fleet, int32_t graph, int32_t *membership, double *K,
                                      double *Sigma, double *m2 /* host */, void *stream);
-leiden_status leiden_fleet_set_variant(leiden_fleet *fleet, int32_t variant /* 0 .. 5 */);
+leiden_status leiden_fleet_set_variant(leiden_fleet *fleet, int32_t variant /* 0 .. 6, or -1 */);
 leiden_status leiden_fleet_variant_info(int32_t variant, int32_t *waves /* host */, int32_t *slots /* host */);
 int32_t leiden_fleet_count(const leiden_fleet *fleet);
 const char *leiden_fleet_last_error(const leiden_fleet *fleet);

@@ -134,7 +134,7 @@ struct leiden_fleet {
   void *pin = nullptr;              // pinned staging (jobs up, results down)
   size_t pin_cap = 0;
   hipStream_t cap_stream = nullptr; // stream used to capture the launch
-  hipGraphExec_t exec[kFleetLaunches] = {};  // captured launch per variant
+  hipGraphExec_t exec[kFleetVariants] = {};  // captured launch per variant
   hipEvent_t t0 = nullptr, t1 = nullptr;
   hipStream_t last = nullptr;
   bool used = false;           // a call has enqueued work (recorded in `order`)
@@ -439,7 +439,7 @@ leiden_status leiden_fleet_destroy(leiden_fleet *f) {
 }
 
 leiden_status leiden_fleet_set_variant(leiden_fleet *f, int32_t variant) {
-  if (!f || variant < 0 || variant >= kFleetVariants) return LEIDEN_EINVAL;
+  if (!f || variant < -1 || variant >= kFleetVariants) return LEIDEN_EINVAL;
   f->variant = variant;
   return LEIDEN_OK;
 }

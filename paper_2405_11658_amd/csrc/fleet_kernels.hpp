@@ -102,18 +102,16 @@ struct FleetLaunch {
 // entries (vertices with up to slots / 2 neighbouring communities use it, by
 // their degree or the level's vertices, others the graph's dense global
 // table).
-constexpr int kFleetVariants = 6;
+constexpr int kFleetVariants = 7;
 struct FleetVariant {
   int waves;
   int slots;
 };
 constexpr FleetVariant kFleetVariant[kFleetVariants] = {{1, 512}, {2, 512}, {4, 512},
-                                                        {1, 2048}, {2, 2048}, {4, 2048}};
-// The variants of a fleet that none was chosen for (workgroups of 8 wavefronts
-// with 2048 slots, beside the caller's variants, and one of those).
-constexpr int kFleetWide = kFleetVariants;
+                                                        {1, 2048}, {2, 2048}, {4, 2048}, {8, 2048}};
+// The variants that the library chooses between.
+constexpr int kFleetWide = 6;
 constexpr int kFleetMany = 2;
-constexpr int kFleetLaunches = kFleetVariants + 1;
 // Enqueue the persistent launch with `blocks` workgroups of variant v.
 hipError_t fleet_launch(const FleetLaunch &L, int variant, int blocks, hipStream_t s);
 

@@ -484,7 +484,7 @@ def leiden_num_entries(h: Handle) -> int:
 
 
 FLEET_STATIC = 0
-FLEET_VARIANTS = 6
+FLEET_VARIANTS = 7
 
 
 def fleet_variant_info(v: int):
@@ -530,6 +530,7 @@ class Fleet:
             raise LeidenError(st, f"{what}: {msg}")
 
     def set_variant(self, v: int):
+        """Launch variant 0 .. FLEET_VARIANTS - 1, or -1: the library's choice."""
         self._err(load().leiden_fleet_set_variant(self.ptr, int(v)), "leiden_fleet_set_variant")
 
     def run(self, jobs, want_membership: bool = True):
