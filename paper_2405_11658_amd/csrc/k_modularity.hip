@@ -68,7 +68,8 @@ __global__ __launch_bounds__(256) void k_mod_edges(const int64_t *off, const int
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       if (c[k] == cr[k]) sig += (double)x[k];
-      int f = lane() == 0 || lane_before(r[k]) != r[k];
+      const int before = lane_before(r[k]);  // by all lanes, not behind the ||
+      int f = lane() == 0 || before != r[k];
       const unsigned long long starts = __ballot(f);
       double row = (double)x[k];
       wave_seg_scan(row, f);
