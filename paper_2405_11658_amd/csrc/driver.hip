@@ -159,9 +159,10 @@ constexpr int64_t kVertsPerWaveUpper = 256;  // the same for the aggregated leve
 constexpr int kStallIters = 3;  // see the iteration loop of run_core
 
 // Wavefronts of an asynchronous sweep over a level with n vertices that have
-// edges: at most `cap`, and few enough that the vertices in flight stay a
-// small fraction of the level (with much of a level in flight the sweep
-// degenerates into a synchronous update that oscillates and loses modularity).
+// edges: at most `cap`, and few enough that the vertices in flight, up to two
+// a wavefront, stay a small fraction of the level (with much of a level in
+// flight the sweep degenerates into a synchronous update that oscillates and
+// loses modularity).
 // The first level decides most of the final modularity; the aggregated ones
 // tolerate four times as many vertices in flight.
 // Larger per-wavefront LDS tables when the level's average degree is high.

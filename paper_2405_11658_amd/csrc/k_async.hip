@@ -4,13 +4,18 @@
 // that read the live membership and community weights and apply their moves
 // at once (Sec. 4.6: asynchronous, with atomics on Sigma).  Here a fixed
 // number of wavefronts sweep the vertex ids in ascending order, each taking
-// the next chunk of ids from a global counter; a wavefront processes the
-// vertices of its chunk one after another, so the vertices in flight at any
-// time are at most one per wavefront.  Every vertex reads the current C and
-// Sigma (agent-scope loads, not a stale L1 line), builds its neighbour
-// community table in LDS (degree <= 256) or in a global-memory region of the
-// wavefront (degree <= 2048), and applies its best move immediately: C store,
-// Sigma atomics, neighbours marked unprocessed.  Changes to the Sigma of the
+// the next chunk of ids from a global counter; a wavefront takes the vertices
+// of its chunk in order, two of at most 64 edges at a time and larger ones
+// singly, so the vertices in flight at any time are at most two per wavefront.
+// Every vertex reads the current C and Sigma (agent-scope loads, not a stale
+// L1 line), the second of two on what the first one's move makes of them,
+// sums its neighbours' communities in an LDS table (degree <= 256) or in a
+// global-memory region of the wavefront (degree <= 2048), and applies its best
+// move immediately: C store, Sigma atomics, neighbours marked unprocessed.
+// Of the chunk's later vertices those that the wavefront's own moves have
+// marked are taken up in the same iteration; marks of other wavefronts that
+// come after the chunk was read are for the next one (a vertex of more than
+// 256 edges reads the flags again after its move).  Changes to the Sigma of the
 // few communities holding a large share of the weight are summed per
 // wavefront and added every few chunks (Pend below).  Vertices of higher
 // degree are handled before the sweep by the multi-workgroup hub kernels.
@@ -432,13 +437,14 @@ __device__ __forceinline__ void best_move(const WaveTable &t, double M2, int d, 
 // move; then all moves are made at once, by the lanes that hold the vertices,
 // so that their atomics wait for memory together.  (One wavefront alone
 // follows the serial sweep exactly: one vertex at a time.)  On a level of 4096
-// vertices and 4 wavefronts: refinement 2.7 -> 0.9 us a vertex (1.25 with
-// groups of 1, 0.98 of 8), local moving 1.1 -> 0.6 us, both in groups of 4;
-// 4096 wavefronts end at the rate of their random reads, ~45e9 a second.  The
-// modularity is that of single vertices (R-MAT scale 22, ten updates: 0.0703
-// and 0.0705, sd 1e-4) also where a batch changes a tenth of the edges (R-MAT
-// scale 20: 0.127 to 0.128, sd 0.0015 to 0.0018, for groups of 1 and 2); there
-// groups of 4 ended below 0.115 in 9 of 144 runs, of 1 and 2 in none of 96.
+// vertices and 4 wavefronts, us a vertex: refinement 2.7 -> 1.03, local moving
+// 1.1 -> 0.68; 4096 wavefronts end at the rate of their random reads, ~45e9 a
+// second.  Modularity of single vertices as they were and of groups of 2, means
+// of 300 static runs (R-MAT scale 16, 18, 20): 0.09022 and 0.09025, 0.08298 and
+// 0.08294, 0.07665 and 0.07661; where a batch changes a tenth of the edges
+// (scale 20, two batches, ND, DS and DF, 288 runs): 0.1263 and 0.1260, sd
+// 0.0027, the lowest runs 0.113 and 0.111.  Groups of 4 ended below 0.115 there
+// in 9 of 144 runs.
 constexpr int kGroup = 2;
 
 // A wavefront takes kGrabChunks chunks of kAsyncChunk list positions at a
@@ -496,12 +502,11 @@ __global__ __launch_bounds__(256) void k_move_async(MoveArgs a) {
     const int64_t base = grab(a.anext, gr);
     if (base >= a.alen) break;
     // each lane fetches the state of one vertex of the chunk; the chunk's
-    // unprocessed vertices are then handled one after another by the whole
-    // wavefront, in list order.  A vertex is marked processed at its turn, and
-    // after a move the flags of the chunk's later vertices are read again, so
-    // that one wavefront alone follows the serial sweep exactly (a vertex
-    // re-marked by an earlier vertex of its chunk is handled in the same
-    // iteration).
+    // unprocessed vertices are then handled by the whole wavefront, in list
+    // order.  A vertex is marked processed at its turn, and a later vertex of
+    // the chunk that a move marks is handled in the same iteration, so that
+    // one wavefront alone, which takes them singly, follows the serial sweep
+    // exactly.
     const int64_t p = base + lane();
     int v = 0, dv = 0;
     int64_t e0v = 0, e1v = 0;

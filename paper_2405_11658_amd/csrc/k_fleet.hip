@@ -30,6 +30,7 @@ constexpr int kGroup = 2;
 // over items are split into kParts ranges for any number of wavefronts (a
 // divisor of kParts), and sums by community are added by one wavefront (one a
 // community), in the items' order.
+// 512 graphs of up to 30,000 vertices: 165 ms, as the wavefronts came 162.
 constexpr int kParts = 8;
 
 // LDS of one workgroup.
@@ -203,7 +204,7 @@ struct Blk {
   // first is `first`): 8 lanes for rows of up to 64 entries, a wavefront for
   // longer ones.  there: the lanes hold a row.  A wavefront a row, most rows
   // being of a few dozen entries, waited out three loads a row: copying 30000
-  // rows 37 -> 5.7 ms, their modularity 40 -> 2.6 ms (8 rows at a time, and 8
+  // rows 37 -> 5.7 ms, their modularity 40 -> 2.8 ms (8 rows at a time, and 8
   // wavefronts).
   template <class F>
   static __device__ __forceinline__ void rows(int64_t n, const int64_t *off, F f) {
@@ -875,7 +876,7 @@ struct FleetRun {
   // in member-then-CSR order, summed in FP64.  The entries are read five times
   // (three passes of the sort, one to count the pairs, one to write them), each
   // time at the latency of a few loads a wavefront: all levels of an update of
-  // 420k entries 160 -> 13 ms with 8 wavefronts.
+  // 420k entries 160 -> 14 ms with 8 wavefronts.
   __device__ __forceinline__ FLevel aggregate(const FLevel &L, int64_t nc, int ob) {
     unsigned long long *key[2] = {g.akey[0], g.akey[1]};
     int32_t *pay[2] = {g.apay[0], g.apay[1]};

@@ -199,8 +199,6 @@ __device__ __forceinline__ uint32_t pow2_at_least(uint64_t x) {
   return c;
 }
 
-// Team argmax over TEAM threads (TEAM = 64 or a multiple); result in t == 0.
-
 // ---- propose: a team (wavefront or workgroup) per vertex, hash table of T
 // slots per team in LDS.
 template <int TEAM, int T, int BLOCK>
