@@ -161,9 +161,9 @@ def _pmc(db: str, counter: str):
     return con.execute(q, (counter,)).fetchall()
 
 
-def summarize_counters(db: str, command: str, kernels=("lk::k_move_async", "void lk::k_move_async",
-                                                       "void lk::k_refine_async", "lk::k_agg_small",
-                                                       "void lk::k_rs_scatter", "lk::k_agg_group")) -> str:
+def summarize_counters(db: str, command: str, kernels=("void lk::k_move_async", "void lk::k_refine_async",
+                                                       "void lk::k_agg_small", "void lk::k_rs_scatter",
+                                                       "lk::k_agg_group")) -> str:
     """Per-kernel sums of every counter of a counter run over the dynamic
     updates, with the derived ratios used in the design notes."""
     import sqlite3
