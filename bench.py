@@ -175,7 +175,8 @@ def summarize_counters(db: str, command: str, kernels=("void lk::k_move_async", 
     for name, cn, v, c in con.execute(q, (win[0], win[1])).fetchall():
         for pre in kernels:
             if name.startswith(pre):
-                agg.setdefault(pre, {})[cn] = (v, c)
+                had = agg.setdefault(pre, {}).get(cn, (0.0, 0))  # of a kernel's other instantiations
+                agg[pre][cn] = (had[0] + v, had[1] + c)
     out = ["Command:", "", "    " + command, "", f"Dynamic updates: {win[2]}; counter sums per update.", ""]
     for k, cs in agg.items():
         out.append(f"### `{k}`")
